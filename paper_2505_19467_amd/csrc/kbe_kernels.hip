@@ -1856,376 +1856,294 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
 }
 
 // ------------------------------------------------------------------ row assembly and update
-// Thread per (k, t'), t' <= m.
+// A block carries 64 consecutive t' of one k; its wavefront w = sc NB + a carries row a of
+// component sc (2 NB wavefronts, lane = t').
 //  EVAL/CORRECT, t' < m: I^{<,>}(t_m, t') = dt [bulk + end-point terms], where the
 //   trapezoid corrections of the two integrals of eq. (CI) are
 //     + 1/2 SR_mm G_{m t'} - 1/2 SR_m0 G_{0 t'}                                  (first, [0, t_m])
 //     + [t' > 0] (-1/2 Sigma_{m t'} GR_{t' t'} + 1/2 Sigma_{m0} GR_{0 t'})       (second, [0, t'])
 //   with GR = G^> - G^<, G_{0 t'} = -(G_{t' 0})^dag.
-//  PREDICT/CORRECT/UPDATE, t' < m: G(t_m, t') = V G(t_{m-1}, t') + Phi Ibar(t') (UPDATE: the
-//   corrector's update with I(t_m, t') read back from an EVAL launch's output).
-//  PREDICT/CORRECT/UPDATE, t' = m: rho_m = V rho_{m-1} V^dag - dt Vh Dbar Vh^dag and the
+//  PREDICT/CORRECT, t' < m: G(t_m, t') = V G(t_{m-1}, t') + Phi Ibar(t').
+//  PREDICT/CORRECT, t' = m: rho_m = V rho_{m-1} V^dag - dt Vh Dbar Vh^dag and the
 //   equal-time block G^< = i rho_m, G^> = -i (1 - rho_m).
-// G_{j t'} (both components) for the end corrections of output t' < m: the diagonal from the
-// band copy; stored blocks j > t' from the ring of recent rows (row m: the current iterate) or
-// the column copies (j < qp); blocks above the diagonal as -G_{t' j}^dag from the column copies
-// (j < qp) or the band (t' - j < qp). Every node the corrections visit is one of these.
-// Component sc (nb^2 entries) of the block G(t_j, t') an end-point correction needs, from the
-// copies that hold it (as end_block, for one component).
+// Bound: HBM, then the latency of the loads. With whole nb x nb blocks in one thread the kernel
+// held 118-500 registers, one to four waves per SIMD, and at nb = 4 needed a separate pass that summed
+// the strips' row partials and a corrector split into two launches; a matrix row per wavefront needs
+// NB complex accumulators, makes Sigma(t_m, t_m), Sigma(t_m, t_0), V and Phi wavefront-uniform (scalar
+// loads), and spreads the gather of the row partials over all wavefronts. What several rows need
+// (G_{0 t'}, GR_{t' t'}, the gathered row partials; then Ibar and G(t_{m-1}, t')) is loaded once per
+// block and passed through LDS. Averages, before -> now: evaluation 9.9 -> 7.1 us (144 points, nb = 2,
+// m <= 400), 127 -> 116 us (576 points, nb = 2, m = 1000, 5.1 TB/s), 318 (with the row-partial pass) -> 196 us
+// (256 points, nb = 4, m = 800, 5.1 TB/s); corrector with four Gregory nodes 86 -> 30 us (63 points, nb = 3,
+// m <= 150).
+//
+// Gregory corrections: element (a, b) of component sc of the block G(t_j, t') an end correction of
+// output t' < m needs: the diagonal from the band copy; stored blocks j > t' from the ring of recent
+// rows (row m: the current iterate) or the column copies (j < qp); blocks above the diagonal as
+// -G_{t' j}^dag from the column copies (j < qp) or the band (t' - j < qp). Every node the
+// corrections visit is in one of these.
 template <int NB>
-__device__ __forceinline__ void end_block1(const Dims& d, const cplx* __restrict__ row64, const cplx* __restrict__ colq,
-                                           const cplx* __restrict__ band, int k, int m, int j, int tp, int sc,
-                                           cplx* G) {
-  constexpr int NBB = NB * NB;
-  if (j == tp) {
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) G[e] = band[band_idx(d, k, sc * NBB + e, tp, 0)];
-  } else if (j > tp) {
-    if (j > m - d.rring) {
-#pragma unroll
-      for (int e = 0; e < NBB; ++e) G[e] = row64[row64_idx(d, j, k, sc * NBB + e, tp)];
-    } else {
-#pragma unroll
-      for (int e = 0; e < NBB; ++e) G[e] = colq[colq_idx(d, k, sc * NBB + e, j, tp)];
-    }
-  } else {
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        int cs = sc * NBB + b * NB + a;
-        cplx v = j < d.qp ? colq[colq_idx(d, k, cs, tp, j)] : band[band_idx(d, k, cs, tp, tp - j)];
-        G[a * NB + b] = cneg(cconj(v));
+struct EndBlock {
+  const cplx* p;     // component 0
+  int64_t stride;    // one component further
+  bool flip;         // element (a, b) is -conj of the stored (b, a)
+  __device__ __forceinline__ EndBlock(const Dims& d, const cplx* __restrict__ row64, const cplx* __restrict__ colq,
+                                      const cplx* __restrict__ band, int k, int m, int j, int tp) {
+    flip = j < tp;
+    stride = (int64_t)d.qp * d.Tp;
+    if (j == tp) {
+      p = band + band_idx(d, k, 0, tp, 0);
+    } else if (j > tp) {
+      if (j > m - d.rring) {
+        p = row64 + row64_idx(d, j, k, 0, tp);
+        stride = d.Tp;
+      } else {
+        p = colq + colq_idx(d, k, 0, j, tp);
       }
-  }
-}
-template <int NB>
-__device__ __forceinline__ void end_block(const Dims& d, const cplx* __restrict__ row64, const cplx* __restrict__ colq,
-                                          const cplx* __restrict__ band, int k, int m, int j, int tp, cplx* G) {
-  constexpr int NBB = NB * NB, C = 2 * NBB;
-  if (j == tp) {
-#pragma unroll
-    for (int c = 0; c < C; ++c) G[c] = band[band_idx(d, k, c, tp, 0)];
-  } else if (j > tp) {
-    if (j > m - d.rring) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) G[c] = row64[row64_idx(d, j, k, c, tp)];
     } else {
-#pragma unroll
-      for (int c = 0; c < C; ++c) G[c] = colq[colq_idx(d, k, c, j, tp)];
+      p = j < d.qp ? colq + colq_idx(d, k, 0, tp, j) : band + band_idx(d, k, 0, tp, tp - j);
     }
-  } else {
-#pragma unroll
-    for (int sc = 0; sc < 2; ++sc)
-#pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          int cs = sc * NBB + b * NB + a;
-          cplx v = j < d.qp ? colq[colq_idx(d, k, cs, tp, j)] : band[band_idx(d, k, cs, tp, tp - j)];
-          G[sc * NBB + a * NB + b] = cneg(cconj(v));
-        }
   }
-}
-
-// Threads per (k, t') of the row kernel: one carrying both components G^<, G^> (nb <= 3), or at
-// nb = 4 two, lanes 2i and 2i + 1 carrying G^< and G^> (the state of both, 32 complex numbers in
-// each of several rows, would not fit one thread's registers).
-template <int NB>
-struct RowSplit {
-  static constexpr int SCN = NB == 4 ? 1 : 2;   // components per thread
-  static constexpr int TPT = 2 / SCN;           // threads per (k, t')
-  static constexpr int TPB = 256 / TPT;         // t' per block of 256 threads
-  // nb = 4: the strips' row partials are summed into slot 0 by k_rowpart_fold before the row
-  // kernel runs (at one wave per SIMD, the row kernel's serial gather of up to n_t / 64 slots
-  // would be latency-bound)
-  static constexpr bool FOLD = NB == 4;
-  // nb = 4: a corrector pass runs as EVAL (the collision row, stored) + UPDATE (the update from
-  // the stored row), two waves per SIMD each without spills: the fused kernel holds 256 VGPRs +
-  // 100 AGPRs, one wave per SIMD
-  static constexpr bool CSPLIT = NB == 4;
+  __device__ __forceinline__ cplx at(int sc, int a, int b) const {
+    cplx v = p[(sc * NB * NB + (flip ? b * NB + a : a * NB + b)) * stride];
+    return flip ? cneg(cconj(v)) : v;
+  }
 };
 
-// Row term of the history sums at nb = 4: the per-strip partials of row t' (slots 0 .. t' / 64)
-// summed in slot order into slot 0, one thread per (k, entry, t'). Each slot-0 element is read
-// and written by its own thread only, so the fold is in place; it runs once after each history
-// pass, and the row kernels then read slot 0 alone. The sum has the order of the row kernels'
-// own gather, so the result is the same.
-template <int NB>
-__global__ __launch_bounds__(256) void k_rowpart_fold(Dims d, cplx* __restrict__ rowpart, int m) {
-  const int nblk = (m + 255) / 256;           // blocks per (k, entry)
-  const int ke = blockIdx.x / nblk;           // k * nb^2 + entry
-  const int tp = (blockIdx.x - ke * nblk) * 256 + threadIdx.x;
-  const int k = ke / (NB * NB), e = ke - k * (NB * NB);
-  if (tp >= m) return;
-  const int nslot = (tp >> 6) / d.spb + 1;
-  if (nslot == 1) return;
-  const int64_t off = (int64_t)e * d.Tp + tp;
-  cplx* p0 = rowpart + (int64_t)k * d.Smax * d.nbb * d.Tp + off;   // slot 0 of (k, e, t')
-  const int64_t step = (int64_t)d.nbb * d.Tp;                         // one slot further
-  cplx s = p0[0];
-  int q = 1;
-  for (; q + 4 <= nslot; q += 4) {
-    cplx v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = p0[(q + u) * step];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) s = cadd(s, v[u]);
-  }
-  for (; q < nslot; ++q) s = cadd(s, p0[q * step]);
-  p0[0] = s;
-}
-
 template <int NB, int MODE, bool GREG>
-__global__ __launch_bounds__(256) void k_row(Dims d, void* __restrict__ hist, cplx* __restrict__ row64,
-                                             const cplx* __restrict__ sig, const cplx* __restrict__ colsum,
-                                             const cplx* __restrict__ rowpart, cplx* __restrict__ col0,
-                                             cplx* __restrict__ diag, const cplx* __restrict__ Iprev,
-                                             cplx* __restrict__ Icur, const cplx* __restrict__ props,
-                                             const cplx* __restrict__ rho_prev, cplx* __restrict__ rho_cur,
-                                             const cplx* __restrict__ Dprev, const cplx* __restrict__ Dcur, int m,
-                                             double dt, int commit, double* __restrict__ chg, QuadW Q) {
+__global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ hist, cplx* __restrict__ row64,
+                                                  const cplx* __restrict__ sig, const cplx* __restrict__ colsum,
+                                                  const cplx* __restrict__ rowpart, cplx* __restrict__ col0,
+                                                  cplx* __restrict__ diag, const cplx* __restrict__ Iprev,
+                                                  cplx* __restrict__ Icur, const cplx* __restrict__ props,
+                                                  const cplx* __restrict__ rho_prev, cplx* __restrict__ rho_cur,
+                                                  const cplx* __restrict__ Dprev, const cplx* __restrict__ Dcur, int m,
+                                                  double dt, int commit, double* __restrict__ chg, QuadW Q) {
   constexpr int NBB = NB * NB;
-  constexpr int SCN = RowSplit<NB>::SCN, TPT = RowSplit<NB>::TPT;
-  constexpr bool UPD = MODE == KBE_ROW_UPDATE || MODE == KBE_ROW_UPDATE_CHG;   // I(t_m, .) stored
-  constexpr bool CHG = MODE == KBE_ROW_CORRECT || MODE == KBE_ROW_UPDATE_CHG;  // change output
+  constexpr bool INT = MODE == KBE_ROW_CORRECT || MODE == KBE_ROW_EVAL;   // collision row
+  constexpr bool UPD = MODE != KBE_ROW_EVAL;                              // update of the row
+  __shared__ cplx lds[4 * NBB * 64];
   const int k = blockIdx.y;
-  const int tp = blockIdx.x * RowSplit<NB>::TPB + threadIdx.x / TPT;
-  const int sc0 = SCN == 1 ? (threadIdx.x & 1) : 0;   // first component of this thread
-  if (tp > m) return;   // (both lanes of a pair leave together)
-  if (MODE == KBE_ROW_EVAL && tp == m) return;
-  const cplx* P = props + (int64_t)k * 3 * NBB;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sc = w / NB, a = w - (w / NB) * NB;
+  const int tp = blockIdx.x * 64 + lane;
+  const bool in = tp < m;
   double dmax = 0.0;
-  if (tp < m) {
-    cplx rs[NBB];   // row partials of the history sums, shared by both components (gathered after
-                    // the first component's end-point terms, which need the registers more)
+  cplx In[NB];   // the collision row over dt
+  if constexpr (INT) {
+    cplx* s0 = lds;                    // G(t_0, t') of both components: G_00, or -G(t', t_0)^dag
+    cplx* sR = lds + 2 * NBB * 64;     // GR_{t' t'}
+    cplx* sP = lds + 3 * NBB * 64;     // row partials of the history sums, summed over the slots
+    if (in) {
+      if constexpr (!GREG) {
 #pragma unroll
-    for (int ls = 0; ls < SCN; ++ls) {
-      const int sc = sc0 + ls;
-      cplx In[NBB];
-      if (MODE == KBE_ROW_CORRECT || MODE == KBE_ROW_EVAL) {
-        // end-point terms of component sc, accumulated term by term
-        cplx E[NBB];
-        mat_zero<NB>(E);
-        if constexpr (!GREG) {
-          // trapezoid: half weights at j = 0 and j = m (first integral), j = 0 and j = t' (second)
-          {
-            cplx SRmm[NBB], Gm[NBB];
-#pragma unroll
-            for (int e = 0; e < NBB; ++e) {
-              SRmm[e] = cscal(sig[sig_idx(d, k, 2, e, m)], 0.5);
-              Gm[e] = row64[row64_idx(d, m, k, sc * NBB + e, tp)];
-            }
-            mm_acc<NB>(E, SRmm, Gm);
-          }
-          // G(t_0, t') of both components: G_00, or -G(t', t_0)^dag
-          auto g0 = [&](int c, int a, int b) {
-            return tp == 0 ? col0[colq_idx(d, k, c * NBB + a * NB + b, 0, 0)]
-                           : cneg(cconj(col0[colq_idx(d, k, c * NBB + b * NB + a, tp, 0)]));
-          };
-          {
-            cplx SRm0[NBB], G0[NBB];
-#pragma unroll
-            for (int a = 0; a < NB; ++a)
-#pragma unroll
-              for (int b = 0; b < NB; ++b) {
-                SRm0[a * NB + b] = cscal(sig[sig_idx(d, k, 2, a * NB + b, 0)], -0.5);
-                G0[a * NB + b] = g0(sc, a, b);
-              }
-            mm_acc<NB>(E, SRm0, G0);
-          }
-          if (tp > 0) {
-            cplx St[NBB], GRtt[NBB];
-#pragma unroll
-            for (int e = 0; e < NBB; ++e) {
-              St[e] = cscal(sig[sig_idx(d, k, sc, e, tp)], -0.5);
-              GRtt[e] = csub(diag[band_idx(d, k, NBB + e, tp, 0)], diag[band_idx(d, k, e, tp, 0)]);
-            }
-            mm_acc<NB>(E, St, GRtt);
-            cplx S0[NBB], GR0t[NBB];
-#pragma unroll
-            for (int a = 0; a < NB; ++a)
-#pragma unroll
-              for (int b = 0; b < NB; ++b) {
-                S0[a * NB + b] = cscal(sig[sig_idx(d, k, sc, a * NB + b, 0)], 0.5);
-                GR0t[a * NB + b] = csub(g0(1, a, b), g0(0, a, b));
-              }
-            mm_acc<NB>(E, S0, GR0t);
-          }
-        } else {
-          // Gregory end corrections (d.qp nodes per end): against the bulk's unit weights,
-          //   E = sum_j (w^(m)_j - [j < m]) SR_mj G_jt'  +  sum_{j <= t'} (w^(t')_j - [j < t']) Sigma_mj GA_jt',
-          // nonzero on the nodes j < q' and j > N - q' of each interval (q' = min(qp, N + 1)).
-          const int qm = d.qp < m + 1 ? d.qp : m + 1;
-          for (int r = 0; r < 2; ++r) {
-            int j0 = r == 0 ? 0 : (qm > m - qm + 1 ? qm : m - qm + 1);
-            int j1 = r == 0 ? qm : m + 1;
-            for (int j = j0; j < j1; ++j) {
-              double w = quad_w(Q, j, m) - (j < m ? 1.0 : 0.0);
-              if (w == 0.0) continue;
-              cplx G[NBB], SR[NBB];
-              end_block1<NB>(d, row64, col0, diag, k, m, j, tp, sc, G);
-#pragma unroll
-              for (int e = 0; e < NBB; ++e) SR[e] = cscal(sig[sig_idx(d, k, 2, e, j)], w);
-              mm_acc<NB>(E, SR, G);
-            }
-          }
-          if (tp > 0) {
-            const int qt = d.qp < tp + 1 ? d.qp : tp + 1;
-            for (int r = 0; r < 2; ++r) {
-              int j0 = r == 0 ? 0 : (qt > tp - qt + 1 ? qt : tp - qt + 1);
-              int j1 = r == 0 ? qt : tp + 1;
-              for (int j = j0; j < j1; ++j) {
-                double w = quad_w(Q, j, tp) - (j < tp ? 1.0 : 0.0);
-                if (w == 0.0) continue;
-                cplx GA[NBB], Gg[NBB], S[NBB];
-                end_block1<NB>(d, row64, col0, diag, k, m, j, tp, 0, GA);
-                end_block1<NB>(d, row64, col0, diag, k, m, j, tp, 1, Gg);
-#pragma unroll
-                for (int e = 0; e < NBB; ++e) {
-                  GA[e] = csub(GA[e], Gg[e]);  // -(G^> - G^<)
-                  S[e] = cscal(sig[sig_idx(d, k, sc, e, j)], w);
-                }
-                mm_acc<NB>(E, S, GA);
-              }
-            }
-          }
+        for (int b = 0; b < NB; ++b) {
+          cplx v = tp == 0 ? col0[colq_idx(d, k, sc * NBB + a * NB + b, 0, 0)]
+                           : cneg(cconj(col0[colq_idx(d, k, sc * NBB + b * NB + a, tp, 0)]));
+          s0[(sc * NBB + a * NB + b) * 64 + lane] = v;
         }
-        if (ls == 0) {
-          mat_zero<NB>(rs);
-          const int nslot = RowSplit<NB>::FOLD ? 1 : (tp >> 6) / d.spb + 1;
-          // slots in groups of 4: the loads of a group are issued together
+      }
+      // the two wavefronts of row a share its entries b
+#pragma unroll
+      for (int h = 0; h < (NB + 1) / 2; ++h) {
+        const int b = 2 * h + sc;
+        if (b < NB) {
+          const int e = a * NB + b;
+          if constexpr (!GREG)
+            sR[e * 64 + lane] = csub(diag[band_idx(d, k, NBB + e, tp, 0)], diag[band_idx(d, k, e, tp, 0)]);
+          // slots in order, in groups of 4 whose loads are issued together
+          const int nslot = (tp >> 6) / d.spb + 1;
+          const cplx* rp = rowpart_slot(d, rowpart, k, 0) + (int64_t)e * d.Tp + tp;
+          const int64_t step = (int64_t)d.nbb * d.Tp;
+          cplx rs = czero();
           int q = 0;
           for (; q + 4 <= nslot; q += 4) {
-            cplx v[4][NBB];
+            cplx v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const cplx* rp = rowpart_slot(d, rowpart, k, q + u);
+            for (int u = 0; u < 4; ++u) v[u] = rp[(q + u) * step];
 #pragma unroll
-              for (int e = 0; e < NBB; ++e) v[u][e] = rp[(int64_t)e * d.Tp + tp];
+            for (int u = 0; u < 4; ++u) rs = cadd(rs, v[u]);
+          }
+          for (; q < nslot; ++q) rs = cadd(rs, rp[q * step]);
+          sP[e * 64 + lane] = rs;
+        }
+      }
+    }
+    __syncthreads();
+    if (in) {
+      // end-point terms of row a of component sc, accumulated term by term
+      cplx E[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) E[b] = czero();
+      // E += f S G: S[a][l] of Sigma component cs at t_j, G[l][b] from g(l, b)
+      auto term = [&](int cs, int j, double f, auto g) {
+        cplx S[NB];
+#pragma unroll
+        for (int l = 0; l < NB; ++l) S[l] = cscal(sig[sig_idx(d, k, cs, a * NB + l, j)], f);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int l = 0; l < NB; ++l) cmac(E[b], S[l], g(l, b));
+      };
+      if constexpr (!GREG) {
+        // trapezoid: half weights at j = 0 and j = m (first integral), j = 0 and j = t' (second)
+        term(2, m, 0.5, [&](int l, int b) { return row64[row64_idx(d, m, k, sc * NBB + l * NB + b, tp)]; });
+        term(2, 0, -0.5, [&](int l, int b) { return s0[(sc * NBB + l * NB + b) * 64 + lane]; });
+        if (tp > 0) {
+          term(sc, tp, -0.5, [&](int l, int b) { return sR[(l * NB + b) * 64 + lane]; });
+          term(sc, 0, 0.5, [&](int l, int b) {
+            return csub(s0[(NBB + l * NB + b) * 64 + lane], s0[(l * NB + b) * 64 + lane]);
+          });
+        }
+      } else {
+        // Gregory end corrections (d.qp nodes per end): against the bulk's unit weights,
+        //   E = sum_j (w^(m)_j - [j < m]) SR_mj G_jt'  +  sum_{j <= t'} (w^(t')_j - [j < t']) Sigma_mj GA_jt',
+        // nonzero on the nodes j < q' and j > N - q' of each interval (q' = min(qp, N + 1)).
+        const int qm = d.qp < m + 1 ? d.qp : m + 1;
+        for (int r = 0; r < 2; ++r) {
+          int j0 = r == 0 ? 0 : (qm > m - qm + 1 ? qm : m - qm + 1);
+          int j1 = r == 0 ? qm : m + 1;
+          for (int j = j0; j < j1; ++j) {
+            double wgt = quad_w(Q, j, m) - (j < m ? 1.0 : 0.0);
+            if (wgt == 0.0) continue;
+            const EndBlock<NB> G(d, row64, col0, diag, k, m, j, tp);
+            term(2, j, wgt, [&](int l, int b) { return G.at(sc, l, b); });
+          }
+        }
+        if (tp > 0) {
+          const int qt = d.qp < tp + 1 ? d.qp : tp + 1;
+          for (int r = 0; r < 2; ++r) {
+            int j0 = r == 0 ? 0 : (qt > tp - qt + 1 ? qt : tp - qt + 1);
+            int j1 = r == 0 ? qt : tp + 1;
+            for (int j = j0; j < j1; ++j) {
+              double wgt = quad_w(Q, j, tp) - (j < tp ? 1.0 : 0.0);
+              if (wgt == 0.0) continue;
+              const EndBlock<NB> G(d, row64, col0, diag, k, m, j, tp);
+              term(sc, j, wgt, [&](int l, int b) { return csub(G.at(0, l, b), G.at(1, l, b)); });   // -(G^> - G^<)
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-              for (int e = 0; e < NBB; ++e) rs[e] = cadd(rs[e], v[u][e]);
-          }
-          for (; q < nslot; ++q) {
-            const cplx* rp = rowpart_slot(d, rowpart, k, q);
-#pragma unroll
-            for (int e = 0; e < NBB; ++e) rs[e] = cadd(rs[e], rp[(int64_t)e * d.Tp + tp]);
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < NBB; ++e) {
-          In[e] = cscal(cadd(cadd(colsum[rowbuf_idx(d, k, sc * NBB + e, tp)], rs[e]), E[e]), dt);
-          Icur[rowbuf_idx(d, k, sc * NBB + e, tp)] = In[e];
-        }
-      }
-      if (MODE != KBE_ROW_EVAL) {
-        // G(t_m, t') = V G(t_{m-1}, t') + Phi Ibar(t') for component sc
-        cplx Ib[NBB], Go[NBB], g[NBB];
-#pragma unroll
-        for (int e = 0; e < NBB; ++e) {
-          cplx ip = Iprev[rowbuf_idx(d, k, sc * NBB + e, tp)];
-          if constexpr (UPD) In[e] = Icur[rowbuf_idx(d, k, sc * NBB + e, tp)];
-          Ib[e] = (MODE == KBE_ROW_PREDICT) ? ip : cscal(cadd(ip, In[e]), 0.5);
-          Go[e] = row64[row64_idx(d, m - 1, k, sc * NBB + e, tp)];
-        }
-        mat_zero<NB>(g);
-        {
-          cplx V[NBB];
-#pragma unroll
-          for (int e = 0; e < NBB; ++e) V[e] = P[e];
-          mm_acc<NB>(g, V, Go);
-        }
-        {
-          cplx Phi[NBB];
-#pragma unroll
-          for (int e = 0; e < NBB; ++e) Phi[e] = P[2 * NBB + e];
-          mm_acc<NB>(g, Phi, Ib);
-        }
-#pragma unroll
-        for (int e = 0; e < NBB; ++e) {
-          const int c = sc * NBB + e;
-          if (CHG && chg) {  // change against the iterate this pass started from
-            cplx dg = csub(g[e], row64[row64_idx(d, m, k, c, tp)]);
-            dmax = fmax(dmax, sqrt(dg.x * dg.x + dg.y * dg.y));
-          }
-          row64[row64_idx(d, m, k, c, tp)] = g[e];
-          if (commit) {
-            commit_store(d, hist, k, c, m, tp, g[e]);
-            if (tp < d.qp) col0[colq_idx(d, k, c, m, tp)] = g[e];
-            if (m - tp < d.qp) diag[band_idx(d, k, c, m, m - tp)] = g[e];
           }
         }
       }
-    }
-  } else if (sc0 == 0) {
-    // tp == m, PREDICT or CORRECT: density matrix and equal-time block (one thread per k)
-    cplx V[NBB], Vh[NBB], r0[NBB], Db[NBB], t1[NBB], rho[NBB], t2[NBB];
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) {
-      V[e] = P[e];
-      Vh[e] = P[NBB + e];
-      r0[e] = rho_prev[(int64_t)k * NBB + e];
-      cplx dp = Dprev[(int64_t)k * NBB + e];
-      Db[e] = (MODE == KBE_ROW_PREDICT) ? dp : cscal(cadd(dp, Dcur[(int64_t)k * NBB + e]), 0.5);
-    }
-    mat_zero<NB>(t1);
-    mm_acc<NB>(t1, V, r0);
-    mat_zero<NB>(rho);
-    mm_acc_bdag<NB>(rho, t1, V);
-    mat_zero<NB>(t1);
-    mm_acc<NB>(t1, Vh, Db);
-    mat_zero<NB>(t2);
-    mm_acc_bdag<NB>(t2, t1, Vh);
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        int e = a * NB + b;
-        cplx rv = csub(rho[e], cscal(t2[e], dt));
-        rho_cur[(int64_t)k * NBB + e] = rv;
-        cplx gg[2];
-        gg[0] = cmuli(rv);
-        gg[1] = cneg(cmuli(csub(cmk(a == b ? 1.0 : 0.0, 0.0), rv)));
+        const int e = a * NB + b;
+        In[b] = cadd(cadd(colsum[rowbuf_idx(d, k, sc * NBB + e, tp)], sP[e * 64 + lane]), E[b]);
+        Icur[rowbuf_idx(d, k, sc * NBB + e, tp)] = cscal(In[b], dt);
+      }
+    }
+  }
+  if constexpr (UPD) {
+    const cplx* P = props + (int64_t)k * 3 * NBB;
+    cplx* sI = lds + sc * NBB * 64;                // Ibar of this component
+    cplx* sG = lds + (2 + sc) * NBB * 64;          // G(t_{m-1}, t')
+    if constexpr (INT) __syncthreads();            // the first part's LDS is free
+    if (in) {
 #pragma unroll
-        for (int sc = 0; sc < 2; ++sc) {
-          int c = sc * NBB + e;
-          if (CHG && chg) {
-            cplx dg = csub(gg[sc], row64[row64_idx(d, m, k, c, m)]);
-            dmax = fmax(dmax, sqrt(dg.x * dg.x + dg.y * dg.y));
-          }
-          row64[row64_idx(d, m, k, c, m)] = gg[sc];
-          if (commit) {
-            commit_store(d, hist, k, c, m, m, gg[sc]);
-            diag[band_idx(d, k, c, m, 0)] = gg[sc];
-            if (m < d.qp) col0[colq_idx(d, k, c, m, m)] = gg[sc];
+      for (int b = 0; b < NB; ++b) {
+        const int e = a * NB + b;
+        cplx ip = Iprev[rowbuf_idx(d, k, sc * NBB + e, tp)];
+        if constexpr (INT) ip = cscal(cmk(fma(In[b].x, dt, ip.x), fma(In[b].y, dt, ip.y)), 0.5);
+        sI[e * 64 + lane] = ip;
+        sG[e * 64 + lane] = row64[row64_idx(d, m - 1, k, sc * NBB + e, tp)];
+      }
+    }
+    __syncthreads();
+    if (tp <= m) {
+      cplx g[NB];   // the new row a of component sc
+      if (in) {
+        cplx V[NB], Phi[NB];
+#pragma unroll
+        for (int l = 0; l < NB; ++l) {
+          V[l] = P[a * NB + l];
+          Phi[l] = P[2 * NBB + a * NB + l];
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          g[b] = czero();
+#pragma unroll
+          for (int l = 0; l < NB; ++l) cmac(g[b], V[l], sG[(l * NB + b) * 64 + lane]);
+#pragma unroll
+          for (int l = 0; l < NB; ++l) cmac(g[b], Phi[l], sI[(l * NB + b) * 64 + lane]);
+        }
+      } else {
+        // t' = m: row a of rho_m = (V rho) V^dag - dt (Vh Dbar) Vh^dag, the same in both components
+        cplx t1[NB], t2[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          t1[b] = t2[b] = czero();
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            const int e = l * NB + b;
+            cplx db = Dprev[(int64_t)k * NBB + e];
+            if (MODE != KBE_ROW_PREDICT) db = cscal(cadd(db, Dcur[(int64_t)k * NBB + e]), 0.5);
+            cmac(t1[b], P[a * NB + l], rho_prev[(int64_t)k * NBB + e]);
+            cmac(t2[b], P[NBB + a * NB + l], db);
           }
         }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          cplx r = czero(), x = czero();
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            cmacc(r, t1[l], P[b * NB + l]);
+            cmacc(x, t2[l], P[NBB + b * NB + l]);
+          }
+          cplx rv = cmk(fma(x.x, -dt, r.x), fma(x.y, -dt, r.y));
+          if (sc == 0) rho_cur[(int64_t)k * NBB + a * NB + b] = rv;
+          g[b] = sc == 0 ? cmuli(rv) : cneg(cmuli(csub(cmk(a == b ? 1.0 : 0.0, 0.0), rv)));
+        }
       }
-  }
-  if (CHG && chg) {
-    if constexpr (TPT == 2) dmax = fmax(dmax, __shfl_xor(dmax, 1));   // the pair's two components
-    if (sc0 == 0) chg[(int64_t)k * d.Tp + tp] = dmax;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int c = sc * NBB + a * NB + b;
+        if (MODE == KBE_ROW_CORRECT && chg) {  // change against the iterate this pass started from
+          cplx dg = csub(g[b], row64[row64_idx(d, m, k, c, tp)]);
+          dmax = fmax(dmax, sqrt(dg.x * dg.x + dg.y * dg.y));
+        }
+      }
+      // a corrector wavefront reads only its own row of the old iterate above, but the end-point
+      // terms of every row read the whole block: they are behind a block barrier
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int c = sc * NBB + a * NB + b;
+        row64[row64_idx(d, m, k, c, tp)] = g[b];
+        if (commit) {
+          commit_store(d, hist, k, c, m, tp, g[b]);
+          if (tp < d.qp) col0[colq_idx(d, k, c, m, tp)] = g[b];
+          if (m - tp < d.qp) diag[band_idx(d, k, c, m, m - tp)] = g[b];
+        }
+      }
+    }
+    if (MODE == KBE_ROW_CORRECT && chg) {   // one value per block: its largest change
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
+      __syncthreads();
+      double* red = reinterpret_cast<double*>(lds);
+      if (lane == 0) red[w] = dmax;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        for (int i = 1; i < 2 * NB; ++i) dmax = fmax(dmax, red[i]);
+        chg[(int64_t)k * gridDim.x + blockIdx.x] = dmax;
+      }
+    }
   }
 }
 
-// Largest change of the corrector's row: out[0] = max over k and t' <= m of chg[k][t'].
+// Largest change of the corrector's row: out[0] = max over the row kernel's n blocks.
 // One block, a fixed reduction order (max is exact, so any order gives the same value).
-__global__ __launch_bounds__(1024) void k_change_max(const double* __restrict__ chg, int nk, int Tp, int m,
-                                                     double* __restrict__ out) {
-  __shared__ double red[1024];
+__global__ __launch_bounds__(1024) void k_change_max(const double* __restrict__ chg, int n, double* __restrict__ out) {
+  __shared__ double red[16];
   double mx = 0.0;
-  for (int k = 0; k < nk; ++k)
-    for (int t = threadIdx.x; t <= m; t += 1024) mx = fmax(mx, chg[(int64_t)k * Tp + t]);
-  red[threadIdx.x] = mx;
+  for (int i = threadIdx.x; i < n; i += 1024) mx = fmax(mx, chg[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < 16; ++i) mx = fmax(mx, red[i]);
+    out[0] = mx;
   }
-  if (threadIdx.x == 0) out[0] = red[0];
 }
 
 // ------------------------------------------------------------------ dipole kick
@@ -2424,6 +2342,9 @@ static hipError_t allow_lds(const void* kern, size_t bytes) {
   return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Blocks of 64 t' per k of the row kernel: t' < m in the evaluation mode, t' <= m otherwise.
+static int row_tiles(int m, int mode) { return mode == KBE_ROW_EVAL ? (m + 63) / 64 : m / 64 + 1; }
+
 template <int NB>
 struct Launch {
   static hipError_t init(const Dims& d, const LaunchArgs& a, hipStream_t st) {
@@ -2515,44 +2436,18 @@ struct Launch {
     }
     return hipGetLastError();
   }
-  static hipError_t fold(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-    if constexpr (RowSplit<NB>::FOLD) {
-      if (m < 65) return hipSuccess;   // one strip: nothing to fold
-      hipLaunchKernelGGL(k_rowpart_fold<NB>, dim3((m + 255) / 256 * NB * NB * d.nk), dim3(256), 0, st, d,
-                         a.rowpart, m);
-      return hipGetLastError();
-    }
-    return hipSuccess;
-  }
   static hipError_t row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st) {
-    dim3 grid((m + 1 + RowSplit<NB>::TPB - 1) / RowSplit<NB>::TPB, d.nk);
-#define KBE_ROW_ARGS                                                                                      \
-  d, a.hist, a.row64, (const cplx*)a.sig, (const cplx*)a.colsum, (const cplx*)a.rowpart, a.col0, a.diag, \
-      (const cplx*)a.I_prev, a.I_cur, (const cplx*)a.props, (const cplx*)a.rho_prev, a.rho_cur,           \
-      (const cplx*)a.D_prev, (const cplx*)a.D_cur, m, a.dt, a.commit, a.chg, a.quad
     // the trapezoid's end terms are a fixed handful; Gregory corrections loop over their nodes
-    if (d.qp > 1) {
-      if (mode == KBE_ROW_PREDICT)
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_PREDICT, true>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-      else if (mode == KBE_ROW_CORRECT && !RowSplit<NB>::CSPLIT)
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_CORRECT, true>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-      else
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_EVAL, true>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-    } else {
-      if (mode == KBE_ROW_PREDICT)
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_PREDICT, false>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-      else if (mode == KBE_ROW_CORRECT && !RowSplit<NB>::CSPLIT)
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_CORRECT, false>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-      else
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_EVAL, false>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-    }
-    if (mode == KBE_ROW_CORRECT && RowSplit<NB>::CSPLIT) {
-      if (a.chg)
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_UPDATE_CHG, false>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-      else
-        hipLaunchKernelGGL((k_row<NB, KBE_ROW_UPDATE, false>), grid, dim3(256), 0, st, KBE_ROW_ARGS);
-    }
-#undef KBE_ROW_ARGS
+    auto kern = mode == KBE_ROW_PREDICT ? k_row<NB, KBE_ROW_PREDICT, false>   // (no end terms)
+                : mode == KBE_ROW_CORRECT
+                    ? (d.qp > 1 ? k_row<NB, KBE_ROW_CORRECT, true> : k_row<NB, KBE_ROW_CORRECT, false>)
+                    : (d.qp > 1 ? k_row<NB, KBE_ROW_EVAL, true> : k_row<NB, KBE_ROW_EVAL, false>);
+    const int tiles = row_tiles(m, mode);
+    if (tiles == 0) return hipSuccess;
+    hipLaunchKernelGGL(kern, dim3(tiles, d.nk), dim3(128 * NB), 0, st, d, a.hist, a.row64, (const cplx*)a.sig,
+                       (const cplx*)a.colsum, (const cplx*)a.rowpart, a.col0, a.diag, (const cplx*)a.I_prev, a.I_cur,
+                       (const cplx*)a.props, (const cplx*)a.rho_prev, a.rho_cur, (const cplx*)a.D_prev,
+                       (const cplx*)a.D_cur, m, a.dt, a.commit, a.chg, a.quad);
     return hipGetLastError();
   }
   static hipError_t obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st) {
@@ -2613,14 +2508,11 @@ hipError_t launch_diag_I(const Dims& d, const LaunchArgs& a, int m, hipStream_t 
 hipError_t launch_bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
   KBE_DISPATCH(d.nb, bulk(d, a, m, st));
 }
-hipError_t launch_rowpart_fold(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-  KBE_DISPATCH(d.nb, fold(d, a, m, st));
-}
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st) {
   KBE_DISPATCH(d.nb, row(d, a, m, mode, st));
 }
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_change_max, dim3(1), dim3(1024), 0, st, chg, d.nk, d.Tp, m, out);
+  hipLaunchKernelGGL(k_change_max, dim3(1), dim3(1024), 0, st, chg, d.nk * row_tiles(m, KBE_ROW_CORRECT), out);
   return hipGetLastError();
 }
 hipError_t launch_obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st) {

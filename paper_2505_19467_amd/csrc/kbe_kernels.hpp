@@ -14,11 +14,6 @@
 #define KBE_ROW_PREDICT 0
 #define KBE_ROW_CORRECT 1
 #define KBE_ROW_EVAL 2
-// the corrector's update alone, from the I(t_m, .) an EVAL launch has just stored (launch_row
-// runs a corrector pass at nb = 4 as EVAL + UPDATE: kernels of two waves per SIMD, where the
-// fused one fits one); UPDATE_CHG also writes the row's largest change (tolerance mode)
-#define KBE_ROW_UPDATE 3
-#define KBE_ROW_UPDATE_CHG 4
 
 namespace kbe {
 
@@ -46,7 +41,7 @@ struct LaunchArgs {
   double* mu;
   double* obs;
   int commit;      // 0: the row kernel writes only the FP64 working row (recomputation)
-  double* chg;     // if set, the corrector row kernel writes max |G_new - G_old| per (k, t') here ([k][Tp])
+  double* chg;     // if set, the corrector row kernel writes max |G_new - G_old| of each of its blocks here
   cplx* gR;        // interband self-energy: real-space lines of row m, [t_j][comp][ab][R] (else null)
   QuadW quad;      // quadrature weights of eq. (CI)
   double Ax, Ay;  // A(t) * pol for the launch at hand
@@ -67,11 +62,8 @@ hipError_t launch_kick(const Dims& d, const LaunchArgs& a, int m, double kc, dou
                        hipStream_t st);
 hipError_t launch_diag_I(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
 hipError_t launch_bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
-// after each history pass at nb = 4 (a no-op otherwise): sums the strips' row partials into slot 0,
-// which the row kernels then read alone; not idempotent, so exactly once per history pass
-hipError_t launch_rowpart_fold(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st);
-// out[0] = max over k and t' <= m of chg[k][t'] (one block, deterministic)
+// out[0] = max of the row kernel's per-block changes at row m (one block, deterministic)
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st);
 hipError_t launch_obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st);
 hipError_t launch_aux(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
