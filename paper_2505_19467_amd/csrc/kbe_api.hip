@@ -32,6 +32,12 @@ struct Layout {
   size_t ws_bytes, hist_bytes, obs_bytes;
 };
 
+// What the reverse sweep takes of a configuration (the pulse kind aside).
+bool adjoint_config(const kbe_config* c) {
+  return c->precision == KBE_FP64 && c->n_corr == 1 && c->corr_tol == 0.0 && c->quad_points <= 1 && c->nb <= 2 &&
+         c->interaction == KBE_INT_HUBBARD && c->nkx <= 64;
+}
+
 int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   if (!c) { *why = "null config"; return KBE_ERR_INVALID_ARG; }
   if (c->nb < 1 || c->nb > 4) { *why = "nb must be 1..4"; return KBE_ERR_SHAPE; }
@@ -82,7 +88,7 @@ int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   sz[B_IA] = sz[B_IB] = nk * d.C * d.Tp * cz;
   sz[B_RHOA] = sz[B_RHOB] = sz[B_DA] = sz[B_DB] = nk * d.nbb * cz;
   sz[B_PROP] = nk * 3 * d.nbb * cz;
-  sz[B_COLSUM] = nk * d.C * d.Tp * cz;
+  sz[B_COLSUM] = nk * d.C * d.Tp * cz;   // one row segment's column sums; the others are added below
   sz[B_COL0] = sz[B_DIAG] = nk * d.C * (size_t)d.qp * d.Tp * cz;  // qp columns / band offsets
   sz[B_ROWPART] = nk * (size_t)d.Smax * d.nbb * d.Tp * cz;
   sz[B_HF] = d.nbb * cz;
@@ -96,6 +102,23 @@ int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   sz[B_CHGMAX] = c->corr_tol > 0.0 ? sizeof(double) : 0;
   // interband self-energy: real-space lines of the current row, [t_j][comp][ab][R]
   sz[B_GR] = c->interaction == KBE_INT_INTERBAND ? (size_t)d.Tp * 2 * d.nbb * nk * cz : 0;
+  // Column-sum slots, one per row segment: up to 24 (the most that blocks of 16 rows want on the
+  // smallest grids) and 32 MB in all, which leaves the large grids, whose blocks are not split, with
+  // one; and no more than keep a workspace that fits the allocation-free contexts' array within it.
+  // One-band contexts that the adjoint accepts keep one: their gradients vanish by particle
+  // conservation, so what a caller gets is the rounding residue of the sums in their order.
+  size_t total = 0;
+  for (int i = 0; i < B_COUNT; ++i) total += (sz[i] + 255) / 256 * 256;
+  const size_t seg = sz[B_COLSUM];
+  size_t nseg = ((size_t)32 << 20) / seg;
+  if (nseg > 24) nseg = 24;
+  if (nseg < 1 || (c->nb == 1 && adjoint_config(c))) nseg = 1;
+  if (total <= KBE_NOALLOC_WORKSPACE_MAX && total + (nseg - 1) * seg + 256 > KBE_NOALLOC_WORKSPACE_MAX) {
+    const size_t room = KBE_NOALLOC_WORKSPACE_MAX - total;
+    nseg = 1 + (room > 256 ? (room - 256) / seg : 0);
+  }
+  d.cseg = (int)nseg;
+  sz[B_COLSUM] = nseg * seg;
   size_t off = 0;
   for (int i = 0; i < B_COUNT; ++i) {
     L->off[i] = off;
@@ -246,7 +269,7 @@ struct kbe_ctx {
     a.I_cur = buf<cplx>(cur == 0 ? B_IB : B_IA);
     a.col0 = buf<cplx>(B_COL0);
     a.diag = buf<cplx>(B_DIAG);
-    a.colsum = buf<cplx>(B_COLSUM);
+    a.colpart = buf<cplx>(B_COLSUM);
     a.rowpart = buf<cplx>(B_ROWPART);
     a.rho_prev = buf<cplx>(cur == 0 ? B_RHOA : B_RHOB);
     a.rho_cur = buf<cplx>(cur == 0 ? B_RHOB : B_RHOA);
@@ -897,18 +920,14 @@ int kbe_adjoint_query(const kbe_config* cfg, size_t* adjoint_bytes) {
   std::string why;
   int rc = make_layout(cfg, &L, &why);
   if (rc) return rc;
-  if (cfg->precision != KBE_FP64 || cfg->n_corr != 1 || cfg->corr_tol != 0.0 || cfg->quad_points > 1 || cfg->nb > 2 ||
-      cfg->interaction != KBE_INT_HUBBARD || cfg->nkx > 64)
-    return KBE_ERR_SHAPE;
+  if (!adjoint_config(cfg)) return KBE_ERR_SHAPE;
   *adjoint_bytes = adj_layout(L, nullptr);
   return KBE_OK;
 }
 
 int kbe_adjoint_attach(kbe_ctx* ctx, void* d_adjoint, size_t bytes) {
   if (!ctx || !d_adjoint) return KBE_ERR_INVALID_ARG;
-  if (ctx->cfg.precision != KBE_FP64 || ctx->cfg.n_corr != 1 || ctx->cfg.corr_tol != 0.0 || ctx->L.d.qp > 1 ||
-      ctx->L.d.nb > 2 || ctx->cfg.interaction != KBE_INT_HUBBARD || ctx->pulse.kind != KBE_PULSE_PEIERLS ||
-      ctx->cfg.nkx > 64)
+  if (!adjoint_config(&ctx->cfg) || ctx->pulse.kind != KBE_PULSE_PEIERLS)
     return ctx->fail(KBE_ERR_SHAPE,
                      "the adjoint needs precision KBE_FP64, a fixed n_corr = 1 (corr_tol = 0), the trapezoid rule "
                      "(quad_points <= 1), nb <= 2, the Hubbard preset, the Peierls pulse and nkx <= 64");

@@ -88,6 +88,7 @@ struct Dims {
   int spb;         // 64-column strips per row-partial slot group: 2 when one history-sum block
                    // covers a pair of strips (nb <= 2), else 1
   int qp;          // quadrature nodes per end carrying end corrections (1: trapezoid)
+  int cseg;        // row segments a column strip's history sums can be split into (column-sum slots)
   int rring;       // FP64 working rows kept (the last rring rows, max(2, qp))
   int64_t P;       // history elements per (k, component): one k occupies C * P elements
 };
@@ -141,6 +142,33 @@ __host__ __device__ __forceinline__ int64_t band_idx(const Dims& d, int k, int c
 // Row-partial sums of the history sums: [k][slot][nb^2][Tp], slot = strip / spb.
 __host__ __device__ __forceinline__ const cplx* rowpart_slot(const Dims& d, const cplx* rowpart, int k, int slot) {
   return rowpart + ((int64_t)k * d.Smax + slot) * d.nbb * d.Tp;
+}
+// Row segments of the history sums. A block of a history pass takes 2^lgL consecutive rows of one
+// column strip (W = 64 spb columns) of one k; segment g of strip s holds rows
+// W s + g 2^lgL .. and its column sums go to slot g of the strip's columns.
+__host__ __device__ __forceinline__ int hist_nseg(int rows, int lgL) { return (rows + (1 << lgL) - 1) >> lgL; }
+struct HistTask {
+  int s, g, r0, r1;  // strip, segment, rows r0 <= j < r1
+};
+// task = position of (s, g) in the order s = 0, 1, ..., g = 0, 1, ...
+template <int W>
+__device__ __forceinline__ HistTask hist_task(int task, int m, int lgL) {
+  HistTask t;
+  t.s = 0;
+  int n = hist_nseg(m, lgL);
+  while (task >= n) {
+    task -= n;
+    t.s += 1;
+    n = hist_nseg(m - W * t.s, lgL);
+  }
+  t.g = task;
+  t.r0 = W * t.s + (task << lgL);
+  t.r1 = m - t.r0 > (1 << lgL) ? t.r0 + (1 << lgL) : m;
+  return t;
+}
+// Column sums of the history sums: [k][segment][C][Tp].
+__host__ __device__ __forceinline__ int64_t colpart_idx(const Dims& d, int k, int g, int c, int t) {
+  return (((int64_t)k * d.cseg + g) * d.C + c) * d.Tp + t;
 }
 __host__ __device__ __forceinline__ int64_t rowbuf_idx(const Dims& d, int k, int c, int t) {
   return ((int64_t)k * d.C + c) * d.Tp + t;

@@ -710,8 +710,8 @@ __device__ __forceinline__ void flush_chunk_fold(const cplx* st0, const cplx* st
 // wavefronts' column sums are combined in LDS. Deterministic: no atomics.
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restrict__ hist,
-                                                   const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-                                                   cplx* __restrict__ rowpart, int m) {
+                                                   const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+                                                   cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int R = NB == 1 ? 4 : 1;
   __shared__ cplx red[3][C][64];
@@ -719,8 +719,10 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
   constexpr int ROWS_ST = 256;
   __shared__ cplx stg[NBB][ROWS_ST];
   __shared__ cplx sS[2][2][NBB][64];  // [strip of the pair][Sigma^<, Sigma^>][e][lane]
-  const int sp = blockIdx.x / d.nk;
-  const int k = blockIdx.x - sp * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<128>(task, m, lgL);
+  const int sp = ht.s, r0 = ht.r0, r1 = ht.r1;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // rows and Sigma^R wavefront-uniform
   const cplx* sk = sig + (int64_t)k * 3 * NBB * d.Tp;
@@ -747,14 +749,14 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[h][c] = czero();
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, sp));
-  for (int cb = 128 * sp; cb < m; cb += 64) {
+  for (int cb = r0; cb < r1; cb += 64) {
     const int rb = cb + wv;   // the wavefront's rows of the chunk: rb, rb + 4, ..., rb + 60
-    const int cslot = ((cb - 128 * sp) >> 6) % (ROWS_ST / 64);   // chunk's place in the staging
+    const int cslot = ((cb - r0) >> 6) % (ROWS_ST / 64);   // chunk's place in the staging
     cplx* st = &stg[0][64 * cslot];                                // st[e * ROWS_ST + (row - cb)]
     for (int i = 0; i < 16;) {
       const int jb = rb + 4 * i;
-      if (jb >= m) break;
-      // rows past the pair's first 128 (and below m) need no masks (as in k_hist_pair32)
+      if (jb >= r1) break;
+      // rows past the pair's first 128 (and below the segment's end) need no masks (as in k_hist_pair32)
       auto iteration = [&](auto tag, auto nh, auto nr) {
         constexpr int RR = decltype(nr)::value;   // rows in this iteration
         constexpr int MM = decltype(tag)::value;   // masks: 0 none, 1 the second strip's only, 2 all
@@ -766,7 +768,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
 #pragma unroll
           for (int h = 0; h < NH; ++h) {
             int j = jb + 4 * r;
-            bool v = (MM == 2 || (MM == 1 && h == 1)) ? (colv[h] && tp[h] <= j && j < m) : true;
+            bool v = (MM == 2 || (MM == 1 && h == 1)) ? (colv[h] && tp[h] <= j && j < r1) : true;
             const cplx* row = hk[h] + 64 * (int64_t)C * j;
 #pragma unroll
             for (int c = 0; c < C; ++c) G[r][h][c] = v ? load_stream(row + 64 * c) : czero();
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
 #pragma unroll
         for (int r = 0; r < RR; ++r) {
           int j = jb + 4 * r;
-          int jc = MASKED ? (j < m ? j : m - 1) : j;
+          int jc = MASKED ? (j < r1 ? j : r1 - 1) : j;
           cplx SR[NBB];
 #pragma unroll
           for (int e = 0; e < NBB; ++e) SR[e] = sk[(2 * NBB + e) * d.Tp + jc];
@@ -828,10 +830,10 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
       // work; in its next 64 rows every column of the first strip lies below the row: masks for
       // the second strip only
       // (an iteration's rows jb, jb + 4, ..., jb + 4 (RR - 1) lie in one 64-row chunk)
-      if (jb >= 128 * sp + 128 && jb + 4 * (R - 1) < m) {
+      if (jb >= 128 * sp + 128 && jb + 4 * (R - 1) < r1) {
         iteration(IntTag<0>{}, IntTag<2>{}, IntTag<R>{});
         i += R;
-      } else if (R == 1 && jb + 4 < 128 * sp + 64 && jb + 4 < m) {
+      } else if (R == 1 && jb + 4 < 128 * sp + 64 && jb + 4 < r1) {
         // two rows at a time where only the first strip has work: its loads of both rows in
         // flight together (one row would keep half the loads of a full iteration in flight)
         iteration(IntTag<2>{}, IntTag<1>{}, IntTag<2>{});
@@ -839,7 +841,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
       } else if (jb + 4 * (R - 1) < 128 * sp + 64) {
         iteration(IntTag<2>{}, IntTag<1>{}, IntTag<R>{});
         i += R;
-      } else if (jb >= 128 * sp + 64 && jb + 4 * (R - 1) < m && jb + 4 * (R - 1) < 128 * sp + 128) {
+      } else if (jb >= 128 * sp + 64 && jb + 4 * (R - 1) < r1 && jb + 4 * (R - 1) < 128 * sp + 128) {
         iteration(IntTag<1>{}, IntTag<2>{}, IntTag<R>{});
         i += R;
       } else {
@@ -849,10 +851,10 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
     }
     // every fourth chunk (and the last): the staged rows of all four wavefronts leave as one
     // contiguous run of up to 256 rows per component (4 KB), streaming stores
-    if (cslot == ROWS_ST / 64 - 1 || cb + 64 >= m) {
+    if (cslot == ROWS_ST / 64 - 1 || cb + 64 >= r1) {
       __syncthreads();
       const int base = cb - 64 * cslot;
-      const int nrows = (cb + 64 < m ? cb + 64 : m) - base;
+      const int nrows = (cb + 64 < r1 ? cb + 64 : r1) - base;
       for (int q = threadIdx.x; q < NBB * nrows; q += 256) {
         const int e = q / nrows, row = q - e * nrows;
         store_stream(rp + (int64_t)e * d.Tp + base + row, stg[e][row]);
@@ -875,7 +877,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
         a = cadd(a, red[0][c][lane]);
         a = cadd(a, red[1][c][lane]);
         a = cadd(a, red[2][c][lane]);
-        colsum[rowbuf_idx(d, k, c, tp[h])] = a;
+        colpart[colpart_idx(d, k, ht.g, c, tp[h])] = a;
       }
     }
     __syncthreads();
@@ -892,16 +894,18 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
 // stay FP64).
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __restrict__ hist,
-                                                     const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-                                                     cplx* __restrict__ rowpart, int m) {
+                                                     const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+                                                     cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int R = NB == 1 ? 4 : 2;
   __shared__ cplx red[3][C][64];
   constexpr int ROWS_ST = 256;   // row partials staged over four 64-row chunks, as in k_hist_pair
   __shared__ cplx stg[NBB][ROWS_ST];
   __shared__ cplx32 sS[2][2][NBB][64];
-  const int sp = blockIdx.x / d.nk;
-  const int k = blockIdx.x - sp * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<128>(task, m, lgL);
+  const int sp = ht.s, r0 = ht.r0, r1 = ht.r1;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const cplx* sk = sig + (int64_t)k * 3 * NBB * d.Tp;
@@ -931,14 +935,14 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
       acc32[h][c] = make_float2(0.f, 0.f);
     }
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, sp));
-  for (int cb = 128 * sp; cb < m; cb += 64) {
+  for (int cb = r0; cb < r1; cb += 64) {
     const int rb = cb + wv;   // the wavefront's rows of the chunk: rb, rb + 4, ..., rb + 60
-    const int cslot = ((cb - 128 * sp) >> 6) % (ROWS_ST / 64);
+    const int cslot = ((cb - r0) >> 6) % (ROWS_ST / 64);
     cplx* st = &stg[0][64 * cslot];   // st[e * ROWS_ST + (row - cb)]
     for (int i = 0; i < 16 / R; ++i) {
       const int jb = rb + 4 * R * i;
-      if (jb >= m) break;
-      // rows past the pair's first 128 (and below m) need no masks: every lane's columns lie
+      if (jb >= r1) break;
+      // rows past the pair's first 128 (and below the segment's end) need no masks: every lane's columns lie
       // below the row, so that common case runs without the bounds selects
       auto iteration = [&](auto tag, auto nh) {
         constexpr int MM = decltype(tag)::value;   // masks: 0 none, 1 the second strip's only, 2 all
@@ -950,7 +954,7 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
 #pragma unroll
           for (int h = 0; h < NH; ++h) {
             int j = jb + 4 * r;
-            bool v = (MM == 2 || (MM == 1 && h == 1)) ? (colv[h] && tp[h] <= j && j < m) : true;
+            bool v = (MM == 2 || (MM == 1 && h == 1)) ? (colv[h] && tp[h] <= j && j < r1) : true;
             const cplx32* row = hk[h] + 64 * (int64_t)C * j;
 #pragma unroll
             for (int c2 = 0; c2 < C / 2; ++c2) {
@@ -966,7 +970,7 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           int j = jb + 4 * r;
-          int jc = MASKED ? (j < m ? j : m - 1) : j;
+          int jc = MASKED ? (j < r1 ? j : r1 - 1) : j;
           cplx32 SR[NBB];
 #pragma unroll
           for (int e = 0; e < NBB; ++e) SR[e] = to32(sk[(2 * NBB + e) * d.Tp + jc]);
@@ -1032,11 +1036,11 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
       // work; in its next 64 rows every column of the first strip lies below the row: masks for
       // the second strip only
       // (an iteration's rows jb, jb + 4, ..., jb + 4 (R - 1) lie in one 64-row chunk)
-      if (jb >= 128 * sp + 128 && jb + 4 * (R - 1) < m)
+      if (jb >= 128 * sp + 128 && jb + 4 * (R - 1) < r1)
         iteration(IntTag<0>{}, IntTag<2>{});
       else if (jb + 4 * (R - 1) < 128 * sp + 64)
         iteration(IntTag<2>{}, IntTag<1>{});
-      else if (jb >= 128 * sp + 64 && jb + 4 * (R - 1) < m && jb + 4 * (R - 1) < 128 * sp + 128)
+      else if (jb >= 128 * sp + 64 && jb + 4 * (R - 1) < r1 && jb + 4 * (R - 1) < 128 * sp + 128)
         iteration(IntTag<1>{}, IntTag<2>{});
       else
         iteration(IntTag<2>{}, IntTag<2>{});
@@ -1050,10 +1054,10 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
         acc[h][c].y += (double)acc32[h][c].y;
         acc32[h][c] = make_float2(0.f, 0.f);
       }
-    if (cslot == ROWS_ST / 64 - 1 || cb + 64 >= m) {
+    if (cslot == ROWS_ST / 64 - 1 || cb + 64 >= r1) {
       __syncthreads();
       const int base = cb - 64 * cslot;
-      const int nrows = (cb + 64 < m ? cb + 64 : m) - base;
+      const int nrows = (cb + 64 < r1 ? cb + 64 : r1) - base;
       for (int q = threadIdx.x; q < NBB * nrows; q += 256) {
         const int e = q / nrows, row = q - e * nrows;
         store_stream(rp + (int64_t)e * d.Tp + base + row, stg[e][row]);
@@ -1075,7 +1079,7 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
         a = cadd(a, red[0][c][lane]);
         a = cadd(a, red[1][c][lane]);
         a = cadd(a, red[2][c][lane]);
-        colsum[rowbuf_idx(d, k, c, tp[h])] = a;
+        colpart[colpart_idx(d, k, ht.g, c, tp[h])] = a;
       }
     }
     __syncthreads();
@@ -1088,14 +1092,16 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
 // iteration, the per-column Sigma of the row term in LDS. Row partials stored by lane 0.
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restrict__ hist,
-                                                   const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-                                                   cplx* __restrict__ rowpart, int m) {
+                                                   const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+                                                   cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int CH = (C < 8) ? C : 8;  // components per LDS combine round
   __shared__ cplx red[3][CH][64];
   __shared__ cplx sS[2][NBB][64];
-  int s = blockIdx.x / d.nk;  // strips with the most rows first
-  int k = blockIdx.x - s * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<64>(task, m, lgL);
+  const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tp = 64 * s + lane;
@@ -1112,7 +1118,7 @@ __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restric
   for (int c = 0; c < C; ++c) acc[c] = czero();
   const cplx* hk = hist + strip_lane_base(d, k, s, lane);
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
-  for (int j = 64 * s + wv; j < m; j += 4) {
+  for (int j = r0 + wv; j < r1; j += 4) {
     bool v = colv && tp <= j;
     const cplx* row = hk + 64 * (int64_t)C * j;
     cplx G[C];
@@ -1160,7 +1166,7 @@ __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restric
         a = cadd(a, red[0][c][lane]);
         a = cadd(a, red[1][c][lane]);
         a = cadd(a, red[2][c][lane]);
-        if (colv) colsum[rowbuf_idx(d, k, c0 + c, tp)] = a;
+        if (colv) colpart[colpart_idx(d, k, ht.g, c0 + c, tp)] = a;
       }
     }
     __syncthreads();
@@ -1171,15 +1177,17 @@ __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restric
 // of 16 rows per wavefront added into FP64 accumulators.
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __restrict__ hist,
-                                                     const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-                                                     cplx* __restrict__ rowpart, int m) {
+                                                     const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+                                                     cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int CH = (C < 8) ? C : 8;
   constexpr int R = 2;
   constexpr int FLUSH = 16 / R;  // iterations per FP32 accumulation tile (16 rows)
   __shared__ cplx red[3][CH][64];
-  int s = blockIdx.x / d.nk;
-  int k = blockIdx.x - s * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<64>(task, m, lgL);
+  const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tp = 64 * s + lane;
@@ -1201,12 +1209,12 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
   const cplx32* hk = hist + strip_lane_base(d, k, s, lane);
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
   int it = 0;
-  for (int jb = 64 * s + R * wv; jb < m; jb += 4 * R) {
+  for (int jb = r0 + R * wv; jb < r1; jb += 4 * R) {
     cplx32 G[R][C];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       int j = jb + r;
-      bool v = colv && tp <= j && j < m;
+      bool v = colv && tp <= j && j < r1;
       const cplx32* row = hk + 64 * (int64_t)C * j;
 #pragma unroll
       for (int c2 = 0; c2 < C / 2; ++c2) {
@@ -1222,7 +1230,7 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       int j = jb + r;
-      int jc = j < m ? j : m - 1;
+      int jc = j < r1 ? j : r1 - 1;
       cplx32 SR[NBB];
 #pragma unroll
       for (int e = 0; e < NBB; ++e) SR[e] = to32(sk[(2 * NBB + e) * d.Tp + jc]);
@@ -1261,7 +1269,7 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
     }
     reduce_rows32<R>(rt);
     int rsel = reduced_row<R>(lane);
-    if (rsel >= 0 && jb + rsel < m) {
+    if (rsel >= 0 && jb + rsel < r1) {
 #pragma unroll
       for (int e = 0; e < NBB; ++e)
         rp[(int64_t)e * d.Tp + jb + rsel] = cmk((double)rt[0][2 * e], (double)rt[0][2 * e + 1]);
@@ -1286,7 +1294,7 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
         a = cadd(a, red[0][c][lane]);
         a = cadd(a, red[1][c][lane]);
         a = cadd(a, red[2][c][lane]);
-        if (colv) colsum[rowbuf_idx(d, k, c0 + c, tp)] = a;
+        if (colv) colpart[colpart_idx(d, k, ht.g, c0 + c, tp)] = a;
       }
     }
     __syncthreads();
@@ -1307,15 +1315,17 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
 // term is read from LDS. FP64 storage; 2 waves per SIMD.
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_hist_bulk_split(
-    Dims d, const cplx* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-    cplx* __restrict__ rowpart, int m) {
+    Dims d, const cplx* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+    cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   static_assert(NB == 4, "the four block rows share one reduce-scatter");
   __shared__ cplx sS[2][NBB][64];  // [half][e][lane]: half 0 needs Sigma^>, half 1 Sigma^<;
                                    // reused for the column-sum combine after the row loop
   __shared__ cplx stg[2][2][2][NBB * 16];  // [buffer][row pair][half][e * 16 + row]
-  int s = blockIdx.x / d.nk;
-  int k = blockIdx.x - s * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<64>(task, m, lgL);
+  const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront-uniform: rows and Sigma^R in SGPRs
   int h = wv & 1, rg = wv >> 1;
@@ -1335,12 +1345,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
   const double sgn = h ? 1.0 : -1.0;
   int buf = 0;
-  for (int cb = 64 * s; cb < m; cb += 32) {  // the same chunks in every wavefront
+  for (int cb = r0; cb < r1; cb += 32) {  // the same chunks in every wavefront
     const int rb = cb + 16 * rg;
     cplx* st = stg[buf][rg][h];
     for (int i = 0; i < 16; ++i) {
       const int j = rb + i;
-      if (j >= m) break;
+      if (j >= r1) break;
       bool v = colv && tp <= j;
       const cplx* row = hk + 64 * (int64_t)C * j;
       cplx G[NBB];
@@ -1376,7 +1386,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     __syncthreads();  // both halves of the chunk staged; the other buffer is free again
-    flush_rows_fold<NBB>(stg[buf][rg][0], stg[buf][rg][1], rp, d.Tp, rb, m, lane, h);
+    flush_rows_fold<NBB>(stg[buf][rg][0], stg[buf][rg][1], rp, d.Tp, rb, r1, lane, h);
     buf ^= 1;
   }
   __syncthreads();  // every wavefront is done with sS
@@ -1388,7 +1398,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __syncthreads();
   if (rg == 0 && colv) {
 #pragma unroll
-    for (int e = 0; e < NBB; ++e) colsum[rowbuf_idx(d, k, h * NBB + e, tp)] = cadd(acc[e], red[h][e][lane]);
+    for (int e = 0; e < NBB; ++e) colpart[colpart_idx(d, k, ht.g, h * NBB + e, tp)] = cadd(acc[e], red[h][e][lane]);
   }
 }
 
@@ -1401,16 +1411,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // consecutive rows per pair).
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_hist_bulk32_split(
-    Dims d, const cplx32* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-    cplx* __restrict__ rowpart, int m) {
+    Dims d, const cplx32* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+    cplx* __restrict__ rowpart, int m, int lgL) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   static_assert(NB == 4, "the four block rows share one reduce-scatter");
   static_assert(NBB % 2 == 0, "component pairs must not straddle the halves");
   __shared__ cplx32 sS[2][NBB][64];
   __shared__ cplx stg[2][2][NBB * 32];  // [buffer][half][e * 32 + row - cb]; column-sum combine
                                         // after the row loop
-  int s = blockIdx.x / d.nk;
-  int k = blockIdx.x - s * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<64>(task, m, lgL);
+  const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
   int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int h = wv & 1, rg = wv >> 1;
@@ -1434,7 +1446,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
   const float sgn = h ? 1.f : -1.f;
   int buf = 0;
-  for (int cb = 64 * s; cb < m; cb += 32) {  // the same chunks in every wavefront
+  for (int cb = r0; cb < r1; cb += 32) {  // the same chunks in every wavefront
     const int rb = cb + rg;   // the wave pair's rows of the chunk: rb, rb + 2, ..., rb + 30
     cplx* st = stg[buf][h];
     // groups of 16 rows past the strip's first 64 rows and below m need no masks (this
@@ -1444,7 +1456,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       constexpr bool MASKED = decltype(tag)::value;
       for (int i = 0; i < 16; ++i) {
         const int j = rb + 2 * i;
-        if (MASKED && j >= m) break;
+        if (MASKED && j >= r1) break;
         bool v = MASKED ? (colv && tp <= j) : true;
         const cplx32* row = hk + 64 * (int64_t)C * j;
         cplx32 G[NBB];
@@ -1485,7 +1497,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
       }
     };
-    if (rb >= 64 * s + 64 && rb + 30 < m)
+    if (rb >= 64 * s + 64 && rb + 30 < r1)
       rows16(BoolTag<false>{});
     else
       rows16(BoolTag<true>{});
@@ -1496,7 +1508,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       acc32[e] = make_float2(0.f, 0.f);
     }
     __syncthreads();  // both halves of the chunk staged; the other buffer is free again
-    flush_chunk_fold<NBB>(stg[buf][0], stg[buf][1], rp, d.Tp, cb, m);
+    flush_chunk_fold<NBB>(stg[buf][0], stg[buf][1], rp, d.Tp, cb, r1);
     buf ^= 1;
   }
   __syncthreads();  // every wavefront is done with stg
@@ -1508,7 +1520,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __syncthreads();
   if (rg == 0 && colv) {
 #pragma unroll
-    for (int e = 0; e < NBB; ++e) colsum[rowbuf_idx(d, k, h * NBB + e, tp)] = cadd(acc[e], red[h][e][lane]);
+    for (int e = 0; e < NBB; ++e) colpart[colpart_idx(d, k, ht.g, h * NBB + e, tp)] = cadd(acc[e], red[h][e][lane]);
   }
 }
 
@@ -1631,8 +1643,8 @@ struct AfrFill {
 
 template <int NB>
 __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_hist_mfma(
-    Dims d, const float2* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colsum,
-    cplx* __restrict__ rowpart, int m) {
+    Dims d, const float2* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
+    cplx* __restrict__ rowpart, int m, int lgL) {
   using Sh = MfmaShape<NB>;
   constexpr int NBB = Sh::NBB, C = Sh::C, HS = Sh::HS, NCH = Sh::NCH, VP = Sh::VP, CQ = Sh::CQ, WAVES = Sh::WAVES;
   static_assert(HS == 2 || NBB % 2 == 0, "halves must not share a 16-byte load");
@@ -1642,8 +1654,11 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
   float* stg = reinterpret_cast<float*>(smem);  // [2][WAVES][CQ][4][VP]
   float* afr = reinterpret_cast<float*>(smem + Sh::STAGE);  // [2][CQ][64][2 nb]
   constexpr int NTHR = WAVES * 64, NE = (CQ * 64 + NTHR - 1) / NTHR;
-  const int s = blockIdx.x / d.nk;
-  const int k = blockIdx.x - s * d.nk;
+  const int task = blockIdx.x / d.nk;
+  const int k = blockIdx.x - task * d.nk;
+  const HistTask ht = hist_task<64>(task, m, lgL);
+  const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
+  const int qs = (r0 - 64 * s) >> 2;      // the segment's first quad
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = HS == 1 ? (wv >> 1) : wv;
@@ -1679,7 +1694,8 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
   const kbe_f4v* hq = reinterpret_cast<const kbe_f4v*>(hist) +
                       ((int64_t)k * C * d.P + 256 * (int64_t)C * quad_base(s, d.N)) / 2 +
                       (int64_t)(g * (C / 2) + h0 * (NBB / 2)) * 64 + lane;
-  const int nq = (m - 64 * s + 3) >> 2;   // quads holding rows below m
+  const int nq = (r1 - 64 * s + 3) >> 2;  // one past its last (segments are whole chunks of 64 rows,
+                                          // or end at m)
   constexpr int PF = Sh::PF, RING = PF + 1;
   static_assert(CQ % RING == 0, "a chunk holds whole turns of the load ring");
   // quad x lives in ring[x % RING]; its loads are issued while quad x - PF is processed
@@ -1692,21 +1708,21 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
   const int qlo = 4 * g < nq - 1 ? 4 * g : nq - 1;
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
-    const int qu = u < qlo ? qlo : (u < nq ? u : nq - 1);
+    const int qu = qs + u < qlo ? qlo : (qs + u < nq ? qs + u : nq - 1);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) ring[u][i] = __builtin_nontemporal_load(hq + (int64_t)qu * 128 * C + i * 64);
   }
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
   AfrFill<NB, NE> fill;
-  fill.load(d, sk, s, 0, m, threadIdx.x, NTHR);
+  fill.load(d, sk, s, qs, r1, threadIdx.x, NTHR);
   fill.store(afr, threadIdx.x, NTHR);
   __syncthreads();
   int buf = 0;
-  for (int q0 = 0, ci = 0; q0 < nq; q0 += CQ, ++ci) {
+  for (int q0 = qs, ci = 0; q0 < nq; q0 += CQ, ++ci) {
     float* sb = stg + buf * (WAVES * CQ * 4 * VP);
     const float* ab = afr + buf * (CQ * 64 * 2 * NB);
     const bool more = q0 + CQ < nq;
-    if (more) fill.load(d, sk, s, q0 + CQ, m, threadIdx.x, NTHR);  // the next chunk's A operands
+    if (more) fill.load(d, sk, s, q0 + CQ, r1, threadIdx.x, NTHR);  // the next chunk's A operands
     for (int qt = 0; qt < CQ; qt += RING) {
 #pragma unroll
     for (int u = 0; u < RING; ++u) {
@@ -1725,7 +1741,7 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
       auto quad = [&](auto tag) {
         constexpr bool MASKED = decltype(tag)::value;
         cplx32 G[HS * NBB];
-        const bool valid = MASKED ? (colv && tp <= j && j < m) : true;
+        const bool valid = MASKED ? (colv && tp <= j && j < r1) : true;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
           G[2 * i] = valid ? make_float2(cur[i].x, cur[i].y) : make_float2(0.f, 0.f);
@@ -1780,7 +1796,7 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
           if (n % (16 / VP) == 0) row[n / (16 / VP)] = x[0];
         }
       };
-      if (q >= 16 && j0 + 4 <= m)   // (q >= nq implies j0 >= m: masked)
+      if (q >= 16 && j0 + 4 <= r1)   // (q >= nq implies j0 >= r1: masked)
         quad(BoolTag<false>{});
       else
         quad(BoolTag<true>{});
@@ -1801,7 +1817,7 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
     for (int o = threadIdx.x; o < 4 * CQ * NBB; o += WAVES * 64) {
       const int e = o / (4 * CQ), rho = o - e * (4 * CQ);
       const int jj = 64 * s + 4 * q0 + rho;
-      if (jj < m) {
+      if (jj < r1) {
         double re = 0.0, im = 0.0;
         for (int w = 0; w < WAVES; ++w) {
           const float* src = sb + (w * CQ * 4 + rho) * VP + 2 * e;
@@ -1819,7 +1835,7 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
         __syncthreads();
         const int base = 64 * s + 4 * q0 - (ci % CPF) * 4 * CQ;
         const int end = 64 * s + 4 * q0 + 4 * CQ;
-        const int nrows = (end < m ? end : m) - base;
+        const int nrows = (end < r1 ? end : r1) - base;
         for (int o = threadIdx.x; o < NBB * nrows; o += WAVES * 64) {
           const int e = o / nrows, row = o - e * nrows;
           store_stream(rp + (int64_t)e * d.Tp + base + row, rstg[e * Sh::ROWS + row]);
@@ -1850,7 +1866,7 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
         double re = t[mre * 16 + n] + t[(lo + mre) * 16 + n];
         double im = t[mim * 16 + n] + t[(lo + mim) * 16 + n];
         const int c = (h0 + hh) * NBB + a * NB + b;
-        colsum[rowbuf_idx(d, k, c, tp)] = cmk(re, im);
+        colpart[colpart_idx(d, k, ht.g, c, tp)] = cmk(re, im);
       }
   }
 }
@@ -1912,13 +1928,13 @@ struct EndBlock {
 
 template <int NB, int MODE, bool GREG>
 __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ hist, cplx* __restrict__ row64,
-                                                  const cplx* __restrict__ sig, const cplx* __restrict__ colsum,
+                                                  const cplx* __restrict__ sig, const cplx* __restrict__ colpart,
                                                   const cplx* __restrict__ rowpart, cplx* __restrict__ col0,
                                                   cplx* __restrict__ diag, const cplx* __restrict__ Iprev,
                                                   cplx* __restrict__ Icur, const cplx* __restrict__ props,
                                                   const cplx* __restrict__ rho_prev, cplx* __restrict__ rho_cur,
                                                   const cplx* __restrict__ Dprev, const cplx* __restrict__ Dcur, int m,
-                                                  double dt, int commit, double* __restrict__ chg, QuadW Q) {
+                                                  int lgL, double dt, int commit, double* __restrict__ chg, QuadW Q) {
   constexpr int NBB = NB * NB;
   constexpr bool INT = MODE == KBE_ROW_CORRECT || MODE == KBE_ROW_EVAL;   // collision row
   constexpr bool UPD = MODE != KBE_ROW_EVAL;                              // update of the row
@@ -2025,10 +2041,33 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
           }
         }
       }
+      // column sums over the row segments, in groups whose loads are issued together
+      const int nseg = hist_nseg(m - 64 * d.spb * (tp / (64 * d.spb)), lgL);
+      const cplx* cp = colpart + colpart_idx(d, k, 0, sc * NBB + a * NB, tp);
+      const int64_t cstep = (int64_t)d.C * d.Tp;
+      constexpr int CG = NB <= 2 ? 4 : 2;
+      cplx cs[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) cs[b] = cp[b * (int64_t)d.Tp];
+      int sg = 1;
+      for (; sg + CG <= nseg; sg += CG) {
+        cplx v[CG][NB];
+#pragma unroll
+        for (int u = 0; u < CG; ++u)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) v[u][b] = cp[(sg + u) * cstep + b * (int64_t)d.Tp];
+#pragma unroll
+        for (int u = 0; u < CG; ++u)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) cs[b] = cadd(cs[b], v[u][b]);
+      }
+      for (; sg < nseg; ++sg)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) cs[b] = cadd(cs[b], cp[sg * cstep + b * (int64_t)d.Tp]);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         const int e = a * NB + b;
-        In[b] = cadd(cadd(colsum[rowbuf_idx(d, k, sc * NBB + e, tp)], sP[e * 64 + lane]), E[b]);
+        In[b] = cadd(cadd(cs[b], sP[e * 64 + lane]), E[b]);
         Icur[rowbuf_idx(d, k, sc * NBB + e, tp)] = cscal(In[b], dt);
       }
     }
@@ -2345,6 +2384,35 @@ static hipError_t allow_lds(const void* kern, size_t bytes) {
 // Blocks of 64 t' per k of the row kernel: t' < m in the evaluation mode, t' <= m otherwise.
 static int row_tiles(int m, int mode) { return mode == KBE_ROW_EVAL ? (m + 63) / 64 : m / 64 + 1; }
 
+// Rows per block of a history pass at row m, as a power of two (30: every strip is one block).
+// One block per strip leaves a small N_k with fewer blocks than the 512 that the chip holds at a
+// time (two per CU), and a medium one with a last round of a few long blocks; shorter blocks cost
+// each a prologue and a column combine (5-10 rows' worth of time) and their column sums are read
+// once more by the row kernel. Measured best over N_k = 16..1024, m = 20..500, nb = 1..4: blocks of about
+// 1.5 times the rows that an even share of the launch would be (a strip's triangular first 64 rows
+// count half), at least 16 (32 in the FP64 nb = 4 kernel and 64 in the MFMA form, whose blocks work
+// in chunks of that many). FP64, nb = 2, one block per strip -> split: 16 points, m = 200 84 -> 17 us;
+// 61 points, m = 200 93 -> 40 us; 144 points, m = 128 / 200 / 400 66 -> 47, 102 -> 80, 287 -> 272 us;
+// 1024 points 2.76 ms unsplit against 2.83 ms in blocks of 256 rows at m = 500.
+static int hist_lgseg(const Dims& d, int m) {
+  if (d.cseg == 1) return 30;
+  const int W = 64 * d.spb;
+  int64_t rows = 0;
+  for (int r = m; r > 0; r -= W) rows += r - (r < 64 ? r / 2 : 32);
+  const int slots = (d.nb == 3 && !d.mfma) ? 256 : 512;   // nb = 3: one block per CU
+  const double share = 1.5 * d.nk * (double)rows / slots;
+  int lg = d.mfma ? 6 : (d.nb == 4 && !d.fp32 ? 5 : 4);
+  while ((2 << lg) <= share && (2 << lg) < m) ++lg;
+  while (hist_nseg(m, lg) > d.cseg) ++lg;
+  return (1 << lg) < m ? lg : 30;
+}
+// Blocks per k of a history pass whose strips have W columns.
+static int hist_tasks(int W, int m, int lgL) {
+  int n = 0;
+  for (int r = m; r > 0; r -= W) n += hist_nseg(r, lgL);
+  return n;
+}
+
 template <int NB>
 struct Launch {
   static hipError_t init(const Dims& d, const LaunchArgs& a, hipStream_t st) {
@@ -2405,34 +2473,34 @@ struct Launch {
   }
   static hipError_t bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
     if (m < 1) return hipSuccess;
-    int ns = (m + 63) / 64;
+    const int lgL = hist_lgseg(d, m);
+    const int ns = hist_tasks(64 * d.spb, m, lgL);
     if (d.mfma) {
       hipLaunchKernelGGL(k_hist_mfma<NB>, dim3(ns * d.nk), dim3(MfmaShape<NB>::WAVES * 64), 0, st, d,
-                         (const float2*)a.hist, (const cplx*)a.sig, a.colsum, a.rowpart, m);
+                         (const float2*)a.hist, (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
       return hipGetLastError();
     }
     if constexpr (NB <= 2) {
-      int np = (ns + 1) / 2;  // pairs of strips
       if (d.fp32)
-        hipLaunchKernelGGL(k_hist_pair32<NB>, dim3(np * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+        hipLaunchKernelGGL(k_hist_pair32<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
       else
-        hipLaunchKernelGGL(k_hist_pair<NB>, dim3(np * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+        hipLaunchKernelGGL(k_hist_pair<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
     } else if constexpr (NB == 4) {
       if (d.fp32)
         hipLaunchKernelGGL(k_hist_bulk32_split<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
       else
         hipLaunchKernelGGL(k_hist_bulk_split<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
     } else {
       if (d.fp32)
         hipLaunchKernelGGL(k_hist_bulk32<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
       else
         hipLaunchKernelGGL(k_hist_bulk<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colsum, a.rowpart, m);
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
     }
     return hipGetLastError();
   }
@@ -2445,9 +2513,9 @@ struct Launch {
     const int tiles = row_tiles(m, mode);
     if (tiles == 0) return hipSuccess;
     hipLaunchKernelGGL(kern, dim3(tiles, d.nk), dim3(128 * NB), 0, st, d, a.hist, a.row64, (const cplx*)a.sig,
-                       (const cplx*)a.colsum, (const cplx*)a.rowpart, a.col0, a.diag, (const cplx*)a.I_prev, a.I_cur,
+                       (const cplx*)a.colpart, (const cplx*)a.rowpart, a.col0, a.diag, (const cplx*)a.I_prev, a.I_cur,
                        (const cplx*)a.props, (const cplx*)a.rho_prev, a.rho_cur, (const cplx*)a.D_prev,
-                       (const cplx*)a.D_cur, m, a.dt, a.commit, a.chg, a.quad);
+                       (const cplx*)a.D_cur, m, hist_lgseg(d, m), a.dt, a.commit, a.chg, a.quad);
     return hipGetLastError();
   }
   static hipError_t obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st) {

@@ -27,7 +27,7 @@ struct LaunchArgs {
   cplx* I_cur;
   cplx* col0;
   cplx* diag;
-  cplx* colsum;
+  cplx* colpart;   // column sums of the history sums, per row segment: [k][cseg][C][Tp]
   cplx* rowpart;
   cplx* rho_prev;
   cplx* rho_cur;
