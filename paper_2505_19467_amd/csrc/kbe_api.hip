@@ -354,9 +354,7 @@ struct kbe_ctx {
   }
   int props(LaunchArgs& a, int m, int mode) {
     set_A(a, (m - 0.5) * cfg.dt);
-    int rc = check(kbe::launch_hf(L.d, a, mode == 0 ? 0.0 : 0.5, st), "mean-field launch");
-    if (!rc) rc = check(kbe::launch_props(L.d, a, st), "propagator launch");
-    return rc;
+    return check(kbe::launch_props(L.d, a, mode == 0 ? 0.0 : 0.5, st), "propagator launch");
   }
   int observe(int m) {
     LaunchArgs a = args();
@@ -531,8 +529,7 @@ struct kbe_ctx {
     p.props = b.props_p;
     p.hfbuf = b.hf_p;
     p.commit = 0;
-    if (!rc) rc = check(kbe::launch_hf(d, p, 0.0, st), "mean-field launch");
-    if (!rc) rc = check(kbe::launch_props(d, p, st), "propagator launch");
+    if (!rc) rc = check(kbe::launch_props(d, p, 0.0, st), "propagator launch");
     if (!rc) rc = check(kbe::launch_row(d, p, m, KBE_ROW_PREDICT, st), "predictor launch");
     // recompute the corrector's collision row and propagators
     LaunchArgs c = p;
@@ -544,8 +541,7 @@ struct kbe_ctx {
     if (!rc) rc = check(kbe::launch_diag_I(d, c, m, st), "equal-time collision launch");
     if (!rc) rc = check(kbe::launch_bulk(d, c, m, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, c, m, KBE_ROW_EVAL, st), "collision-row launch");
-    if (!rc) rc = check(kbe::launch_hf(d, c, 0.5, st), "mean-field launch");
-    if (!rc) rc = check(kbe::launch_props(d, c, st), "propagator launch");
+    if (!rc) rc = check(kbe::launch_props(d, c, 0.5, st), "propagator launch");
     // corrector update, its propagators and mean field
     if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, b.lam, b.Rbar, rho0, st), "adjoint update launch");
     if (!rc) rc = check(kbe::launch_adj_props(d, a, b, b.hf_c, st), "adjoint propagator launch");

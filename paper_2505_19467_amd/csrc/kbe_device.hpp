@@ -343,6 +343,33 @@ __device__ __forceinline__ void block_sum_cplx(cplx* v, cplx* lds /* [N][256] */
   __syncthreads();
 }
 
+// Block sums of N values per thread (256 threads) into out[N], with two block barriers: the values
+// of threads t, t + 64, t + 128, t + 192 are added pairwise by one wavefront per value, then across
+// its lanes (the order of block_sum_cplx).
+template <int N>
+__device__ __forceinline__ void block_sum_once(const double* v, double* lds /* [N][256] */, double* out) {
+  const int t = threadIdx.x, lane = t & 63;
+#pragma unroll
+  for (int i = 0; i < N; ++i) lds[i * 256 + t] = v[i];
+  __syncthreads();
+  for (int i = t >> 6; i < N; i += 4) {
+    const double* x = lds + i * 256 + lane;
+    double a = (x[0] + x[128]) + (x[64] + x[192]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
+    if (lane == 0) out[i] = a;
+  }
+  __syncthreads();
+}
+__device__ __forceinline__ int wave_max(int x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const int y = __shfl_xor(x, o, 64);
+    x = x > y ? x : y;
+  }
+  return x;
+}
+
 __device__ __forceinline__ double wave_sum(double x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);

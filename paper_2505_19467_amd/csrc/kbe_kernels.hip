@@ -1,9 +1,8 @@
 // HIP kernels (gfx950) of the Kadanoff-Baym propagation step.
 //
 //   k_init_*        uncorrelated initial state (Fermi-Dirac density of h0, mu by bisection)
-//   k_hf            mean-field (first-order) self-energy from the local density matrix
-//   k_props         per-k propagators V, Vh, Phi of the midpoint Hamiltonian (scaling and
-//                   squaring of an augmented matrix exponential, one wavefront per k)
+//   k_props         mean-field (first-order) self-energy from the local density matrix, and the
+//                   per-k propagators V, Vh, Phi of the midpoint Hamiltonian
 //   k_kick_row      the dipole kick of eq. (dipole) on the completed slice nearest t0
 //   k_sigma         second-Born self-energy of a time slice, eq. (2BSE), by k <-> R transforms
 //                   (Hubbard preset)
@@ -148,115 +147,200 @@ __global__ __launch_bounds__(64) void k_init_rho(Dims d, const double* __restric
     }
 }
 
-// ------------------------------------------------------------------ mean field
-// hf_out = one-body extra term + Sigma^HF[rho_loc], rho = (1 - wb) rhoA + wb rhoB (one block).
+// ------------------------------------------------------------------ propagators
+// Mean field and propagators of the midpoint Hamiltonian hbar = h0(k - A) + Sigma^HF[rho_loc],
+// rho = (1 - wb) rhoA + wb rhoB. Bound by latency (a chain of 13 dependent matrix-vector products on
+// nb x nb matrices); one lane carries one column of one k, so that the chain needs no exchange
+// between lanes, and every block sums the local density by itself (N_k nb^2 numbers from the L2)
+// instead of a launch of its own: 16 points 11.2 -> 4.0 us, 576 points 20.9 -> 6.6 us (nb = 2) for both,
+// against one wavefront per k on the augmented 2nb x 2nb matrix with every product through LDS.
+//
+// Phi = -i dt phi1(X), V = exp(X), Vh = exp(X/2), X = -i hbar dt. phi1(X / 2^s) by its Taylor
+// polynomial of degree 13 (||X / 2^s||_F <= 1/4: the rest is below 2e-19), exp = 1 + X phi1, then s >= 1
+// squarings E(2X) = E^2, phi1(2X) = (E + 1) phi1 / 2; the square before the last gives Vh. nb = 1 keeps
+// the augmented matrix's own recurrence of degree 16 (its two nontrivial entries).
+//
+// The one-body term beside h0 and the first-order self-energy of the local density sum loc:
+// (loc: the real diagonal in the Hubbard preset, all (re, im) in the interband one)
 template <int NB>
-__global__ __launch_bounds__(256) void k_hf(Dims d, const cplx* __restrict__ rhoA, const cplx* __restrict__ rhoB,
-                                            double wb, int interaction, int hf, double U,
-                                            cplx* __restrict__ hf_out) {
-  constexpr int NBB = NB * NB;
-  __shared__ cplx lds[NBB * 256];
-  cplx loc[NBB];
-#pragma unroll
-  for (int e = 0; e < NBB; ++e) loc[e] = czero();
-  for (int k = threadIdx.x; k < d.nk; k += 256)
-#pragma unroll
-    for (int e = 0; e < NBB; ++e)
-      loc[e] = cadd(loc[e], cadd(cscal(rhoA[(int64_t)k * NBB + e], 1.0 - wb), cscal(rhoB[(int64_t)k * NBB + e], wb)));
-  block_sum_cplx<NBB>(loc, lds);
-  if (threadIdx.x == 0) {
-    double inv = 1.0 / d.nk;
-    cplx out[NBB];
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) out[e] = czero();
-    if (interaction == KBE_DEV_INT_HUBBARD) {
-      if (hf)
-#pragma unroll
-        for (int a = 0; a < NB; ++a) out[a * NB + a] = cmk(U * loc[a * NB + a].x * inv, 0.0);
-    } else {
-      // eq. (ham): -U c_c^dag c_c one-body term; Hartree U n_c / U n_v, Fock -U rho_vc
-      out[NBB - 1] = cmk(-U, 0.0);
-      if constexpr (NB == 2) {
-        if (hf) {
-          out[0] = cadd(out[0], cmk(U * loc[3].x * inv, 0.0));
-          out[3] = cadd(out[3], cmk(U * loc[0].x * inv, 0.0));
-          out[1] = cscal(loc[1], -U * inv);
-          out[2] = cscal(loc[2], -U * inv);
-        }
+__device__ __forceinline__ cplx hf_element(const double* loc, int e, double inv, int interaction, int hf, double U) {
+  cplx out = czero();
+  if (interaction == KBE_DEV_INT_HUBBARD) {
+    if (hf && e % (NB + 1) == 0) out = cmk(U * loc[e / (NB + 1)] * inv, 0.0);
+  } else {
+    // eq. (ham): -U c_c^dag c_c one-body term; Hartree U n_c / U n_v, Fock -U rho_vc
+    if (e == NB * NB - 1) out = cmk(-U, 0.0);
+    if constexpr (NB == 2) {
+      if (hf) {
+        if (e == 0 || e == 3) out.x += U * loc[2 * (3 - e)] * inv;
+        else out = cscal(cmk(loc[2 * e], loc[2 * e + 1]), -U * inv);
       }
     }
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) hf_out[e] = out[e];
   }
+  return out;
 }
-
-// ------------------------------------------------------------------ propagators
-// One wavefront per k. The augmented matrix M = [[-i hbar dt, dt 1], [0, 0]] (2NB x 2NB)
-// has exp(M) = [[V, dt phi1(-i hbar dt)], [0, 1]], so Phi = -i * (top-right block).
-// exp(M / 2^s) by a degree-16 Taylor polynomial (Horner), ||M / 2^s||_F <= 1/4, then s
-// squarings; the square before the last is exp(M/2), whose top-left block is Vh.
 template <int NB>
-__global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ hf,
-                                               double Ax, double Ay, double dt, cplx* __restrict__ props) {
-  constexpr int N2 = 2 * NB, NN = N2 * N2, NBB = NB * NB;
-  __shared__ cplx sX[4][NN], sE[4][NN];
-  int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int k = blockIdx.x * 4 + wv;
-  bool kval = k < d.nk;
-  int r = lane / N2, c = lane - (lane / N2) * N2;
-  bool act = kval && lane < NN;
-  cplx m = czero();
-  if (act) {
-    if (r < NB && c < NB) {
-      cplx h[NBB];
-      bloch_h0<NB>(hop, d.nkx, d.nky, k, Ax, Ay, h);
-      cplx hb = cadd(h[r * NB + c], hf[r * NB + c]);
-      m = cscal(cmuli(hb), -dt);  // -i hbar dt
-    } else if (r < NB && c == r + NB) {
-      m = cmk(dt, 0.0);
+struct PropsShape {
+  static constexpr int LPK = NB == 3 ? 4 : NB;   // lanes per k
+  static constexpr int KPB = 256 / LPK;          // k per block
+};
+template <int NB>
+__global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ rhoA,
+                                               const cplx* __restrict__ rhoB, double wb, int interaction, int hf,
+                                               double U, double Ax, double Ay, double dt, cplx* __restrict__ hf_out,
+                                               cplx* __restrict__ props) {
+  constexpr int NBB = NB * NB, LPK = PropsShape<NB>::LPK, KPB = PropsShape<NB>::KPB;
+  __shared__ double red[NB <= 2 ? 2 * NBB * 256 : 2 * NBB * KPB];   // density sums, then exp(X) of the block's k
+  __shared__ double loc[2 * NBB];
+  __shared__ cplx hfm[NBB];
+  const int t = threadIdx.x;
+  {
+    // local density: the Hubbard field needs the real diagonal only; N_k <= 1024
+    auto rho = [&](int i, int e) {
+      const int k = t + 256 * i;
+      if (k >= d.nk) return czero();
+      const cplx a = rhoA[(int64_t)k * NBB + e];
+      if (wb == 0.0) return a;
+      return cadd(cscal(a, 1.0 - wb), cscal(rhoB[(int64_t)k * NBB + e], wb));
+    };
+    if (interaction == KBE_DEV_INT_HUBBARD) {
+      double v[NB];
+#pragma unroll
+      for (int a = 0; a < NB; ++a) {
+        v[a] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[a] += rho(i, a * (NB + 1)).x;
+      }
+      block_sum_once<NB>(v, red, loc);
+    } else if constexpr (NB == 2) {
+      double v[2 * NBB];
+#pragma unroll
+      for (int e = 0; e < NBB; ++e) {
+        v[2 * e] = v[2 * e + 1] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const cplx r = rho(i, e);
+          v[2 * e] += r.x;
+          v[2 * e + 1] += r.y;
+        }
+      }
+      block_sum_once<2 * NBB>(v, red, loc);
     }
+    if (t < NBB) {
+      hfm[t] = hf_element<NB>(loc, t, 1.0 / d.nk, interaction, hf, U);
+      if (blockIdx.x == 0) hf_out[t] = hfm[t];
+    }
+    __syncthreads();
   }
-  double nrm2 = wave_sum(act ? cabs2(m) : 0.0);
+  const int kl = t / LPK, c = t - kl * LPK;
+  const int k = blockIdx.x * KPB + kl;
+  const bool act = k < d.nk && c < NB;
+  cplx X[NBB];
+  {
+    cplx h[NBB];
+    bloch_h0<NB>(hop, d.nkx, d.nky, act ? k : 0, Ax, Ay, h);
+#pragma unroll
+    for (int e = 0; e < NBB; ++e) X[e] = cscal(cmuli(cadd(h[e], hfm[e])), -dt);  // -i hbar dt
+  }
+  cplx* P = props + (int64_t)(act ? k : 0) * 3 * NBB;
+  double nrm2 = 0.0;
+#pragma unroll
+  for (int e = 0; e < NBB; ++e) nrm2 += cabs2(X[e]);
   int s = 1;
-  double nrm = sqrt(nrm2);
-  while (nrm > ldexp(0.25, s) && s < 60) ++s;
-  double scale = ldexp(1.0, -s);
-  cplx x = cscal(m, scale);
-  cplx id = cmk((act && r == c) ? 1.0 : 0.0, 0.0);
-  if (lane < NN) sX[wv][lane] = x;
-  cplx e = id;
-  if (lane < NN) sE[wv][lane] = e;
-  wave_sync();  // every LDS array here is per wavefront
-  for (int n = 16; n >= 1; --n) {  // E <- 1 + X E / n
-    cplx acc = czero();
-    if (lane < NN)
-#pragma unroll
-      for (int l = 0; l < N2; ++l) cmac(acc, sX[wv][r * N2 + l], sE[wv][l * N2 + c]);
-    wave_sync();  // every LDS array here is per wavefront
-    e = cadd(id, cscal(acc, 1.0 / n));
-    if (lane < NN) sE[wv][lane] = e;
-    wave_sync();  // every LDS array here is per wavefront
-  }
-  cplx half = czero();
-  for (int q = 0; q < s; ++q) {  // E <- E E
-    if (q == s - 1) half = e;
-    cplx acc = czero();
-    if (lane < NN)
-#pragma unroll
-      for (int l = 0; l < N2; ++l) cmac(acc, sE[wv][r * N2 + l], sE[wv][l * N2 + c]);
-    wave_sync();  // every LDS array here is per wavefront
-    e = acc;
-    if (lane < NN) sE[wv][lane] = e;
-    wave_sync();  // every LDS array here is per wavefront
-  }
-  if (act && r < NB) {
-    cplx* P = props + (int64_t)k * 3 * NBB;
-    if (c < NB) {
-      P[r * NB + c] = e;              // V
-      P[NBB + r * NB + c] = half;     // Vh
-    } else {
-      P[2 * NBB + r * NB + (c - NB)] = cneg(cmuli(e));  // Phi = -i * top-right
+  if constexpr (NB == 1) {
+    // E = exp(M), M = [[X, dt], [0, 0]]: entries (0, 0) and (0, 1) of the Horner steps 1 + M E / n
+    // and of the squarings
+    double nrm = sqrt(nrm2 + dt * dt);
+    while (nrm > ldexp(0.25, s) && s < 60) ++s;
+    const double scale = ldexp(1.0, -s);
+    const cplx x = cscal(X[0], scale), y = cmk(dt * scale, 0.0), one = cmk(1.0, 0.0);
+    cplx e0 = one, e1 = czero();
+    for (int n = 16; n >= 1; --n) {
+      cplx a0 = czero(), a1 = czero();
+      cmac(a0, x, e0);
+      cmac(a1, x, e1);
+      cmac(a1, y, one);
+      e0 = cadd(one, cscal(a0, 1.0 / n));
+      e1 = cscal(a1, 1.0 / n);
     }
+    cplx half = czero();
+    for (int q = 0; q < s; ++q) {
+      if (q == s - 1) half = e0;
+      cplx a0 = czero(), a1 = czero();
+      cmac(a0, e0, e0);
+      cmac(a1, e0, e1);
+      cmac(a1, e1, one);
+      e0 = a0;
+      e1 = a1;
+    }
+    if (act) {
+      P[0] = e0;
+      P[1] = half;
+      P[2] = cneg(cmuli(e1));
+    }
+  } else {
+    double nrm = sqrt(nrm2);
+    while (nrm > ldexp(0.25, s) && s < 60) ++s;
+    const double scale = ldexp(1.0, -s);
+#pragma unroll
+    for (int e = 0; e < NBB; ++e) X[e] = cscal(X[e], scale);
+    cplx f[NB], E[NB];   // column c of phi1 and of exp
+    auto mulX = [&](const cplx* v, cplx* out) {
+#pragma unroll
+      for (int r = 0; r < NB; ++r) {
+        out[r] = czero();
+#pragma unroll
+        for (int l = 0; l < NB; ++l) cmac(out[r], X[r * NB + l], v[l]);
+      }
+    };
+#pragma unroll
+    for (int r = 0; r < NB; ++r) f[r] = cmk(r == c ? 1.0 : 0.0, 0.0);
+#pragma unroll
+    for (int n = 13; n >= 1; --n) {
+      cplx u[NB];
+      mulX(f, u);
+#pragma unroll
+      for (int r = 0; r < NB; ++r) f[r] = cadd(cmk(r == c ? 1.0 : 0.0, 0.0), cscal(u[r], 1.0 / (n + 1)));
+    }
+    mulX(f, E);
+#pragma unroll
+    for (int r = 0; r < NB; ++r) E[r].x += r == c ? 1.0 : 0.0;
+    cplx* sE = reinterpret_cast<cplx*>(red) + kl * NBB;   // exp of this k, columns from its lanes (one wavefront)
+    const int smax = wave_max(act ? s : 0);
+    for (int q = 0; q < smax; ++q) {
+      if (act)
+#pragma unroll
+        for (int r = 0; r < NB; ++r) sE[r * NB + c] = E[r];
+      wave_sync();
+      if (act && q < s) {
+        if (q == s - 1)
+#pragma unroll
+          for (int r = 0; r < NB; ++r) P[NBB + r * NB + c] = E[r];   // Vh
+        cplx e2[NB], f2[NB];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) {
+          e2[r] = f2[r] = czero();
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            const cplx x = sE[r * NB + l];
+            cmac(e2[r], x, E[l]);
+            cmac(f2[r], x, f[l]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < NB; ++r) {
+          E[r] = e2[r];
+          f[r] = cscal(cadd(f2[r], f[r]), 0.5);
+        }
+      }
+      wave_sync();
+    }
+    if (act)
+#pragma unroll
+      for (int r = 0; r < NB; ++r) {
+        P[r * NB + c] = E[r];                                          // V
+        P[2 * NBB + r * NB + c] = cneg(cmuli(cscal(f[r], dt)));        // Phi
+      }
   }
 }
 
@@ -2425,14 +2509,10 @@ struct Launch {
                        a.row64, a.col0, a.diag);
     return hipGetLastError();
   }
-  static hipError_t hf(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
-    hipLaunchKernelGGL(k_hf<NB>, dim3(1), dim3(256), 0, st, d, (const cplx*)a.rho_prev, (const cplx*)a.rho_cur,
-                       wb, a.interaction, a.hf, a.U, a.hfbuf);
-    return hipGetLastError();
-  }
-  static hipError_t props(const Dims& d, const LaunchArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_props<NB>, dim3((d.nk + 3) / 4), dim3(256), 0, st, d, a.hop, (const cplx*)a.hfbuf,
-                       a.Ax, a.Ay, a.dt, a.props);
+  static hipError_t props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
+    constexpr int KPB = PropsShape<NB>::KPB;
+    hipLaunchKernelGGL(k_props<NB>, dim3((d.nk + KPB - 1) / KPB), dim3(256), 0, st, d, a.hop, (const cplx*)a.rho_prev,
+                       (const cplx*)a.rho_cur, wb, a.interaction, a.hf, a.U, a.Ax, a.Ay, a.dt, a.hfbuf, a.props);
     return hipGetLastError();
   }
   static hipError_t sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
@@ -2548,10 +2628,9 @@ hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t st) {
   }
 
 hipError_t launch_init(const Dims& d, const LaunchArgs& a, hipStream_t st) { KBE_DISPATCH(d.nb, init(d, a, st)); }
-hipError_t launch_hf(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
-  KBE_DISPATCH(d.nb, hf(d, a, wb, st));
+hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
+  KBE_DISPATCH(d.nb, props(d, a, wb, st));
 }
-hipError_t launch_props(const Dims& d, const LaunchArgs& a, hipStream_t st) { KBE_DISPATCH(d.nb, props(d, a, st)); }
 hipError_t launch_sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
   KBE_DISPATCH(d.nb, sigma(d, a, m, st));
 }

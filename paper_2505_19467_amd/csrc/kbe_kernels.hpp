@@ -52,8 +52,8 @@ struct LaunchArgs {
 
 hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t st);
 hipError_t launch_init(const Dims& d, const LaunchArgs& a, hipStream_t st);
-hipError_t launch_hf(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st);
-hipError_t launch_props(const Dims& d, const LaunchArgs& a, hipStream_t st);
+// mean field (into hfbuf) and propagators for the density (1 - wb) rho_prev + wb rho_cur
+hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st);
 hipError_t launch_sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
 // the paper's direct-sum self-energy (interband preset, chain with even n <= 1024)
 hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
