@@ -313,27 +313,26 @@ struct kbe_ctx {
     if (e != hipSuccess) return fail(KBE_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
     return KBE_OK;
   }
-  int bulk_timed(const LaunchArgs& a, int m) {
+  int collide(const LaunchArgs& a, int m, bool with_props) {
     // the event pool is created whole by kbe_timing before any launch is queued; launches past
     // its end (more passes than it was sized for) run untimed
-    if (timing && m >= 1 && ev_used + 2 <= ev.size()) {
-      if (hipEventRecord(ev[ev_used], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
-      int rc = check(kbe::launch_bulk(L.d, a, m, st), "history-sum launch");
-      if (rc) return rc;
+    const bool timed = timing && m >= 1 && ev_used + 2 <= ev.size();
+    if (timed && hipEventRecord(ev[ev_used], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
+    int rc = check(kbe::launch_collide(L.d, a, m, with_props, st), "history-sum launch");
+    if (rc) return rc;
+    if (timed) {
       if (hipEventRecord(ev[ev_used + 1], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
       ev_used += 2;
       ev_m.push_back(m);
-    } else {
-      int rc = check(kbe::launch_bulk(L.d, a, m, st), "history-sum launch");
-      if (rc) return rc;
     }
     return KBE_OK;
   }
-  // Sigma row, equal-time collision integral, history sums of row m.
-  int collision_parts(LaunchArgs& a, int m) {
+  // Sigma row, equal-time collision integral, history sums of row m; with_props: also the
+  // propagators of the corrector's update.
+  int collision_parts(LaunchArgs& a, int m, bool with_props = false) {
+    if (with_props) set_A(a, (m - 0.5) * cfg.dt);
     int rc = check(kbe::launch_sigma(L.d, a, m, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_diag_I(L.d, a, m, st), "equal-time collision launch");
-    if (!rc) rc = bulk_timed(a, m);
+    if (!rc) rc = collide(a, m, with_props);
     return rc;
   }
   // The dipole pulse E(t) = I delta(t - t0) of eq. (dipole) acts as the kick K = exp(-i I X) on the
@@ -376,8 +375,7 @@ struct kbe_ctx {
     double last_change = 0.0;
     int taken = 0;
     for (int it = 0; it < cfg.n_corr && !rc; ++it) {
-      rc = collision_parts(a, m);
-      if (!rc) rc = props(a, m, 1);
+      rc = collision_parts(a, m, true);
       a.chg = tol ? buf<double>(B_CHG) : nullptr;
       if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_CORRECT, st), "corrector launch");
       a.chg = nullptr;
@@ -517,8 +515,7 @@ struct kbe_ctx {
     e.I_cur = b.Ire_prev;
     e.D_cur = b.Dscratch;
     if (!rc) rc = check(kbe::launch_sigma(d, e, m - 1, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_diag_I(d, e, m - 1, st), "equal-time collision launch");
-    if (!rc) rc = check(kbe::launch_bulk(d, e, m - 1, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, false, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
     // recompute the predictor (row m of the working copy only)
     LaunchArgs p = a;
@@ -538,10 +535,8 @@ struct kbe_ctx {
     c.props = b.props_c;
     c.hfbuf = b.hf_c;
     if (!rc) rc = check(kbe::launch_sigma(d, c, m, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_diag_I(d, c, m, st), "equal-time collision launch");
-    if (!rc) rc = check(kbe::launch_bulk(d, c, m, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_collide(d, c, m, true, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, c, m, KBE_ROW_EVAL, st), "collision-row launch");
-    if (!rc) rc = check(kbe::launch_props(d, c, 0.5, st), "propagator launch");
     // corrector update, its propagators and mean field
     if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, b.lam, b.Rbar, rho0, st), "adjoint update launch");
     if (!rc) rc = check(kbe::launch_adj_props(d, a, b, b.hf_c, st), "adjoint propagator launch");
@@ -827,8 +822,7 @@ int kbe_stage_collision(kbe_ctx* ctx, int32_t m) {
   int rc = check_m(ctx, m, 0);
   if (rc) return rc;
   LaunchArgs a = ctx->args();
-  rc = ctx->check(kbe::launch_diag_I(ctx->L.d, a, m, ctx->st), "equal-time collision launch");
-  if (!rc) rc = ctx->bulk_timed(a, m);
+  rc = ctx->collide(a, m, false);
   if (!rc) rc = ctx->check(kbe::launch_row(ctx->L.d, a, m, KBE_ROW_EVAL, ctx->st), "collision-row launch");
   return rc;
 }

@@ -343,16 +343,17 @@ __device__ __forceinline__ void block_sum_cplx(cplx* v, cplx* lds /* [N][256] */
   __syncthreads();
 }
 
-// Block sums of N values per thread (256 threads) into out[N], with two block barriers: the values
+// Block sums of N values of the first 256 threads into out[N], with two block barriers: the values
 // of threads t, t + 64, t + 128, t + 192 are added pairwise by one wavefront per value, then across
-// its lanes (the order of block_sum_cplx).
+// its lanes (the order of block_sum_cplx). Every thread of the block calls it.
 template <int N>
 __device__ __forceinline__ void block_sum_once(const double* v, double* lds /* [N][256] */, double* out) {
   const int t = threadIdx.x, lane = t & 63;
+  if (t < 256)
 #pragma unroll
-  for (int i = 0; i < N; ++i) lds[i * 256 + t] = v[i];
+    for (int i = 0; i < N; ++i) lds[i * 256 + t] = v[i];
   __syncthreads();
-  for (int i = t >> 6; i < N; i += 4) {
+  for (int i = t >> 6; i < N; i += blockDim.x >> 6) {
     const double* x = lds + i * 256 + lane;
     double a = (x[0] + x[128]) + (x[64] + x[192]);
 #pragma unroll

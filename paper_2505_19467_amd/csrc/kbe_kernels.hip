@@ -9,10 +9,11 @@
 //   k_sigma_fwd/ib  the same for the interband preset: lines to real space, then products
 //                   and back
 //   k_sigma_direct  the paper's direct momentum sums for the interband preset (comparison)
-//   k_diag_I        equal-time collision integral I^<(t_m, t_m) and D_m
 //   k_hist_pair, k_hist_bulk(_split) and their FP32 forms
 //                   the history sums of eq. (CI): stream the packed triangle of rows 0..m-1
-//                   once, every stored block feeding its column and its row
+//                   once, every stored block feeding its column and its row; in front of them
+//                   the equal-time collision integral I^<(t_m, t_m) and D_m (and, in a corrector
+//                   pass, the propagators), k_extras where there is no history yet
 //   k_row           end-point terms (trapezoid or Gregory), collision row assembly,
 //                   predictor/corrector update
 //   k_change_max    the corrector's row change (stopping rule)
@@ -184,21 +185,33 @@ struct PropsShape {
   static constexpr int LPK = NB == 3 ? 4 : NB;   // lanes per k
   static constexpr int KPB = 256 / LPK;          // k per block
 };
+struct PropsArgs {
+  const cplx *hop, *rhoA, *rhoB;
+  cplx *hf_out, *props;
+  double wb, U, Ax, Ay, dt;
+  int interaction, hf;
+};
+// Block blk of the propagator blocks, any block of at least 256 threads; red: props_lds<NB>() doubles.
 template <int NB>
-__global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ rhoA,
-                                               const cplx* __restrict__ rhoB, double wb, int interaction, int hf,
-                                               double U, double Ax, double Ay, double dt, cplx* __restrict__ hf_out,
-                                               cplx* __restrict__ props) {
+constexpr int props_lds() {
+  constexpr int sums = (NB == 2 ? 8 : NB) * 256, mats = 2 * NB * NB * PropsShape<NB>::KPB;
+  return (NB == 1 || sums > mats ? sums : mats) + 4 * NB * NB;
+}
+template <int NB>
+__device__ __forceinline__ void props_block(const Dims& d, const PropsArgs& x, int blk, double* red) {
   constexpr int NBB = NB * NB, LPK = PropsShape<NB>::LPK, KPB = PropsShape<NB>::KPB;
-  __shared__ double red[NB <= 2 ? 2 * NBB * 256 : 2 * NBB * KPB];   // density sums, then exp(X) of the block's k
-  __shared__ double loc[2 * NBB];
-  __shared__ cplx hfm[NBB];
+  double* loc = red + props_lds<NB>() - 4 * NBB;
+  cplx* hfm = reinterpret_cast<cplx*>(loc + 2 * NBB);
+  const cplx* __restrict__ rhoA = x.rhoA;
+  const cplx* __restrict__ rhoB = x.rhoB;
+  const double wb = x.wb, U = x.U, dt = x.dt;
+  const int interaction = x.interaction, hf = x.hf;
   const int t = threadIdx.x;
   {
     // local density: the Hubbard field needs the real diagonal only; N_k <= 1024
     auto rho = [&](int i, int e) {
       const int k = t + 256 * i;
-      if (k >= d.nk) return czero();
+      if (k >= d.nk || t >= 256) return czero();
       const cplx a = rhoA[(int64_t)k * NBB + e];
       if (wb == 0.0) return a;
       return cadd(cscal(a, 1.0 - wb), cscal(rhoB[(int64_t)k * NBB + e], wb));
@@ -228,21 +241,21 @@ __global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ 
     }
     if (t < NBB) {
       hfm[t] = hf_element<NB>(loc, t, 1.0 / d.nk, interaction, hf, U);
-      if (blockIdx.x == 0) hf_out[t] = hfm[t];
+      if (blk == 0) x.hf_out[t] = hfm[t];
     }
     __syncthreads();
   }
   const int kl = t / LPK, c = t - kl * LPK;
-  const int k = blockIdx.x * KPB + kl;
-  const bool act = k < d.nk && c < NB;
+  const int k = blk * KPB + kl;
+  const bool act = t < 256 && k < d.nk && c < NB;
   cplx X[NBB];
   {
     cplx h[NBB];
-    bloch_h0<NB>(hop, d.nkx, d.nky, act ? k : 0, Ax, Ay, h);
+    bloch_h0<NB>(x.hop, d.nkx, d.nky, act ? k : 0, x.Ax, x.Ay, h);
 #pragma unroll
     for (int e = 0; e < NBB; ++e) X[e] = cscal(cmuli(cadd(h[e], hfm[e])), -dt);  // -i hbar dt
   }
-  cplx* P = props + (int64_t)(act ? k : 0) * 3 * NBB;
+  cplx* P = x.props + (int64_t)(act ? k : 0) * 3 * NBB;
   double nrm2 = 0.0;
 #pragma unroll
   for (int e = 0; e < NBB; ++e) nrm2 += cabs2(X[e]);
@@ -253,12 +266,12 @@ __global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ 
     double nrm = sqrt(nrm2 + dt * dt);
     while (nrm > ldexp(0.25, s) && s < 60) ++s;
     const double scale = ldexp(1.0, -s);
-    const cplx x = cscal(X[0], scale), y = cmk(dt * scale, 0.0), one = cmk(1.0, 0.0);
+    const cplx xs = cscal(X[0], scale), y = cmk(dt * scale, 0.0), one = cmk(1.0, 0.0);
     cplx e0 = one, e1 = czero();
     for (int n = 16; n >= 1; --n) {
       cplx a0 = czero(), a1 = czero();
-      cmac(a0, x, e0);
-      cmac(a1, x, e1);
+      cmac(a0, xs, e0);
+      cmac(a1, xs, e1);
       cmac(a1, y, one);
       e0 = cadd(one, cscal(a0, 1.0 / n));
       e1 = cscal(a1, 1.0 / n);
@@ -322,9 +335,9 @@ __global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ 
           e2[r] = f2[r] = czero();
 #pragma unroll
           for (int l = 0; l < NB; ++l) {
-            const cplx x = sE[r * NB + l];
-            cmac(e2[r], x, E[l]);
-            cmac(f2[r], x, f[l]);
+            const cplx el = sE[r * NB + l];
+            cmac(e2[r], el, E[l]);
+            cmac(f2[r], el, f[l]);
           }
         }
 #pragma unroll
@@ -342,6 +355,11 @@ __global__ __launch_bounds__(256) void k_props(Dims d, const cplx* __restrict__ 
         P[2 * NBB + r * NB + c] = cneg(cmuli(cscal(f[r], dt)));        // Phi
       }
   }
+}
+template <int NB>
+__global__ __launch_bounds__(256) void k_props(Dims d, PropsArgs x) {
+  __shared__ double red[props_lds<NB>()];
+  props_block<NB>(d, x, blockIdx.x, red);
 }
 
 // ------------------------------------------------------------------ self-energy
@@ -635,56 +653,113 @@ __global__ __launch_bounds__(512) void k_sigma_direct(Dims d, const cplx* __rest
 // I^<(t_m, t_m) = dt sum_j a_j [Sigma^>_mj G^<_jm - Sigma^<_mj G^>_jm],  G_jm = -(G_mj)^dag
 // for j < m, a_j the quadrature weights on [0, t_m] (trapezoid, or with Gregory end
 // corrections); I^>(t_m, t_m) is the same matrix (both integrals of eq. (CI) run over
-// [0, t_m] and combine term by term). One block per k.
+// [0, t_m] and combine term by term). One block of at least 256 threads per k.
+// Thread (row a, j) of 256: NB complex sums of one row each.
 template <int NB>
-__global__ __launch_bounds__(256) void k_diag_I(Dims d, const cplx* __restrict__ row64,
-                                                const cplx* __restrict__ sig, cplx* __restrict__ Icur,
-                                                cplx* __restrict__ Dcur, int m, double dt, QuadW Q) {
-  constexpr int NBB = NB * NB;
-  __shared__ cplx lds[NBB * 256];
-  int k = blockIdx.x;
-  cplx acc[NBB];
-  mat_zero<NB>(acc);
-  if (m > 0) {
-    for (int j = threadIdx.x; j <= m; j += 256) {
-      double wgt = quad_w(Q, j, m);
-      cplx Gl[NBB], Gg[NBB], Sl[NBB], Sg[NBB], t[NBB];
+constexpr int diag_lds() {
+  return 2 * NB * 256;
+}
+template <int NB>
+__device__ __forceinline__ void diag_block(const Dims& d, const cplx* __restrict__ row64, const cplx* __restrict__ sig,
+                                           cplx* __restrict__ Icur, cplx* __restrict__ Dcur, int m, double dt,
+                                           const QuadW& Q, int k, double* lds) {
+  constexpr int NBB = NB * NB, RP = PropsShape<NB>::LPK, JT = 256 / RP;   // rows (padded), j per round
+  const int t = threadIdx.x, a = t / JT;
+  cplx acc[NB];
 #pragma unroll
-      for (int e = 0; e < NBB; ++e) {
-        Gl[e] = row64[row64_idx(d, m, k, e, j)];
-        Gg[e] = row64[row64_idx(d, m, k, NBB + e, j)];
-        Sl[e] = sig[sig_idx(d, k, 0, e, j)];
-        Sg[e] = sig[sig_idx(d, k, 1, e, j)];
+  for (int b = 0; b < NB; ++b) acc[b] = czero();
+  if (m > 0 && a < NB && t < 256) {
+    for (int j = t - a * JT; j <= m; j += JT) {
+      const double wgt = quad_w(Q, j, m);
+      cplx u[NB], v[NB], Sl[NB], Sg[NB];
+#pragma unroll
+      for (int l = 0; l < NB; ++l) {
+        Sl[l] = sig[sig_idx(d, k, 0, a * NB + l, j)];
+        Sg[l] = sig[sig_idx(d, k, 1, a * NB + l, j)];
+        u[l] = v[l] = czero();
       }
       // j < m: G_jm = -G_mj^dag, so Sg G^<_jm - Sl G^>_jm = Sl Gg^dag - Sg Gl^dag;
       // j = m: the stored equal-time block, Sg Gl - Sl Gg.
-      cplx u[NBB];
-      mat_zero<NB>(t);
-      mat_zero<NB>(u);
       if (j < m) {
-        mm_acc_bdag<NB>(t, Sl, Gg);
-        mm_acc_bdag<NB>(u, Sg, Gl);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            cmacc(u[b], Sl[l], row64[row64_idx(d, m, k, NBB + b * NB + l, j)]);
+            cmacc(v[b], Sg[l], row64[row64_idx(d, m, k, b * NB + l, j)]);
+          }
       } else {
-        mm_acc<NB>(t, Sg, Gl);
-        mm_acc<NB>(u, Sl, Gg);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            cmac(u[b], Sg[l], row64[row64_idx(d, m, k, l * NB + b, j)]);
+            cmac(v[b], Sl[l], row64[row64_idx(d, m, k, NBB + l * NB + b, j)]);
+          }
       }
 #pragma unroll
-      for (int e = 0; e < NBB; ++e) acc[e] = cadd(acc[e], cscal(csub(t[e], u[e]), wgt));
+      for (int b = 0; b < NB; ++b) acc[b] = cadd(acc[b], cscal(csub(u[b], v[b]), wgt));
     }
   }
-  block_sum_cplx<NBB>(acc, lds);
-  if (threadIdx.x == 0) {
+  // sums over the JT threads of a row
+  if (t < 256)
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+    for (int b = 0; b < NB; ++b) {
+      lds[(2 * b) * 256 + t] = acc[b].x;
+      lds[(2 * b + 1) * 256 + t] = acc[b].y;
+    }
+  __syncthreads();
+  const int lane = t & 63;
+  for (int i = t >> 6; i < 2 * NBB; i += blockDim.x >> 6) {
+    const int r = i / (2 * NB), q = i - r * 2 * NB;   // row, real/imaginary part of column q / 2
+    const double* x = lds + q * 256 + r * JT + lane;
+    double v;
+    if constexpr (JT == 256) v = (x[0] + x[128]) + (x[64] + x[192]);
+    else if constexpr (JT == 128) v = x[0] + x[64];
+    else v = x[0];
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        cplx I = cscal(acc[a * NB + b], dt);
-        Icur[rowbuf_idx(d, k, a * NB + b, m)] = I;
-        Icur[rowbuf_idx(d, k, NBB + a * NB + b, m)] = I;
-        cplx Dv = cadd(cscal(acc[a * NB + b], dt), cconj(cscal(acc[b * NB + a], dt)));
-        Dcur[(int64_t)k * NBB + a * NB + b] = Dv;
-      }
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    // the sum's own place in LDS is read by no other wavefront
+    if (lane == 0) lds[q * 256 + r * JT] = v;
   }
+  __syncthreads();
+  if (t < NBB) {
+    const int r = t / NB, b = t - r * NB;
+    auto sum = [&](int i, int j) { return cmk(lds[2 * j * 256 + i * JT], lds[(2 * j + 1) * 256 + i * JT]); };
+    const cplx I = cscal(sum(r, b), dt);
+    Icur[rowbuf_idx(d, k, t, m)] = I;
+    Icur[rowbuf_idx(d, k, NBB + t, m)] = I;
+    Dcur[(int64_t)k * NBB + t] = cadd(I, cconj(cscal(sum(b, r), dt)));
+  }
+}
+
+// Blocks that ride in front of a history pass's own, on work that is independent of it: the
+// equal-time integral of each k and, in a corrector pass, the propagators of the iterate. Both are a
+// few microseconds of latency and N_k (resp. N_k nb / 256) blocks; in launches of their own they held
+// up the stream 5 and 4 us per pass.
+struct PassExtras {
+  const cplx *row64, *sig;
+  cplx *Icur, *Dcur;
+  double dt;
+  QuadW Q;
+  int m, nprops;      // nprops: propagator blocks (0: none)
+  PropsArgs props;
+  __host__ __device__ int blocks(const Dims& d) const { return d.nk + nprops; }
+};
+template <int NB>
+constexpr int extras_lds() {
+  return props_lds<NB>() > diag_lds<NB>() ? props_lds<NB>() : diag_lds<NB>();
+}
+template <int NB>
+__device__ __forceinline__ void extras_block(const Dims& d, const PassExtras& x, int blk, void* lds) {
+  double* w = reinterpret_cast<double*>(lds);
+  if (blk < x.nprops) props_block<NB>(d, x.props, blk, w);
+  else diag_block<NB>(d, x.row64, x.sig, x.Icur, x.Dcur, x.m, x.dt, x.Q, blk - x.nprops, w);
+}
+template <int NB>
+__global__ __launch_bounds__(256) void k_extras(Dims d, PassExtras x) {
+  __shared__ double lds[extras_lds<NB>()];
+  extras_block<NB>(d, x, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------ history sums (hot loop)
@@ -795,7 +870,7 @@ __device__ __forceinline__ void flush_chunk_fold(const cplx* st0, const cplx* st
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restrict__ hist,
                                                    const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-                                                   cplx* __restrict__ rowpart, int m, int lgL) {
+                                                   cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int R = NB == 1 ? 4 : 1;
   __shared__ cplx red[3][C][64];
@@ -803,8 +878,14 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
   constexpr int ROWS_ST = 256;
   __shared__ cplx stg[NBB][ROWS_ST];
   __shared__ cplx sS[2][2][NBB][64];  // [strip of the pair][Sigma^<, Sigma^>][e][lane]
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(red) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, red);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<128>(task, m, lgL);
   const int sp = ht.s, r0 = ht.r0, r1 = ht.r1;
   const int lane = threadIdx.x & 63;
@@ -979,15 +1060,21 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __restrict__ hist,
                                                      const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-                                                     cplx* __restrict__ rowpart, int m, int lgL) {
+                                                     cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int R = NB == 1 ? 4 : 2;
   __shared__ cplx red[3][C][64];
   constexpr int ROWS_ST = 256;   // row partials staged over four 64-row chunks, as in k_hist_pair
   __shared__ cplx stg[NBB][ROWS_ST];
   __shared__ cplx32 sS[2][2][NBB][64];
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(red) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, red);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<128>(task, m, lgL);
   const int sp = ht.s, r0 = ht.r0, r1 = ht.r1;
   const int lane = threadIdx.x & 63;
@@ -1177,13 +1264,19 @@ __global__ __launch_bounds__(256) void k_hist_pair32(Dims d, const cplx32* __res
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restrict__ hist,
                                                    const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-                                                   cplx* __restrict__ rowpart, int m, int lgL) {
+                                                   cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int CH = (C < 8) ? C : 8;  // components per LDS combine round
   __shared__ cplx red[3][CH][64];
   __shared__ cplx sS[2][NBB][64];
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(red) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, red);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<64>(task, m, lgL);
   const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
@@ -1262,14 +1355,20 @@ __global__ __launch_bounds__(256) void k_hist_bulk(Dims d, const cplx* __restric
 template <int NB>
 __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __restrict__ hist,
                                                      const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-                                                     cplx* __restrict__ rowpart, int m, int lgL) {
+                                                     cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int CH = (C < 8) ? C : 8;
   constexpr int R = 2;
   constexpr int FLUSH = 16 / R;  // iterations per FP32 accumulation tile (16 rows)
   __shared__ cplx red[3][CH][64];
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(red) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, red);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<64>(task, m, lgL);
   const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
@@ -1400,14 +1499,20 @@ __global__ __launch_bounds__(256) void k_hist_bulk32(Dims d, const cplx32* __res
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_hist_bulk_split(
     Dims d, const cplx* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-    cplx* __restrict__ rowpart, int m, int lgL) {
+    cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   static_assert(NB == 4, "the four block rows share one reduce-scatter");
   __shared__ cplx sS[2][NBB][64];  // [half][e][lane]: half 0 needs Sigma^>, half 1 Sigma^<;
                                    // reused for the column-sum combine after the row loop
   __shared__ cplx stg[2][2][2][NBB * 16];  // [buffer][row pair][half][e * 16 + row]
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(sS) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, sS);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<64>(task, m, lgL);
   const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
@@ -1496,15 +1601,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_hist_bulk32_split(
     Dims d, const cplx32* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-    cplx* __restrict__ rowpart, int m, int lgL) {
+    cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   static_assert(NB == 4, "the four block rows share one reduce-scatter");
   static_assert(NBB % 2 == 0, "component pairs must not straddle the halves");
   __shared__ cplx32 sS[2][NBB][64];
   __shared__ cplx stg[2][2][NBB * 32];  // [buffer][half][e * 32 + row - cb]; column-sum combine
                                         // after the row loop
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(stg) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, stg);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<64>(task, m, lgL);
   const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   int lane = threadIdx.x & 63;
@@ -1728,7 +1839,7 @@ struct AfrFill {
 template <int NB>
 __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_hist_mfma(
     Dims d, const float2* __restrict__ hist, const cplx* __restrict__ sig, cplx* __restrict__ colpart,
-    cplx* __restrict__ rowpart, int m, int lgL) {
+    cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   using Sh = MfmaShape<NB>;
   constexpr int NBB = Sh::NBB, C = Sh::C, HS = Sh::HS, NCH = Sh::NCH, VP = Sh::VP, CQ = Sh::CQ, WAVES = Sh::WAVES;
   static_assert(HS == 2 || NBB % 2 == 0, "halves must not share a 16-byte load");
@@ -1738,8 +1849,14 @@ __global__ __launch_bounds__(MfmaShape<NB>::WAVES * 64) __attribute__((amdgpu_wa
   float* stg = reinterpret_cast<float*>(smem);  // [2][WAVES][CQ][4][VP]
   float* afr = reinterpret_cast<float*>(smem + Sh::STAGE);  // [2][CQ][64][2 nb]
   constexpr int NTHR = WAVES * 64, NE = (CQ * 64 + NTHR - 1) / NTHR;
-  const int task = blockIdx.x / d.nk;
-  const int k = blockIdx.x - task * d.nk;
+  static_assert(sizeof(smem) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  const int nx = x.blocks(d);
+  if ((int)blockIdx.x < nx) {
+    extras_block<NB>(d, x, blockIdx.x, smem);
+    return;
+  }
+  const int task = (blockIdx.x - nx) / d.nk;
+  const int k = blockIdx.x - nx - task * d.nk;
   const HistTask ht = hist_task<64>(task, m, lgL);
   const int s = ht.s, r0 = ht.r0, r1 = ht.r1;
   const int qs = (r0 - 64 * s) >> 2;      // the segment's first quad
@@ -2509,10 +2626,12 @@ struct Launch {
                        a.row64, a.col0, a.diag);
     return hipGetLastError();
   }
+  static int props_blocks(const Dims& d) { return (d.nk + PropsShape<NB>::KPB - 1) / PropsShape<NB>::KPB; }
+  static PropsArgs props_args(const LaunchArgs& a, double wb) {
+    return {a.hop, a.rho_prev, a.rho_cur, a.hfbuf, a.props, wb, a.U, a.Ax, a.Ay, a.dt, a.interaction, a.hf};
+  }
   static hipError_t props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
-    constexpr int KPB = PropsShape<NB>::KPB;
-    hipLaunchKernelGGL(k_props<NB>, dim3((d.nk + KPB - 1) / KPB), dim3(256), 0, st, d, a.hop, (const cplx*)a.rho_prev,
-                       (const cplx*)a.rho_cur, wb, a.interaction, a.hf, a.U, a.Ax, a.Ay, a.dt, a.hfbuf, a.props);
+    hipLaunchKernelGGL(k_props<NB>, dim3(props_blocks(d)), dim3(256), 0, st, d, props_args(a, wb));
     return hipGetLastError();
   }
   static hipError_t sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
@@ -2546,41 +2665,43 @@ struct Launch {
     hipLaunchKernelGGL(kern, dim3(per * 8), dim3(256), shm, st, d, (const cplx*)a.row64, a.sig, m, a.UU, a.corr);
     return hipGetLastError();
   }
-  static hipError_t diag_I(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-    hipLaunchKernelGGL(k_diag_I<NB>, dim3(d.nk), dim3(256), 0, st, d, (const cplx*)a.row64, (const cplx*)a.sig,
-                       a.I_cur, a.D_cur, m, a.dt, a.quad);
-    return hipGetLastError();
-  }
-  static hipError_t bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-    if (m < 1) return hipSuccess;
+  // the history sums and the equal-time integral of row m; with_props: the corrector's propagators too
+  static hipError_t collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st) {
+    PassExtras x{a.row64, a.sig, a.I_cur, a.D_cur, a.dt, a.quad, m, with_props ? props_blocks(d) : 0,
+                 props_args(a, 0.5)};
+    const int nx = x.blocks(d);
+    if (m < 1) {
+      hipLaunchKernelGGL(k_extras<NB>, dim3(nx), dim3(256), 0, st, d, x);
+      return hipGetLastError();
+    }
     const int lgL = hist_lgseg(d, m);
     const int ns = hist_tasks(64 * d.spb, m, lgL);
     if (d.mfma) {
-      hipLaunchKernelGGL(k_hist_mfma<NB>, dim3(ns * d.nk), dim3(MfmaShape<NB>::WAVES * 64), 0, st, d,
-                         (const float2*)a.hist, (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+      hipLaunchKernelGGL(k_hist_mfma<NB>, dim3(nx + ns * d.nk), dim3(MfmaShape<NB>::WAVES * 64), 0, st, d,
+                         (const float2*)a.hist, (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
       return hipGetLastError();
     }
     if constexpr (NB <= 2) {
       if (d.fp32)
-        hipLaunchKernelGGL(k_hist_pair32<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_pair32<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
       else
-        hipLaunchKernelGGL(k_hist_pair<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_pair<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
     } else if constexpr (NB == 4) {
       if (d.fp32)
-        hipLaunchKernelGGL(k_hist_bulk32_split<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_bulk32_split<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
       else
-        hipLaunchKernelGGL(k_hist_bulk_split<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_bulk_split<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
     } else {
       if (d.fp32)
-        hipLaunchKernelGGL(k_hist_bulk32<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_bulk32<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
       else
-        hipLaunchKernelGGL(k_hist_bulk<NB>, dim3(ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
-                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL);
+        hipLaunchKernelGGL(k_hist_bulk<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
+                           (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
     }
     return hipGetLastError();
   }
@@ -2649,11 +2770,8 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
                      a.corr);
   return hipGetLastError();
 }
-hipError_t launch_diag_I(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-  KBE_DISPATCH(d.nb, diag_I(d, a, m, st));
-}
-hipError_t launch_bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
-  KBE_DISPATCH(d.nb, bulk(d, a, m, st));
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st) {
+  KBE_DISPATCH(d.nb, collide(d, a, m, with_props, st));
 }
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st) {
   KBE_DISPATCH(d.nb, row(d, a, m, mode, st));

@@ -60,8 +60,9 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
 // the dipole kick on the completed slice m (nb = 2): the row's copies and rho_cur (and rho_other)
 hipError_t launch_kick(const Dims& d, const LaunchArgs& a, int m, double kc, double ks, cplx* rho_other,
                        hipStream_t st);
-hipError_t launch_diag_I(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
-hipError_t launch_bulk(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
+// history sums of row m and the equal-time integral I(t_m, t_m), D_m; with_props: also what
+// launch_props(d, a, 0.5, st) does (independent work in the same launch)
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st);
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st);
 // out[0] = max of the row kernel's per-block changes at row m (one block, deterministic)
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st);
