@@ -313,12 +313,12 @@ struct kbe_ctx {
     if (e != hipSuccess) return fail(KBE_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
     return KBE_OK;
   }
-  int collide(const LaunchArgs& a, int m, bool with_props) {
+  int collide(const LaunchArgs& a, int m, bool with_props, const kbe::ObsStep* o = nullptr) {
     // the event pool is created whole by kbe_timing before any launch is queued; launches past
     // its end (more passes than it was sized for) run untimed
     const bool timed = timing && m >= 1 && ev_used + 2 <= ev.size();
     if (timed && hipEventRecord(ev[ev_used], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
-    int rc = check(kbe::launch_collide(L.d, a, m, with_props, st), "history-sum launch");
+    int rc = check(kbe::launch_collide(L.d, a, m, with_props, o, st), "history-sum launch");
     if (rc) return rc;
     if (timed) {
       if (hipEventRecord(ev[ev_used + 1], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
@@ -328,11 +328,13 @@ struct kbe_ctx {
     return KBE_OK;
   }
   // Sigma row, equal-time collision integral, history sums of row m; with_props: also the
-  // propagators of the corrector's update.
+  // propagators of the corrector's update. Takes the observables of the step before along.
   int collision_parts(LaunchArgs& a, int m, bool with_props = false) {
     if (with_props) set_A(a, (m - 0.5) * cfg.dt);
     int rc = check(kbe::launch_sigma(L.d, a, m, st), "self-energy launch");
-    if (!rc) rc = collide(a, m, with_props);
+    const bool o = obs_due && kbe::obs_in_pass(L.d);
+    if (!rc) rc = collide(a, m, with_props, o ? &obs_step : nullptr);
+    if (!rc && o) obs_due = false;
     return rc;
   }
   // The dipole pulse E(t) = I delta(t - t0) of eq. (dipole) acts as the kick K = exp(-i I X) on the
@@ -341,8 +343,9 @@ struct kbe_ctx {
   // kicked and the slice's self-energy and collision integrals are evaluated again on the kicked
   // row; they feed the next step's predictor (at m0 = 0 the integrals are empty).
   int kick_slice() const { return (int)std::floor(pulse.t0 / cfg.dt + 0.5); }
+  bool kicked(int m) const { return pulse.kind == KBE_PULSE_DIPOLE_KICK && m == kick_slice(); }
   int dipole_kick(int m) {
-    if (pulse.kind != KBE_PULSE_DIPOLE_KICK || m != kick_slice()) return KBE_OK;
+    if (!kicked(m)) return KBE_OK;
     LaunchArgs a = args();
     int rc = check(kbe::launch_kick(L.d, a, m, std::cos(pulse.amp), std::sin(pulse.amp),
                                     m == 0 ? a.rho_prev : a.rho_cur, st),
@@ -353,15 +356,32 @@ struct kbe_ctx {
   }
   int props(LaunchArgs& a, int m, int mode) {
     set_A(a, (m - 0.5) * cfg.dt);
-    return check(kbe::launch_props(L.d, a, mode == 0 ? 0.0 : 0.5, st), "propagator launch");
+    const bool o = obs_due && !kbe::obs_in_pass(L.d);
+    int rc = check(kbe::launch_props(L.d, a, mode == 0 ? 0.0 : 0.5, o ? &obs_step : nullptr, st), "propagator launch");
+    if (!rc && o) obs_due = false;
+    return rc;
   }
-  int observe(int m) {
+  // The observables of step m. Its density and collision row stay as they are through step m + 1,
+  // so between the steps of one kbe_step call the launch is left to step m + 1 (obs_due), whose
+  // first history pass (or propagator launch) carries it; kbe_step leaves none behind.
+  kbe::ObsStep obs_step;
+  bool obs_due = false;
+  void due_observables(int m) {
     LaunchArgs a = args();
     double t = m * cfg.dt;
-    set_A(a, t);
-    return check(kbe::launch_obs(L.d, a, m, t, pulse_A(pulse, t), st), "observables launch");
+    obs_step = {m, t, pulse_A(pulse, t), a.rho_cur, a.I_cur};
+    obs_due = true;
   }
-  int one_step() {
+  int flush_observables() {
+    if (!obs_due) return KBE_OK;
+    obs_due = false;
+    return check(kbe::launch_obs(L.d, args(), obs_step, st), "observables launch");
+  }
+  int observe(int m) {
+    due_observables(m);
+    return flush_observables();
+  }
+  int one_step(bool more) {   // more: another step of the same call follows
     int m = step + 1;
     if (m > cfg.nt_max) return fail(KBE_ERR_STATE, "step index would pass nt_max");
     LaunchArgs a = args();
@@ -405,7 +425,9 @@ struct kbe_ctx {
     if (!rc) passes[m] = taken;
     if (!rc) rc = collision_parts(a, m);
     if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_EVAL, st), "collision-row launch");
-    if (!rc) rc = observe(m);
+    if (!rc) due_observables(m);
+    // the kick replaces the slice's density and collision row; a step that reports ends the call
+    if (!rc && (!more || !reached || kicked(m))) rc = flush_observables();
     if (!rc) rc = dipole_kick(m);
     if (rc) return rc;
     cur ^= 1;
@@ -515,7 +537,7 @@ struct kbe_ctx {
     e.I_cur = b.Ire_prev;
     e.D_cur = b.Dscratch;
     if (!rc) rc = check(kbe::launch_sigma(d, e, m - 1, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, false, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, false, nullptr, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
     // recompute the predictor (row m of the working copy only)
     LaunchArgs p = a;
@@ -526,7 +548,7 @@ struct kbe_ctx {
     p.props = b.props_p;
     p.hfbuf = b.hf_p;
     p.commit = 0;
-    if (!rc) rc = check(kbe::launch_props(d, p, 0.0, st), "propagator launch");
+    if (!rc) rc = check(kbe::launch_props(d, p, 0.0, nullptr, st), "propagator launch");
     if (!rc) rc = check(kbe::launch_row(d, p, m, KBE_ROW_PREDICT, st), "predictor launch");
     // recompute the corrector's collision row and propagators
     LaunchArgs c = p;
@@ -535,7 +557,7 @@ struct kbe_ctx {
     c.props = b.props_c;
     c.hfbuf = b.hf_c;
     if (!rc) rc = check(kbe::launch_sigma(d, c, m, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_collide(d, c, m, true, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_collide(d, c, m, true, nullptr, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, c, m, KBE_ROW_EVAL, st), "collision-row launch");
     // corrector update, its propagators and mean field
     if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, b.lam, b.Rbar, rho0, st), "adjoint update launch");
@@ -714,11 +736,10 @@ int kbe_step(kbe_ctx* ctx, int32_t nsteps) {
   if (!ctx || nsteps < 0) return KBE_ERR_INVALID_ARG;
   if (ctx->frozen) return ctx->fail(KBE_ERR_STATE, "the context's buffers were used by a reverse sweep");
   if ((int64_t)ctx->step + nsteps > ctx->cfg.nt_max) return ctx->fail(KBE_ERR_STATE, "step index would pass nt_max");
-  for (int i = 0; i < nsteps; ++i) {
-    int rc = ctx->one_step();
-    if (rc) return rc;
-  }
-  return KBE_OK;
+  int rc = KBE_OK;
+  for (int i = 0; i < nsteps && !rc; ++i) rc = ctx->one_step(i + 1 < nsteps);
+  const int rc_obs = ctx->obs_due ? ctx->flush_observables() : KBE_OK;   // left only by a step that failed
+  return rc ? rc : rc_obs;
 }
 
 int32_t kbe_current_step(const kbe_ctx* ctx) { return ctx ? ctx->step : -1; }

@@ -148,6 +148,142 @@ __global__ __launch_bounds__(64) void k_init_rho(Dims d, const double* __restric
     }
 }
 
+// ------------------------------------------------------------------ observables
+// One block of at least 256 threads. Bound by latency (the Bloch Hamiltonian, its velocities and a
+// Jacobi diagonalisation per k, at most four k per thread); sums by wavefront, then over the four
+// wavefronts in LDS. Inside kbe_step the block of step m rides in the next step's first history pass
+// (nb <= 2) or propagator launch (nb = 3, 4, whose register need the history kernels should not have):
+// alone it held the stream up 8 us (16 points) to 18 us (576 points, nb = 2) per step.
+struct ObsArgs {
+  const cplx *hop, *rho, *Icur;
+  double* obs;
+  double t, A, Ax, Ay, U, spin;
+  int m, interaction, hf;
+};
+template <int N>
+__device__ __forceinline__ void block_sum_waves(const double* v, double* lds /* [N][4] */, double* out) {
+  const int t = threadIdx.x, w = t >> 6;
+  double rt[1][N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) rt[0][i] = v[i];
+  reduce_rows<1>(rt);
+  if ((t & 63) == 0 && w < 4)
+#pragma unroll
+    for (int i = 0; i < N; ++i) lds[4 * i + w] = rt[0][i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) out[i] = (lds[4 * i] + lds[4 * i + 1]) + (lds[4 * i + 2] + lds[4 * i + 3]);
+  __syncthreads();
+}
+template <int NB>
+constexpr int obs_lds() {
+  return 4 * (6 + 2 * NB);
+}
+template <int NB>
+__device__ __forceinline__ void obs_block(const Dims& d, const ObsArgs& o, double* lds) {
+  constexpr int NBB = NB * NB;
+  constexpr int NV = 6 + 2 * NB;  // N, Ekin, Ehf, Ecorr, Jx, Jy, n_orb[NB], n_band[NB]
+  const cplx* __restrict__ rho = o.rho;
+  const int tid = threadIdx.x;
+  const double inv = 1.0 / d.nk, U = o.U;
+  // mean field of the local density matrix
+  cplx hfm[NBB], ob[NBB];
+#pragma unroll
+  for (int e = 0; e < NBB; ++e) hfm[e] = ob[e] = czero();
+  if (o.interaction == KBE_DEV_INT_HUBBARD) {
+    double v[NB], loc[NB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a) v[a] = 0.0;
+    for (int k = tid; k < d.nk && tid < 256; k += 256)
+#pragma unroll
+      for (int a = 0; a < NB; ++a) v[a] += rho[(int64_t)k * NBB + a * (NB + 1)].x;
+    block_sum_waves<NB>(v, lds, loc);
+    if (o.hf)
+#pragma unroll
+      for (int a = 0; a < NB; ++a) hfm[a * (NB + 1)] = cmk(U * (loc[a] * inv), 0.0);
+  } else if constexpr (NB == 2) {
+    double v[8], loc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = 0.0;
+    for (int k = tid; k < d.nk && tid < 256; k += 256)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const cplx r = rho[(int64_t)k * 4 + e];
+        v[2 * e] += r.x;
+        v[2 * e + 1] += r.y;
+      }
+    block_sum_waves<8>(v, lds, loc);
+    ob[3] = cmk(-U, 0.0);
+    if (o.hf) {
+      hfm[0] = cmk(U * (loc[6] * inv), 0.0);
+      hfm[3] = cmk(U * (loc[0] * inv), 0.0);
+      hfm[1] = cscal(cmk(loc[2] * inv, loc[3] * inv), -U);
+      hfm[2] = cscal(cmk(loc[4] * inv, loc[5] * inv), -U);
+    }
+  }
+  double acc[NV], tot[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+  for (int k = tid; k < d.nk && tid < 256; k += 256) {
+    cplx r[NBB], h[NBB], v[NBB], Vv[NBB];
+    double w[NB];
+#pragma unroll
+    for (int e = 0; e < NBB; ++e) r[e] = rho[(int64_t)k * NBB + e];
+    bloch_h0<NB>(o.hop, d.nkx, d.nky, k, o.Ax, o.Ay, h);
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      acc[0] += r[a * NB + a].x;
+      acc[6 + a] += r[a * NB + a].x;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        acc[1] += cmul(cadd(h[a * NB + b], ob[a * NB + b]), r[b * NB + a]).x;
+        acc[2] += cmul(hfm[a * NB + b], r[b * NB + a]).x;
+      }
+      acc[3] += 0.5 * o.Icur[rowbuf_idx(d, k, a * NB + a, o.m)].y;  // Re(-i/2 I) = Im(I)/2
+    }
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+      bloch_vel<NB>(o.hop, d.nkx, d.nky, k, o.Ax, o.Ay, dir, v);
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[4 + dir] += cmul(v[a * NB + b], r[b * NB + a]).x;
+    }
+    jacobi_eigh<NB>(h, w, Vv);
+#pragma unroll
+    for (int bnd = 0; bnd < NB; ++bnd) {
+      double sacc = 0.0;
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          sacc += cmul(cmul(cconj(Vv[a * NB + bnd]), r[a * NB + b]), Vv[b * NB + bnd]).x;
+      acc[6 + NB + bnd] += sacc;
+    }
+  }
+  block_sum_waves<NV>(acc, lds, tot);
+  if (tid == 0) {
+    double* out = o.obs + (int64_t)o.m * KBE_DEV_NOBS;
+    for (int i = 0; i < KBE_DEV_NOBS; ++i) out[i] = 0.0;
+    out[0] = o.t;
+    out[1] = o.spin * tot[0] * inv;
+    out[2] = o.spin * tot[1] * inv;
+    out[3] = 0.5 * o.spin * tot[2] * inv;
+    out[4] = o.spin * tot[3] * inv;
+    out[5] = out[2] + out[3] + out[4];
+    out[6] = o.spin * tot[4] * inv;
+    out[7] = o.spin * tot[5] * inv;
+    out[8] = o.A;
+    for (int a = 0; a < NB; ++a) out[9 + a] = tot[6 + a] * inv;
+    for (int b = 0; b < NB; ++b) out[13 + b] = tot[6 + NB + b] * inv;
+  }
+}
+template <int NB>
+__global__ __launch_bounds__(256) void k_obs(Dims d, ObsArgs o) {
+  __shared__ double lds[obs_lds<NB>() > 32 ? obs_lds<NB>() : 32];
+  obs_block<NB>(d, o, lds);
+}
+
 // ------------------------------------------------------------------ propagators
 // Mean field and propagators of the midpoint Hamiltonian hbar = h0(k - A) + Sigma^HF[rho_loc],
 // rho = (1 - wb) rhoA + wb rhoB. Bound by latency (a chain of 13 dependent matrix-vector products on
@@ -356,9 +492,15 @@ __device__ __forceinline__ void props_block(const Dims& d, const PropsArgs& x, i
       }
   }
 }
+// the last block (nobs = 1): the observables of the step before (nb >= 3)
 template <int NB>
-__global__ __launch_bounds__(256) void k_props(Dims d, PropsArgs x) {
+__global__ __launch_bounds__(256) void k_props(Dims d, PropsArgs x, ObsArgs o, int nobs) {
   __shared__ double red[props_lds<NB>()];
+  if constexpr (NB >= 3)
+    if (nobs && blockIdx.x + 1 == gridDim.x) {
+      obs_block<NB>(d, o, red);
+      return;
+    }
   props_block<NB>(d, x, blockIdx.x, red);
 }
 
@@ -734,9 +876,10 @@ __device__ __forceinline__ void diag_block(const Dims& d, const cplx* __restrict
 }
 
 // Blocks that ride in front of a history pass's own, on work that is independent of it: the
-// equal-time integral of each k and, in a corrector pass, the propagators of the iterate. Both are a
-// few microseconds of latency and N_k (resp. N_k nb / 256) blocks; in launches of their own they held
-// up the stream 5 and 4 us per pass.
+// equal-time integral of each k, in a corrector pass the propagators of the iterate, and in a step's
+// first pass the observables of the step before. They are a few microseconds of latency and N_k,
+// N_k nb / 256 and one block; in launches of their own they held up the stream 5 and 4 us per pass
+// and 8-18 us per step.
 struct PassExtras {
   const cplx *row64, *sig;
   cplx *Icur, *Dcur;
@@ -744,7 +887,9 @@ struct PassExtras {
   QuadW Q;
   int m, nprops;      // nprops: propagator blocks (0: none)
   PropsArgs props;
-  __host__ __device__ int blocks(const Dims& d) const { return d.nk + nprops; }
+  int nobs;           // 1: the observables of the step before (nb <= 2)
+  ObsArgs obs;
+  __host__ __device__ int blocks(const Dims& d) const { return nobs + nprops + d.nk; }
 };
 template <int NB>
 constexpr int extras_lds() {
@@ -753,6 +898,13 @@ constexpr int extras_lds() {
 template <int NB>
 __device__ __forceinline__ void extras_block(const Dims& d, const PassExtras& x, int blk, void* lds) {
   double* w = reinterpret_cast<double*>(lds);
+  if constexpr (NB <= 2) {
+    if (blk < x.nobs) {
+      obs_block<NB>(d, x.obs, w);
+      return;
+    }
+    blk -= x.nobs;
+  }
   if (blk < x.nprops) props_block<NB>(d, x.props, blk, w);
   else diag_block<NB>(d, x.row64, x.sig, x.Icur, x.Dcur, x.m, x.dt, x.Q, blk - x.nprops, w);
 }
@@ -2442,120 +2594,6 @@ __global__ __launch_bounds__(256) void k_kick_row(Dims d, void* __restrict__ his
   }
 }
 
-// ------------------------------------------------------------------ observables
-template <int NB>
-__global__ __launch_bounds__(256) void k_obs(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ rho,
-                                             const cplx* __restrict__ Icur, int m, double t, double A,
-                                             double Ax, double Ay, int interaction, int hf, double U,
-                                             double spin, double* __restrict__ obs) {
-  constexpr int NBB = NB * NB;
-  constexpr int NV = 6 + 2 * NB;  // N, Ekin, Ehf, Ecorr, Jx, Jy, n_orb[NB], n_band[NB]
-  __shared__ double red[NV][256];
-  __shared__ cplx loc_s[NBB];
-  int tid = threadIdx.x;
-  // local density matrix for the mean field
-  {
-    __shared__ cplx lds[NBB * 256];
-    cplx loc[NBB];
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) loc[e] = czero();
-    for (int k = tid; k < d.nk; k += 256)
-#pragma unroll
-      for (int e = 0; e < NBB; ++e) loc[e] = cadd(loc[e], rho[(int64_t)k * NBB + e]);
-    block_sum_cplx<NBB>(loc, lds);
-    if (tid == 0)
-#pragma unroll
-      for (int e = 0; e < NBB; ++e) loc_s[e] = cscal(loc[e], 1.0 / d.nk);
-    __syncthreads();
-  }
-  cplx hfm[NBB], ob[NBB];
-#pragma unroll
-  for (int e = 0; e < NBB; ++e) {
-    hfm[e] = czero();
-    ob[e] = czero();
-  }
-  if (interaction == KBE_DEV_INT_HUBBARD) {
-    if (hf)
-#pragma unroll
-      for (int a = 0; a < NB; ++a) hfm[a * NB + a] = cmk(U * loc_s[a * NB + a].x, 0.0);
-  } else {
-    if constexpr (NB == 2) {
-      ob[3] = cmk(-U, 0.0);
-      if (hf) {
-        hfm[0] = cmk(U * loc_s[3].x, 0.0);
-        hfm[3] = cmk(U * loc_s[0].x, 0.0);
-        hfm[1] = cscal(loc_s[1], -U);
-        hfm[2] = cscal(loc_s[2], -U);
-      }
-    }
-  }
-  double acc[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-  for (int k = tid; k < d.nk; k += 256) {
-    cplx r[NBB], h[NBB], v[NBB], Vv[NBB];
-    double w[NB];
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) r[e] = rho[(int64_t)k * NBB + e];
-    bloch_h0<NB>(hop, d.nkx, d.nky, k, Ax, Ay, h);
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-      acc[0] += r[a * NB + a].x;
-      acc[6 + a] += r[a * NB + a].x;
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        acc[1] += cmul(cadd(h[a * NB + b], ob[a * NB + b]), r[b * NB + a]).x;
-        acc[2] += cmul(hfm[a * NB + b], r[b * NB + a]).x;
-      }
-      acc[3] += 0.5 * Icur[rowbuf_idx(d, k, a * NB + a, m)].y;  // Re(-i/2 I) = Im(I)/2
-    }
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-      bloch_vel<NB>(hop, d.nkx, d.nky, k, Ax, Ay, dir, v);
-#pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[4 + dir] += cmul(v[a * NB + b], r[b * NB + a]).x;
-    }
-    jacobi_eigh<NB>(h, w, Vv);
-#pragma unroll
-    for (int bnd = 0; bnd < NB; ++bnd) {
-      double sacc = 0.0;
-#pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          sacc += cmul(cmul(cconj(Vv[a * NB + bnd]), r[a * NB + b]), Vv[b * NB + bnd]).x;
-      acc[6 + NB + bnd] += sacc;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NV; ++i) red[i][tid] = acc[i];
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s)
-#pragma unroll
-      for (int i = 0; i < NV; ++i) red[i][tid] += red[i][tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    double inv = 1.0 / d.nk;
-    double* o = obs + (int64_t)m * KBE_DEV_NOBS;
-    for (int i = 0; i < KBE_DEV_NOBS; ++i) o[i] = 0.0;
-    o[0] = t;
-    o[1] = spin * red[0][0] * inv;
-    o[2] = spin * red[1][0] * inv;
-    o[3] = 0.5 * spin * red[2][0] * inv;
-    o[4] = spin * red[3][0] * inv;
-    o[5] = o[2] + o[3] + o[4];
-    o[6] = spin * red[4][0] * inv;
-    o[7] = spin * red[5][0] * inv;
-    o[8] = A;
-    for (int a = 0; a < NB; ++a) o[9 + a] = red[6 + a][0] * inv;
-    for (int b = 0; b < NB; ++b) o[13 + b] = red[6 + NB + b][0] * inv;
-  }
-}
-
 // ------------------------------------------------------------------ aux copies
 // Refresh the FP64 working copies from history rows 0..m: columns 0..qp-1, the diagonal band
 // of width qp, and the ring of the last rring rows (m - rring + 1 .. m).
@@ -2630,8 +2668,13 @@ struct Launch {
   static PropsArgs props_args(const LaunchArgs& a, double wb) {
     return {a.hop, a.rho_prev, a.rho_cur, a.hfbuf, a.props, wb, a.U, a.Ax, a.Ay, a.dt, a.interaction, a.hf};
   }
-  static hipError_t props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
-    hipLaunchKernelGGL(k_props<NB>, dim3(props_blocks(d)), dim3(256), 0, st, d, props_args(a, wb));
+  static ObsArgs obs_args(const LaunchArgs& a, const ObsStep& o) {
+    return {a.hop, o.rho, o.Icur, a.obs, o.t, o.A, o.A * a.polx, o.A * a.poly, a.U, a.spin, o.m, a.interaction, a.hf};
+  }
+  static hipError_t props(const Dims& d, const LaunchArgs& a, double wb, const ObsStep* o, hipStream_t st) {
+    const int nobs = o ? 1 : 0;
+    hipLaunchKernelGGL(k_props<NB>, dim3(props_blocks(d) + nobs), dim3(256), 0, st, d, props_args(a, wb),
+                       o ? obs_args(a, *o) : ObsArgs{}, nobs);
     return hipGetLastError();
   }
   static hipError_t sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
@@ -2666,9 +2709,10 @@ struct Launch {
     return hipGetLastError();
   }
   // the history sums and the equal-time integral of row m; with_props: the corrector's propagators too
-  static hipError_t collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st) {
+  static hipError_t collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
+                            hipStream_t st) {
     PassExtras x{a.row64, a.sig, a.I_cur, a.D_cur, a.dt, a.quad, m, with_props ? props_blocks(d) : 0,
-                 props_args(a, 0.5)};
+                 props_args(a, 0.5), o ? 1 : 0, o ? obs_args(a, *o) : ObsArgs{}};
     const int nx = x.blocks(d);
     if (m < 1) {
       hipLaunchKernelGGL(k_extras<NB>, dim3(nx), dim3(256), 0, st, d, x);
@@ -2719,9 +2763,8 @@ struct Launch {
                        (const cplx*)a.D_cur, m, hist_lgseg(d, m), a.dt, a.commit, a.chg, a.quad);
     return hipGetLastError();
   }
-  static hipError_t obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st) {
-    hipLaunchKernelGGL(k_obs<NB>, dim3(1), dim3(256), 0, st, d, a.hop, (const cplx*)a.rho_cur,
-                       (const cplx*)a.I_cur, m, t, A, a.Ax, a.Ay, a.interaction, a.hf, a.U, a.spin, a.obs);
+  static hipError_t obs(const Dims& d, const LaunchArgs& a, const ObsStep& o, hipStream_t st) {
+    hipLaunchKernelGGL(k_obs<NB>, dim3(1), dim3(256), 0, st, d, obs_args(a, o));
     return hipGetLastError();
   }
   static hipError_t aux(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
@@ -2749,8 +2792,8 @@ hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t st) {
   }
 
 hipError_t launch_init(const Dims& d, const LaunchArgs& a, hipStream_t st) { KBE_DISPATCH(d.nb, init(d, a, st)); }
-hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st) {
-  KBE_DISPATCH(d.nb, props(d, a, wb, st));
+hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, const ObsStep* o, hipStream_t st) {
+  KBE_DISPATCH(d.nb, props(d, a, wb, o, st));
 }
 hipError_t launch_sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
   KBE_DISPATCH(d.nb, sigma(d, a, m, st));
@@ -2770,8 +2813,9 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
                      a.corr);
   return hipGetLastError();
 }
-hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st) {
-  KBE_DISPATCH(d.nb, collide(d, a, m, with_props, st));
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
+                          hipStream_t st) {
+  KBE_DISPATCH(d.nb, collide(d, a, m, with_props, o, st));
 }
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st) {
   KBE_DISPATCH(d.nb, row(d, a, m, mode, st));
@@ -2780,8 +2824,8 @@ hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* ou
   hipLaunchKernelGGL(k_change_max, dim3(1), dim3(1024), 0, st, chg, d.nk * row_tiles(m, KBE_ROW_CORRECT), out);
   return hipGetLastError();
 }
-hipError_t launch_obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st) {
-  KBE_DISPATCH(d.nb, obs(d, a, m, t, A, st));
+hipError_t launch_obs(const Dims& d, const LaunchArgs& a, const ObsStep& o, hipStream_t st) {
+  KBE_DISPATCH(d.nb, obs(d, a, o, st));
 }
 hipError_t launch_aux(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
   KBE_DISPATCH(d.nb, aux(d, a, m, st));

@@ -50,10 +50,22 @@ struct LaunchArgs {
   int interaction, hf, corr;
 };
 
+// The observables of one time slice: its index, time, pulse amplitude, density matrices and
+// collision row.
+struct ObsStep {
+  int m;
+  double t, A;
+  const cplx *rho, *Icur;
+};
+// whether the observables of a step ride in the next step's first history pass (else in its
+// propagator launch)
+inline bool obs_in_pass(const Dims& d) { return d.nb <= 2; }
+
 hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t st);
 hipError_t launch_init(const Dims& d, const LaunchArgs& a, hipStream_t st);
-// mean field (into hfbuf) and propagators for the density (1 - wb) rho_prev + wb rho_cur
-hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, hipStream_t st);
+// mean field (into hfbuf) and propagators for the density (1 - wb) rho_prev + wb rho_cur; o (nb >= 3
+// only): also the observables of that slice
+hipError_t launch_props(const Dims& d, const LaunchArgs& a, double wb, const ObsStep* o, hipStream_t st);
 hipError_t launch_sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
 // the paper's direct-sum self-energy (interband preset, chain with even n <= 1024)
 hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
@@ -61,12 +73,14 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
 hipError_t launch_kick(const Dims& d, const LaunchArgs& a, int m, double kc, double ks, cplx* rho_other,
                        hipStream_t st);
 // history sums of row m and the equal-time integral I(t_m, t_m), D_m; with_props: also what
-// launch_props(d, a, 0.5, st) does (independent work in the same launch)
-hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, hipStream_t st);
+// launch_props(d, a, 0.5, nullptr, st) does; o (nb <= 2 only): also the observables of that slice
+// (independent work in the same launch)
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
+                          hipStream_t st);
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st);
 // out[0] = max of the row kernel's per-block changes at row m (one block, deterministic)
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st);
-hipError_t launch_obs(const Dims& d, const LaunchArgs& a, int m, double t, double A, hipStream_t st);
+hipError_t launch_obs(const Dims& d, const LaunchArgs& a, const ObsStep& o, hipStream_t st);
 hipError_t launch_aux(const Dims& d, const LaunchArgs& a, int m, hipStream_t st);
 
 }  // namespace kbe
