@@ -1006,10 +1006,10 @@ __device__ __forceinline__ void flush_chunk_fold(const cplx* st0, const cplx* st
 //   row term    -> output j:   -Sigma^>_{t'} (G^<_{j t'})^dag + Sigma^<_{t'} (G^>_{j t'})^dag,
 //                               t' < j, shared by I^< and I^>    (G_{t' j} = -G_{j t'}^dag)
 // nb <= 2, FP64. Block = (pair of 64-column strips 2 sp, 2 sp + 1; k), the pairs with the
-// most rows launched first. Lane l owns columns 128 sp + l and 128 sp + 64 + l and keeps both
-// column sums in registers; the Sigma of its two columns (row term) sits in LDS. Wavefront w
-// takes rows w, w + 4, ..., w + 60 of every 64-row chunk (so a chunk cut short by m leaves no
-// wavefront idle while the others finish), R rows per iteration (R = 1 at nb = 2: 2 x 8 loads
+// most rows launched first, and a segment of their rows. Lane l owns columns 128 sp + l and
+// 128 sp + 64 + l and keeps both column sums in registers; the Sigma of its two columns (row term)
+// sits in LDS. Of the WAVES wavefronts w takes rows w, w + WAVES, ... of every 64-row chunk (so a
+// chunk cut short by m leaves no wavefront idle while the others finish), R rows per iteration (R = 1 at nb = 2: 2 x 8 loads
 // of 1 KB-contiguous data in flight; R = 4 at nb = 1), so every stored block is read from HBM
 // once. The row terms of the two strips are added before the 64-lane
 // reduce-scatter (at nb = 2 the four components of the row term share one reduce-scatter as
@@ -1017,23 +1017,33 @@ __device__ __forceinline__ void flush_chunk_fold(const cplx* st0, const cplx* st
 // read stream are half of what one strip per block would produce, and they leave in long runs
 // (the block's rows of four 64-row chunks staged in LDS, then stored by all its threads as
 // contiguous 4 KB runs per component, streaming stores). Both measures keep the read stream
-// from stalling on scattered write-backs. Row partials go to slot sp; the 4
-// wavefronts' column sums are combined in LDS. Deterministic: no atomics.
-template <int NB>
-__global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restrict__ hist,
+// from stalling on scattered write-backs. Row partials go to slot sp; the wavefronts' column
+// sums are combined in LDS, a share of the components by each. Deterministic: no atomics.
+template <int NB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_hist_pair(Dims d, const cplx* __restrict__ hist,
                                                    const cplx* __restrict__ sig, cplx* __restrict__ colpart,
                                                    cplx* __restrict__ rowpart, int m, int lgL, PassExtras x) {
   constexpr int NBB = NB * NB, C = 2 * NBB;
   constexpr int R = NB == 1 ? 4 : 1;
-  __shared__ cplx red[3][C][64];
   // row partials of the last ROWS_ST rows (4 chunks of 64), stored by the whole block at once
   constexpr int ROWS_ST = 256;
-  __shared__ cplx stg[NBB][ROWS_ST];
-  __shared__ cplx sS[2][2][NBB][64];  // [strip of the pair][Sigma^<, Sigma^>][e][lane]
-  static_assert(sizeof(red) >= 8 * extras_lds<NB>(), "the extra blocks' LDS");
+  constexpr int RSTEP = WAVES;              // a wavefront's rows are RSTEP apart
+  constexpr int RPC = 64 / WAVES;           // its rows per 64-row chunk
+  struct Rows {
+    cplx stg[NBB][ROWS_ST];
+    cplx sS[2][2][NBB][64];  // [strip of the pair][Sigma^<, Sigma^>][e][lane]
+  };
+  union Shared {
+    Rows r;
+    cplx red[WAVES][C][64];  // column sums of one strip, after the row loop
+  };
+  __shared__ __align__(16) unsigned char shraw[sizeof(Shared) > 8 * extras_lds<NB>() ? sizeof(Shared) : 8 * extras_lds<NB>()];
+  auto& stg = reinterpret_cast<Shared*>(shraw)->r.stg;
+  auto& sS = reinterpret_cast<Shared*>(shraw)->r.sS;
+  auto& red = reinterpret_cast<Shared*>(shraw)->red;
   const int nx = x.blocks(d);
   if ((int)blockIdx.x < nx) {
-    extras_block<NB>(d, x, blockIdx.x, red);
+    extras_block<NB>(d, x, blockIdx.x, shraw);
     return;
   }
   const int task = (blockIdx.x - nx) / d.nk;
@@ -1043,7 +1053,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // rows and Sigma^R wavefront-uniform
   const cplx* sk = sig + (int64_t)k * 3 * NBB * d.Tp;
-  for (int q = threadIdx.x; q < 4 * NBB * 64; q += 256) {
+  for (int q = threadIdx.x; q < 4 * NBB * 64; q += 64 * WAVES) {
     int l = q & 63, e = (q >> 6) % NBB, x = (q >> 6) / NBB;
     int t = 64 * (2 * sp + (x >> 1)) + l;
     sS[x >> 1][x & 1][e][l] = t < m ? sk[((x & 1) * NBB + e) * d.Tp + t] : czero();
@@ -1070,8 +1080,8 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
     const int rb = cb + wv;   // the wavefront's rows of the chunk: rb, rb + 4, ..., rb + 60
     const int cslot = ((cb - r0) >> 6) % (ROWS_ST / 64);   // chunk's place in the staging
     cplx* st = &stg[0][64 * cslot];                                // st[e * ROWS_ST + (row - cb)]
-    for (int i = 0; i < 16;) {
-      const int jb = rb + 4 * i;
+    for (int i = 0; i < RPC;) {
+      const int jb = rb + RSTEP * i;
       if (jb >= r1) break;
       // rows past the pair's first 128 (and below the segment's end) need no masks (as in k_hist_pair32)
       auto iteration = [&](auto tag, auto nh, auto nr) {
@@ -1084,7 +1094,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
         for (int r = 0; r < RR; ++r)
 #pragma unroll
           for (int h = 0; h < NH; ++h) {
-            int j = jb + 4 * r;
+            int j = jb + RSTEP * r;
             bool v = (MM == 2 || (MM == 1 && h == 1)) ? (colv[h] && tp[h] <= j && j < r1) : true;
             const cplx* row = hk[h] + 64 * (int64_t)C * j;
 #pragma unroll
@@ -1093,7 +1103,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
         double rt[RR][2 * NBB];
 #pragma unroll
         for (int r = 0; r < RR; ++r) {
-          int j = jb + 4 * r;
+          int j = jb + RSTEP * r;
           int jc = MASKED ? (j < r1 ? j : r1 - 1) : j;
           cplx SR[NBB];
 #pragma unroll
@@ -1139,7 +1149,7 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
           int rr = reduced_row<RR>(lane);
           if (rr >= 0) {
 #pragma unroll
-            for (int e = 0; e < NBB; ++e) st[e * ROWS_ST + (jb - cb) + 4 * rr] = cmk(rt[0][2 * e], rt[0][2 * e + 1]);
+            for (int e = 0; e < NBB; ++e) st[e * ROWS_ST + (jb - cb) + RSTEP * rr] = cmk(rt[0][2 * e], rt[0][2 * e + 1]);
           }
         }
       };
@@ -1147,18 +1157,18 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
       // work; in its next 64 rows every column of the first strip lies below the row: masks for
       // the second strip only
       // (an iteration's rows jb, jb + 4, ..., jb + 4 (RR - 1) lie in one 64-row chunk)
-      if (jb >= 128 * sp + 128 && jb + 4 * (R - 1) < r1) {
+      if (jb >= 128 * sp + 128 && jb + RSTEP * (R - 1) < r1) {
         iteration(IntTag<0>{}, IntTag<2>{}, IntTag<R>{});
         i += R;
-      } else if (R == 1 && jb + 4 < 128 * sp + 64 && jb + 4 < r1) {
+      } else if (R == 1 && jb + RSTEP < 128 * sp + 64 && jb + RSTEP < r1) {
         // two rows at a time where only the first strip has work: its loads of both rows in
         // flight together (one row would keep half the loads of a full iteration in flight)
         iteration(IntTag<2>{}, IntTag<1>{}, IntTag<2>{});
         i += 2;
-      } else if (jb + 4 * (R - 1) < 128 * sp + 64) {
+      } else if (jb + RSTEP * (R - 1) < 128 * sp + 64) {
         iteration(IntTag<2>{}, IntTag<1>{}, IntTag<R>{});
         i += R;
-      } else if (jb >= 128 * sp + 64 && jb + 4 * (R - 1) < r1 && jb + 4 * (R - 1) < 128 * sp + 128) {
+      } else if (jb >= 128 * sp + 64 && jb + RSTEP * (R - 1) < r1 && jb + RSTEP * (R - 1) < 128 * sp + 128) {
         iteration(IntTag<1>{}, IntTag<2>{}, IntTag<R>{});
         i += R;
       } else {
@@ -1172,32 +1182,28 @@ __global__ __launch_bounds__(256) void k_hist_pair(Dims d, const cplx* __restric
       __syncthreads();
       const int base = cb - 64 * cslot;
       const int nrows = (cb + 64 < r1 ? cb + 64 : r1) - base;
-      for (int q = threadIdx.x; q < NBB * nrows; q += 256) {
+      for (int q = threadIdx.x; q < NBB * nrows; q += 64 * WAVES) {
         const int e = q / nrows, row = q - e * nrows;
         store_stream(rp + (int64_t)e * d.Tp + base + row, stg[e][row]);
       }
       __syncthreads();
     }
   }
-  // combine the 4 wavefronts' column sums, strip by strip
+  // combine the wavefronts' column sums, strip by strip: every wavefront adds up its share of the
+  // components, in the order of the wavefronts
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if (wv > 0) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) red[wv - 1][c][lane] = acc[h][c];
-    }
+    for (int c = 0; c < C; ++c) red[wv][c][lane] = acc[h][c];
     __syncthreads();
-    if (wv == 0 && colv[h]) {
+    if (colv[h])
+      for (int c = wv; c < C; c += WAVES) {
+        cplx a = red[0][c][lane];
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        cplx a = acc[h][c];
-        a = cadd(a, red[0][c][lane]);
-        a = cadd(a, red[1][c][lane]);
-        a = cadd(a, red[2][c][lane]);
+        for (int w = 1; w < WAVES; ++w) a = cadd(a, red[w][c][lane]);
         colpart[colpart_idx(d, k, ht.g, c, tp[h])] = a;
       }
-    }
-    __syncthreads();
+    if (h == 0) __syncthreads();
   }
 }
 
@@ -2623,25 +2629,36 @@ static hipError_t allow_lds(const void* kern, size_t bytes) {
 // Blocks of 64 t' per k of the row kernel: t' < m in the evaluation mode, t' <= m otherwise.
 static int row_tiles(int m, int mode) { return mode == KBE_ROW_EVAL ? (m + 63) / 64 : m / 64 + 1; }
 
+// Wavefronts per block of the FP64 nb <= 2 kernel: at nb = 2 eight where one block per strip pair gives
+// less than two rounds of the 512 four-wavefront blocks that the chip holds (its registers allow two
+// wavefronts per SIMD, so it holds 256 of eight): the same rows in flight with half the blocks to start
+// and to combine. 144 points, m = 300 / 400, best split of either 156 -> 154, 272 -> 265 us; 61 points,
+// m = 400 130 -> 120 us; but 576 points, m = 300 592 -> 608 us, and one band (126 registers, four
+// wavefronts per SIMD), 61 points, m = 200 12.1 -> 13.2 us.
+static int hist_waves(const Dims& d, int m) {
+  return d.nb == 2 && !d.fp32 && d.nk * ((m + 127) / 128) < 1024 ? 8 : 4;
+}
 // Rows per block of a history pass at row m, as a power of two (30: every strip is one block).
-// One block per strip leaves a small N_k with fewer blocks than the 512 that the chip holds at a
-// time (two per CU), and a medium one with a last round of a few long blocks; shorter blocks cost
-// each a prologue and a column combine (5-10 rows' worth of time) and their column sums are read
+// One block per strip leaves a small N_k with fewer blocks than the chip holds at a time (512: two per
+// CU; 256 of eight wavefronts), and a medium one with a last round of a few long blocks; shorter blocks
+// cost each a prologue and a column combine (5-10 rows' worth of time) and their column sums are read
 // once more by the row kernel. Measured best over N_k = 16..1024, m = 20..500, nb = 1..4: blocks of about
 // 1.5 times the rows that an even share of the launch would be (a strip's triangular first 64 rows
-// count half), at least 16 (32 in the FP64 nb = 4 kernel and 64 in the MFMA form, whose blocks work
-// in chunks of that many). FP64, nb = 2, one block per strip -> split: 16 points, m = 200 84 -> 17 us;
-// 61 points, m = 200 93 -> 40 us; 144 points, m = 128 / 200 / 400 66 -> 47, 102 -> 80, 287 -> 272 us;
-// 1024 points 2.76 ms unsplit against 2.83 ms in blocks of 256 rows at m = 500.
+// count half; 2.2 times with eight wavefronts), at least 16 (32 in the FP64 nb = 4 kernel and 64 in the
+// MFMA form, whose blocks work in chunks of that many). FP64, nb = 2, one four-wavefront block per strip ->
+// this rule: 16 points, m = 128 / 200 48 -> 13, 84 -> 19 us; 61 points, m = 200 / 400 93 -> 38, 230 -> 120 us;
+// 144 points, m = 128 / 200 / 400 66 -> 48, 102 -> 79, 287 -> 265 us; 1024 points 2.76 ms unsplit against
+// 2.83 ms in blocks of 256 rows at m = 500.
 static int hist_lgseg(const Dims& d, int m) {
   if (d.cseg == 1) return 30;
   const int W = 64 * d.spb;
   int64_t rows = 0;
   for (int r = m; r > 0; r -= W) rows += r - (r < 64 ? r / 2 : 32);
-  const int slots = (d.nb == 3 && !d.mfma) ? 256 : 512;   // nb = 3: one block per CU
-  const double share = 1.5 * d.nk * (double)rows / slots;
+  const bool eight = hist_waves(d, m) == 8;
+  const int slots = (d.nb == 3 && !d.mfma) || eight ? 256 : 512;   // nb = 3: one block per CU
+  const double share = (eight ? 2.2 : 1.5) * d.nk * (double)rows / slots;
   int lg = d.mfma ? 6 : (d.nb == 4 && !d.fp32 ? 5 : 4);
-  while ((2 << lg) <= share && (2 << lg) < m) ++lg;
+  while ((2 << lg) <= share && (1 << lg) < m) ++lg;
   while (hist_nseg(m, lg) > d.cseg) ++lg;
   return (1 << lg) < m ? lg : 30;
 }
@@ -2730,8 +2747,14 @@ struct Launch {
         hipLaunchKernelGGL(k_hist_pair32<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
                            (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
       else
-        hipLaunchKernelGGL(k_hist_pair<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx*)a.hist,
+      {
+        auto kern = k_hist_pair<NB, 4>;
+        const int waves = NB == 2 ? hist_waves(d, m) : 4;
+        if constexpr (NB == 2)
+          if (waves == 8) kern = k_hist_pair<NB, 8>;
+        hipLaunchKernelGGL(kern, dim3(nx + ns * d.nk), dim3(64 * waves), 0, st, d, (const cplx*)a.hist,
                            (const cplx*)a.sig, a.colpart, a.rowpart, m, lgL, x);
+      }
     } else if constexpr (NB == 4) {
       if (d.fp32)
         hipLaunchKernelGGL(k_hist_bulk32_split<NB>, dim3(nx + ns * d.nk), dim3(256), 0, st, d, (const cplx32*)a.hist,
