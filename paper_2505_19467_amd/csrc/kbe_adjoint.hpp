@@ -9,6 +9,8 @@ namespace kbe {
 // for a real loss L.
 struct AdjArgs {
   cplx* lam;          // adjoint history: same strip-major layout as the FP64 history
+  cplx* lam_diag;     // nb = 2: end-point terms' part of lam on the diagonal, [k][C][Tp] (else unused)
+  cplx* lam_col0;     // and in the first column
   cplx* Ibar;         // adjoint of the collision row being reversed (eval pass of t_m)
   cplx* Ibar_prev;    // adjoint of I(t_{m-1}, .) being accumulated
   cplx* Ibar_c;       // adjoint of the corrector pass's collision row
@@ -16,6 +18,7 @@ struct AdjArgs {
   cplx* sbar;         // [k][2][nb^2][Tp] adjoint of the Sigma row (lesser, greater)
   cplx* sbar_col;     // [k][C][Tp] per-column Sigma adjoint from the history sums
   cplx* sbar_rowpart; // [k][Smax][nb^2][Tp] per-strip partial adjoint of Sigma^R
+  cplx* rowtot;       // [k][4 nb^2] sums over t' of the j = 0 and j = m Sigma adjoints (end-point terms)
   cplx* Dbar;         // adjoint of D of the pass being reversed
   cplx* Dbar_prev;    // adjoint of D_{m-1}
   cplx* Dbar_c;       // adjoint of the corrector pass's D
@@ -52,7 +55,8 @@ hipError_t launch_adj_row(const Dims& d, const LaunchArgs& a, const AdjArgs& b, 
                           const cplx* Dbar, int m, hipStream_t st);
 hipError_t launch_adj_sigma(const Dims& d, const LaunchArgs& a, const AdjArgs& b, int m, int* nblocks,
                             hipStream_t st);
-hipError_t launch_adj_update(const Dims& d, const LaunchArgs& a, const AdjArgs& b, int m, int corrector,
+// nubar: number of dL/dU partials that launch_adj_sigma left in ubar_part (0: none), added to theta_bar
+hipError_t launch_adj_update(const Dims& d, const LaunchArgs& a, const AdjArgs& b, int m, int corrector, int nubar,
                              const cplx* Gbar_hist, const cplx* Gbar_row, const cplx* rho_prev,
                              hipStream_t st);
 hipError_t launch_adj_props(const Dims& d, const LaunchArgs& a, const AdjArgs& b, const cplx* hf,
@@ -60,7 +64,9 @@ hipError_t launch_adj_props(const Dims& d, const LaunchArgs& a, const AdjArgs& b
 hipError_t launch_adj_hf(const Dims& d, const LaunchArgs& a, const AdjArgs& b, const cplx* rho_prev,
                          const cplx* rho_cur, double wb, cplx* rbar_prev, cplx* rbar_cur, double dAdamp,
                          double dAdomega, hipStream_t st);
-hipError_t launch_adj_reduce_u(const AdjArgs& b, int n, hipStream_t st);
+// start of reverse step m: working copies of rows m, m - 1 and rho0 = rho_{m-1} from the history; clears
+// Ibar_prev, Dbar_prev, rhobar_prev and rhobar_P
+hipError_t launch_adj_begin(const Dims& d, const LaunchArgs& a, const AdjArgs& b, int m, hipStream_t st);
 // rho[k][nb^2] = rho_m of the committed FP64 history (its diagonal block G^< = i rho_m)
 hipError_t launch_adj_rho(const Dims& d, const void* hist, int m, cplx* rho, hipStream_t st);
 hipError_t launch_adj_seed(const Dims& d, const LaunchArgs& a, const AdjArgs& b, const cplx* rho_T, int obs_id,

@@ -198,7 +198,7 @@ void pulse_dA(const kbe_pulse& p, double t, double* damp, double* domega) {
 enum {
   A_LAM = 0, A_IBAR0, A_IBAR1, A_IBARC, A_RBAR, A_SBAR, A_SBARCOL, A_IREPREV, A_IREC, A_SBARRP,
   A_DBAR0, A_DBAR1, A_DBARC, A_RHOBAR0, A_RHOBAR1, A_RHOBARP, A_RHOP, A_DC, A_DSCR, A_RHO0,
-  A_PROPSP, A_PROPSC, A_PBAR, A_HFP, A_HFC, A_KPART, A_UBAR, A_THETA, A_SIGEV, A_COUNT
+  A_PROPSP, A_PROPSC, A_PBAR, A_HFP, A_HFC, A_KPART, A_UBAR, A_THETA, A_SIGEV, A_ROWTOT, A_LAMD, A_LAMC, A_COUNT
 };
 
 size_t adj_layout(const Layout& L, size_t* off) {
@@ -217,6 +217,8 @@ size_t adj_layout(const Layout& L, size_t* off) {
   sz[A_UBAR] = ((size_t)((d.N * d.nbb + 7) / 8) * 8) * sizeof(double);
   sz[A_THETA] = 3 * sizeof(double);
   sz[A_SIGEV] = nk * 3 * d.nbb * d.Tp * cz;   // Sigma row of the evaluation pass, kept for the fused pass
+  sz[A_ROWTOT] = 4 * mat;   // end-point sums of a pass
+  sz[A_LAMD] = sz[A_LAMC] = d.nb == 2 ? row : 0;   // end-point terms of the adjoint history, compact
   size_t o = 0;
   for (int i = 0; i < A_COUNT; ++i) {
     if (off) off[i] = o;
@@ -455,6 +457,9 @@ struct kbe_ctx {
     b.sbar = abuf<cplx>(A_SBAR);
     b.sbar_col = abuf<cplx>(A_SBARCOL);
     b.sbar_rowpart = abuf<cplx>(A_SBARRP);
+    b.rowtot = abuf<cplx>(A_ROWTOT);
+    b.lam_diag = abuf<cplx>(A_LAMD);
+    b.lam_col0 = abuf<cplx>(A_LAMC);
     b.Dbar = abuf<cplx>(c == 0 ? A_DBAR0 : A_DBAR1);
     b.Dbar_prev = abuf<cplx>(c == 0 ? A_DBAR1 : A_DBAR0);
     b.Dbar_c = abuf<cplx>(A_DBARC);
@@ -485,6 +490,8 @@ struct kbe_ctx {
     size_t row = (size_t)d.nk * d.C * d.Tp * sizeof(cplx), mat = (size_t)d.nk * d.nbb * sizeof(cplx);
     int rc = zero_adj(A_LAM, (size_t)d.nk * d.C * (size_t)d.P * sizeof(cplx));
     for (int i = A_IBAR0; i <= A_IBAR1 && !rc; ++i) rc = zero_adj(i, row);
+    if (d.nb == 2)
+      for (int i = A_LAMD; i <= A_LAMC && !rc; ++i) rc = zero_adj(i, row);
     // A_RHOP too: the recomputed predictor's mean field reads it with weight 0 before it is written
     for (int i = A_DBAR0; i <= A_RHOP && !rc; ++i) rc = zero_adj(i, mat);
     if (!rc) rc = zero_adj(A_THETA, 3 * sizeof(double));
@@ -496,16 +503,16 @@ struct kbe_ctx {
     kbe::AdjArgs b = adj_args();
     rc = check(kbe::launch_adj_rho(d, hist, step, b.rho0, st), "density read-back launch");
     if (!rc) rc = check(kbe::launch_adj_seed(d, a, b, b.rho0, obs_id, damp, dom, st), "adjoint seed launch");
+    // column and diagonal copies of the committed history, for the whole sweep
+    if (!rc) rc = check(kbe::launch_aux(d, a, step, st), "aux launch");
     return rc;
   }
   int adj_sigma_pass(const LaunchArgs& a, const kbe::AdjArgs& b, const cplx* Ibar, const cplx* Dbar, int m,
-                     int mode, const cplx* sig1 = nullptr, const cplx* Ibar1 = nullptr) {
+                     int mode, int* nubar, const cplx* sig1 = nullptr, const cplx* Ibar1 = nullptr) {
     const Dims& d = L.d;
-    int nblk = 0;
     int rc = check(kbe::launch_adj_bulk(d, a, b, Ibar, m, mode, sig1, Ibar1, st), "adjoint history-sum launch");
     if (!rc) rc = check(kbe::launch_adj_row(d, a, b, Ibar, Dbar, m, st), "adjoint end-point launch");
-    if (!rc) rc = check(kbe::launch_adj_sigma(d, a, b, m, &nblk, st), "adjoint self-energy launch");
-    if (!rc) rc = check(kbe::launch_adj_reduce_u(b, nblk, st), "adjoint reduction launch");
+    if (!rc) rc = check(kbe::launch_adj_sigma(d, a, b, m, nubar, st), "adjoint self-energy launch");
     return rc;
   }
   // Reverse step m (t_m -> t_{m-1}) of the K = 1 scheme: evaluation pass, corrector
@@ -521,9 +528,8 @@ struct kbe_ctx {
     // The committed history is every time slice's checkpoint: rho_{m-1} is its diagonal block,
     // and D_{m-1} comes out of the recomputed evaluation pass of t_{m-1} below.
     cplx* rho0 = b.rho0;
-    int rc = check(kbe::launch_adj_rho(d, hist, m - 1, rho0, st), "density read-back launch");
-    // committed rows m-1, m, column 0 and diagonal
-    if (!rc) rc = check(kbe::launch_aux(d, a, m, st), "aux launch");
+    int nubar = 0;   // dL/dU partials of the latest collision pass
+    int rc = check(kbe::launch_adj_begin(d, a, b, m, st), "reverse-step start launch");
     // Sigma of the committed row m, in a buffer of its own: the corrector pass below applies this
     // pass's adjoint-history update too (both updates are linear in their Sigma row and Ibar and
     // touch the same stored blocks), so the history and the adjoint history stream once for both
@@ -531,7 +537,7 @@ struct kbe_ctx {
     ev.sig = abuf<cplx>(A_SIGEV);
     if (!rc) rc = check(kbe::launch_sigma(d, ev, m, st), "self-energy launch");
     // evaluation pass of t_m: Sigma adjoints only
-    if (!rc) rc = adj_sigma_pass(ev, b, b.Ibar, b.Dbar, m, kbe::ADJ_SUMS);
+    if (!rc) rc = adj_sigma_pass(ev, b, b.Ibar, b.Dbar, m, kbe::ADJ_SUMS, &nubar);
     // recompute I(t_{m-1}, .)
     LaunchArgs e = a;
     e.I_cur = b.Ire_prev;
@@ -560,27 +566,23 @@ struct kbe_ctx {
     if (!rc) rc = check(kbe::launch_collide(d, c, m, true, nullptr, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, c, m, KBE_ROW_EVAL, st), "collision-row launch");
     // corrector update, its propagators and mean field
-    if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, b.lam, b.Rbar, rho0, st), "adjoint update launch");
+    if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, nubar, b.lam, b.Rbar, rho0, st), "adjoint update launch");
     if (!rc) rc = check(kbe::launch_adj_props(d, a, b, b.hf_c, st), "adjoint propagator launch");
     if (!rc)
       rc = check(kbe::launch_adj_hf(d, a, b, rho0, b.rhoP, 0.5, b.rhobar_prev, b.rhobar_P, damp, dom, st),
                  "adjoint mean-field launch");
     // corrector collision pass (Sigma of the predictor row, still in place)
-    if (!rc) rc = adj_sigma_pass(a, b, b.Ibar_c, b.Dbar_c, m, kbe::ADJ_FUSED, ev.sig, b.Ibar);
+    if (!rc) rc = adj_sigma_pass(a, b, b.Ibar_c, b.Dbar_c, m, kbe::ADJ_FUSED, &nubar, ev.sig, b.Ibar);
     // predictor update, its propagators and mean field
-    if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 0, nullptr, b.Rbar, rho0, st), "adjoint update launch");
+    if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 0, nubar, nullptr, b.Rbar, rho0, st), "adjoint update launch");
     if (!rc) rc = check(kbe::launch_adj_props(d, a, b, b.hf_p, st), "adjoint propagator launch");
     if (!rc)
       rc = check(kbe::launch_adj_hf(d, a, b, rho0, rho0, 0.0, b.rhobar_prev, nullptr, damp, dom, st),
                  "adjoint mean-field launch");
     if (rc) return rc;
-    // the accumulated adjoints of step m-1 become the inputs of the next reverse step
+    // the accumulated adjoints of step m-1 become the inputs of the next reverse step, which clears
+    // the ones it accumulates into
     adj_cur ^= 1;
-    size_t row = (size_t)d.nk * d.C * d.Tp * sizeof(cplx), mat = (size_t)d.nk * d.nbb * sizeof(cplx);
-    rc = zero_adj(adj_cur == 0 ? A_IBAR1 : A_IBAR0, row);
-    if (!rc) rc = zero_adj(adj_cur == 0 ? A_DBAR1 : A_DBAR0, mat);
-    if (!rc) rc = zero_adj(adj_cur == 0 ? A_RHOBAR1 : A_RHOBAR0, mat);
-    if (!rc) rc = zero_adj(A_RHOBARP, mat);
     return rc;
   }
 };
