@@ -257,6 +257,12 @@ struct kbe_ctx {
   // corrector log (host): passes taken per step, and the row change after each pass
   std::vector<int32_t> passes;
   std::vector<double> changes;
+  // corr_tol > 0: the row change of the latest pass, in pinned host memory that the GPU writes
+  double* change_host = nullptr;
+  double* change_dev = nullptr;
+  ~kbe_ctx() {
+    if (change_host) (void)hipHostFree(change_host);
+  }
   int noalloc_dev = -1;  // device whose static workspace this context holds (kbe_create_noalloc)
 
   template <class T>
@@ -405,13 +411,10 @@ struct kbe_ctx {
       ++taken;
       if (tol) {
         double ch = 0.0;
-        rc = check(kbe::launch_change_max(L.d, buf<double>(B_CHG), m, buf<double>(B_CHGMAX), st),
-                   "corrector change launch");
-        if (!rc)
-          rc = check(hipMemcpyAsync(&ch, buf<double>(B_CHGMAX), sizeof(double), hipMemcpyDeviceToHost, st),
-                     "corrector change copy");
+        rc = check(kbe::launch_change_max(L.d, buf<double>(B_CHG), m, change_dev, st), "corrector change launch");
         if (!rc) rc = check(hipStreamSynchronize(st), "stream synchronisation");
         if (rc) break;
+        ch = *change_host;
         if (!std::isfinite(ch)) {
           rc = fail(KBE_ERR_NONFINITE, "non-finite corrector change");
           break;
@@ -634,6 +637,14 @@ int create_context(const kbe_config* cfg, const double* hop, const kbe_pulse* pu
   c->quad = quad_corrections(c->L.d.qp);
   c->passes.assign((size_t)cfg->nt_max + 1, 0);
   c->changes.assign((size_t)(cfg->nt_max + 1) * (cfg->n_corr > 0 ? cfg->n_corr : 1), -1.0);
+  if (cfg->corr_tol > 0.0) {
+    rc = c->check(hipHostMalloc((void**)&c->change_host, sizeof(double), hipHostMallocMapped), "pinned host memory");
+    if (!rc) rc = c->check(hipHostGetDevicePointer((void**)&c->change_dev, c->change_host, 0), "pinned host memory");
+    if (rc) {
+      delete c;
+      return rc;
+    }
+  }
   const Dims& d = c->L.d;
   c->hop_host.resize(3 * d.nbb);
   for (int i = 0; i < 3 * d.nbb; ++i) c->hop_host[i] = make_double2(hop[2 * i], hop[2 * i + 1]);

@@ -2566,7 +2566,8 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
   }
 }
 
-// Largest change of the corrector's row: out[0] = max over the row kernel's n blocks.
+// Largest change of the corrector's row: out[0] = max over the row kernel's n blocks; out is in host
+// memory, which saves the copy that the host would wait for.
 // One block, a fixed reduction order (max is exact, so any order gives the same value).
 __global__ __launch_bounds__(1024) void k_change_max(const double* __restrict__ chg, int n, double* __restrict__ out) {
   __shared__ double red[16];
