@@ -2383,22 +2383,108 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
         }
       }
     }
-    __syncthreads();
-    if (in) {
-      // end-point terms of row a of component sc, accumulated term by term
-      cplx E[NB];
+    // end-point terms of row a of component sc, accumulated term by term
+    cplx E[NB];
 #pragma unroll
-      for (int b = 0; b < NB; ++b) E[b] = czero();
-      // E += f S G: S[a][l] of Sigma component cs at t_j, G[l][b] from g(l, b)
-      auto term = [&](int cs, int j, double f, auto g) {
-        cplx S[NB];
+    for (int b = 0; b < NB; ++b) E[b] = czero();
+    // E += f S G: S[a][l] of Sigma component cs at t_j, G[l][b] from g(l, b)
+    auto sigma_row = [&](int cs, int j, cplx* S) {
 #pragma unroll
-        for (int l = 0; l < NB; ++l) S[l] = cscal(sig[sig_idx(d, k, cs, a * NB + l, j)], f);
+      for (int l = 0; l < NB; ++l) S[l] = sig[sig_idx(d, k, cs, a * NB + l, j)];
+    };
+    auto add = [&](cplx* S, double f, auto g) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+      for (int l = 0; l < NB; ++l) S[l] = cscal(S[l], f);
 #pragma unroll
-          for (int l = 0; l < NB; ++l) cmac(E[b], S[l], g(l, b));
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int l = 0; l < NB; ++l) cmac(E[b], S[l], g(l, b));
+    };
+    auto term = [&](int cs, int j, double f, auto g) {
+      cplx S[NB];
+      sigma_row(cs, j, S);
+      add(S, f, g);
+    };
+    if constexpr (GREG) {
+      // Gregory end corrections (d.qp nodes per end): against the bulk's unit weights,
+      //   E = sum_j (w^(m)_j - [j < m]) SR_mj G_jt'  +  sum_{j <= t'} (w^(t')_j - [j < t']) Sigma_mj GA_jt',
+      // nonzero on the nodes j < q' and j > N - q' of each interval (q' = min(qp, N + 1)). Per step
+      // every wavefront loads its row of one block into LDS for all of them (each block is wanted by NB
+      // or 2 NB wavefronts), the next step's rows of G and Sigma meanwhile in flight and the corrections in
+      // LDS: 30.4 -> 27.3 us per corrector launch at nb = 3, 63 points, m <= 150, q = 4, against whole blocks
+      // loaded by each wavefront.
+      auto put = [&](const cplx* v) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) s0[(sc * NBB + a * NB + b) * 64 + lane] = v[b];
       };
+      cplx v[NB], S0[NB], S1[NB];
+      // weight of node j on [0, N], N >= 1, less the bulk's unit weight on j < N (quad_w, corrections in LDS)
+      __shared__ double qc[KBE_QMAX + 1][KBE_QMAX];
+      for (int i = threadIdx.x; i < (KBE_QMAX + 1) * KBE_QMAX; i += 128 * NB) qc[i / KBE_QMAX][i % KBE_QMAX] = Q.c[i / KBE_QMAX][i % KBE_QMAX];
+      auto weight = [&](int j, int N) {
+        const int qq = Q.q < N + 1 ? Q.q : N + 1;
+        const double w0 = qc[qq][j < qq ? j : 0], w1 = qc[qq][N - j < qq ? N - j : 0];
+        return (j < N ? 0.0 : 1.0) + (j < qq ? w0 : 0.0) + (N - j < qq ? w1 : 0.0);
+      };
+      // first integral: the nodes are the same in every lane; slot sc holds component sc
+      {
+        const int qm = d.qp < m + 1 ? d.qp : m + 1, hi = qm > m - qm + 1 ? qm : m - qm + 1;
+        const int n = qm + m + 1 - hi;
+        auto node = [&](int i) { return i < qm ? i : hi + i - qm; };
+        auto load = [&](int jn, cplx* S) {
+          if (in) {
+            const EndBlock<NB> G(d, row64, col0, diag, k, m, jn, tp);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) v[b] = G.at(sc, a, b);
+          }
+          sigma_row(2, jn, S);
+        };
+        load(node(0), S0);
+        for (int i = 0; i < n; ++i) {
+          put(v);
+          __syncthreads();
+          if (i + 1 < n) load(node(i + 1), S1);
+          if (in)
+            add(S0, weight(node(i), m), [&](int l, int b) { return s0[(sc * NBB + l * NB + b) * 64 + lane]; });
+#pragma unroll
+          for (int l = 0; l < NB; ++l) S0[l] = S1[l];
+          __syncthreads();
+        }
+      }
+      // second integral, nodes u (slot 0) and t' - u (slot 1): the wavefronts of component sc load slot sc
+      {
+        const int qt = d.qp < tp + 1 ? d.qp : tp + 1;
+        const int n0 = in && tp > 0 ? qt : 0;                                       // nodes 0 .. qt - 1
+        const int n1 = in && tp > 0 ? (qt < tp + 1 - qt ? qt : tp + 1 - qt) : 0;    // the rest of t' - qt + 1 .. t'
+        cplx T0[NB], T1[NB];
+        auto load = [&](int u, cplx* S, cplx* T) {
+          if (u < (sc ? n1 : n0)) {
+            const EndBlock<NB> G(d, row64, col0, diag, k, m, sc ? tp - u : u, tp);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) v[b] = csub(G.at(0, a, b), G.at(1, a, b));   // -(G^> - G^<)
+          }
+          if (u < n0) sigma_row(sc, u, S);
+          if (u < n1) sigma_row(sc, tp - u, T);
+        };
+        load(0, S0, T0);
+        for (int u = 0; u < d.qp; ++u) {
+          put(v);
+          __syncthreads();
+          if (u + 1 < d.qp) load(u + 1, S1, T1);
+          if (u < n0) add(S0, weight(u, tp), [&](int l, int b) { return s0[(l * NB + b) * 64 + lane]; });
+          if (u < n1) add(T0, weight(tp - u, tp), [&](int l, int b) { return s0[(NBB + l * NB + b) * 64 + lane]; });
+#pragma unroll
+          for (int l = 0; l < NB; ++l) {
+            S0[l] = S1[l];
+            T0[l] = T1[l];
+          }
+          __syncthreads();
+        }
+      }
+    } else {
+      __syncthreads();
+    }
+    if (in) {
       if constexpr (!GREG) {
         // trapezoid: half weights at j = 0 and j = m (first integral), j = 0 and j = t' (second)
         term(2, m, 0.5, [&](int l, int b) { return row64[row64_idx(d, m, k, sc * NBB + l * NB + b, tp)]; });
@@ -2408,34 +2494,6 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
           term(sc, 0, 0.5, [&](int l, int b) {
             return csub(s0[(NBB + l * NB + b) * 64 + lane], s0[(l * NB + b) * 64 + lane]);
           });
-        }
-      } else {
-        // Gregory end corrections (d.qp nodes per end): against the bulk's unit weights,
-        //   E = sum_j (w^(m)_j - [j < m]) SR_mj G_jt'  +  sum_{j <= t'} (w^(t')_j - [j < t']) Sigma_mj GA_jt',
-        // nonzero on the nodes j < q' and j > N - q' of each interval (q' = min(qp, N + 1)).
-        const int qm = d.qp < m + 1 ? d.qp : m + 1;
-        for (int r = 0; r < 2; ++r) {
-          int j0 = r == 0 ? 0 : (qm > m - qm + 1 ? qm : m - qm + 1);
-          int j1 = r == 0 ? qm : m + 1;
-          for (int j = j0; j < j1; ++j) {
-            double wgt = quad_w(Q, j, m) - (j < m ? 1.0 : 0.0);
-            if (wgt == 0.0) continue;
-            const EndBlock<NB> G(d, row64, col0, diag, k, m, j, tp);
-            term(2, j, wgt, [&](int l, int b) { return G.at(sc, l, b); });
-          }
-        }
-        if (tp > 0) {
-          const int qt = d.qp < tp + 1 ? d.qp : tp + 1;
-          for (int r = 0; r < 2; ++r) {
-            int j0 = r == 0 ? 0 : (qt > tp - qt + 1 ? qt : tp - qt + 1);
-            int j1 = r == 0 ? qt : tp + 1;
-            for (int j = j0; j < j1; ++j) {
-              double wgt = quad_w(Q, j, tp) - (j < tp ? 1.0 : 0.0);
-              if (wgt == 0.0) continue;
-              const EndBlock<NB> G(d, row64, col0, diag, k, m, j, tp);
-              term(sc, j, wgt, [&](int l, int b) { return csub(G.at(0, l, b), G.at(1, l, b)); });   // -(G^> - G^<)
-            }
-          }
         }
       }
       // column sums over the row segments, in groups whose loads are issued together
