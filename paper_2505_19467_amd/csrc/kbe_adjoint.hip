@@ -612,7 +612,7 @@ __global__ __launch_bounds__(256) void k_adj_sigma(Dims d, const cplx* __restric
   cplx* tg = lds + 3 * nk;
   auto dft = [&](int sgn, double scale) {
     if constexpr (NX > 0) grid_dft_ct<NX, NY>(xl, xg, tl, tg, twx, twy, sgn, scale);
-    else grid_dft(xl, xg, tl, tg, nx, ny, twx, twy, sgn, scale);
+    else grid_dft(d, xl, xg, tl, tg, twx, twy, sgn, scale);
   };
   int total = (m + 1) * NBB;
   int per = (total + 7) >> 3;

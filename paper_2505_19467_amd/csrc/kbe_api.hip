@@ -79,6 +79,8 @@ int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   d.spb = (c->nb <= 2 && !d.mfma) ? 2 : 1;
   d.qp = c->quad_points > 1 ? c->quad_points : 1;
   d.rring = d.qp > 2 ? d.qp : 2;
+  d.fx = kbe::fft_split(d.nkx);
+  d.fy = kbe::fft_split(d.nky);
   d.N = c->nt_max + 1;
   d.P = d.mfma ? 256 * kbe::quad_base((d.N + 63) / 64, d.N) : kbe::strip_base((d.N + 63) / 64, d.N);
   const size_t cz = sizeof(cplx);

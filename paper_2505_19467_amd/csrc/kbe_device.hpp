@@ -90,6 +90,7 @@ struct Dims {
   int qp;          // quadrature nodes per end carrying end corrections (1: trapezoid)
   int cseg;        // row segments a column strip's history sums can be split into (column-sum slots)
   int rring;       // FP64 working rows kept (the last rring rows, max(2, qp))
+  int fx, fy;      // line-transform splits: the largest divisor f of nkx (nky) with f * f <= nkx (nky)
   int64_t P;       // history elements per (k, component): one k occupies C * P elements
 };
 
@@ -513,6 +514,14 @@ __host__ __device__ __forceinline__ int fft_split(int n) {
   return best;
 }
 
+// Division by a fixed divisor of numbers below 2^16 (the transforms' item counts): one multiply-high
+// instead of the ~40 instructions of an integer division.
+struct FastDiv {
+  unsigned mul;
+  __device__ __forceinline__ explicit FastDiv(int div) : mul(0xFFFFFFFFu / (unsigned)div + 1u) {}
+  __device__ __forceinline__ int operator()(int x) const { return (int)__umulhi((unsigned)x, mul); }
+};
+
 // In-place DFT of the lines of two arrays held in LDS:
 //   x[line][q] <- scale * sum_p x[line][p] w^{sgn p q},  w = e^{2 pi i / n},
 // element p of a line at line * line_mul + p * stride; (t0, t1) are scratch of the same shape.
@@ -520,93 +529,107 @@ __host__ __device__ __forceinline__ int fft_split(int n) {
 // q = q1 + n1 q2: first the n1-point transforms over p1 with the twiddle w^{p2 q1} into the
 // scratch, then the n2-point transforms over p2 back into x; each output costs n1 + n2
 // multiply-adds instead of n. Horner chains in registers (8 outputs per item), roots from the
-// LDS table tw (n entries, fill_roots).
+// LDS table tw (n entries, fill_roots). Bound by the latency of the chains and of their LDS reads
+// (unrolled, so that a chain's next reads are in flight). n >= 2.
 // Every stage ends with a block barrier; the caller synchronises before the first.
 __device__ __forceinline__ void axis_dft(cplx* __restrict__ x0, cplx* __restrict__ x1, cplx* __restrict__ t0,
-                                         cplx* __restrict__ t1, int n, int nlines, int line_mul, int stride,
+                                         cplx* __restrict__ t1, int n, int n1, int nlines, int line_mul, int stride,
                                          const cplx* __restrict__ tw, int sgn, double scale) {
-  const int n1 = fft_split(n);
   if (n1 == 1) {
-    int items = 2 * nlines * n;
+    const int items = 2 * nlines * n;
+    const FastDiv by_array(nlines * n), by_n(n);
+    auto place = [&](int it, int& arr, int& line, int& q) {
+      arr = nlines * n == 1 ? it : by_array(it);
+      const int rem = it - arr * nlines * n;
+      line = n == 1 ? rem : by_n(rem);
+      q = rem - line * n;
+    };
     for (int it = threadIdx.x; it < items; it += blockDim.x) {
-      int arr = it / (nlines * n);
-      int rem = it - arr * nlines * n;
-      int line = rem / n, q = rem - (rem / n) * n;
+      int arr, line, q;
+      place(it, arr, line, q);
       const cplx* x = (arr ? x1 : x0) + line * line_mul;
       cplx z = root(tw, q, sgn), acc = czero();
+#pragma unroll 8
       for (int p = n - 1; p >= 0; --p) acc = cadd(cmul(acc, z), x[p * stride]);
       (arr ? t1 : t0)[line * line_mul + q * stride] = cscal(acc, scale);
     }
     __syncthreads();
     for (int it = threadIdx.x; it < items; it += blockDim.x) {
-      int arr = it / (nlines * n);
-      int rem = it - arr * nlines * n;
-      int line = rem / n, q = rem - (rem / n) * n;
+      int arr, line, q;
+      place(it, arr, line, q);
       int o = line * line_mul + q * stride;
       (arr ? x1 : x0)[o] = (arr ? t1 : t0)[o];
     }
     __syncthreads();
     return;
   }
-  const int n2 = n / n1;
+  const int n2 = FastDiv(n1)(n);
   constexpr int Q = 8;
   // stage A: item = (array, line, p2, group of 8 q1): Horner chains over p1 read from LDS
   const int groupsA = (n1 + Q - 1) / Q;
-  int itemsA = 2 * nlines * n2 * groupsA;
-  for (int it = threadIdx.x; it < itemsA; it += blockDim.x) {
-    int arr = it / (nlines * n2 * groupsA);
-    int rem = it - arr * nlines * n2 * groupsA;
-    int line = rem / (n2 * groupsA);
-    rem -= line * n2 * groupsA;
-    int p2 = rem / groupsA, g = rem - (rem / groupsA) * groupsA;
-    const cplx* x = (arr ? x1 : x0) + line * line_mul;
-    cplx* t = (arr ? t1 : t0) + line * line_mul;
-    cplx z[Q], acc[Q];
+  const int itemsA = 2 * nlines * n2 * groupsA;
+  {
+    const FastDiv by_array(nlines * n2 * groupsA), by_line(n2 * groupsA);
+    for (int it = threadIdx.x; it < itemsA; it += blockDim.x) {
+      int arr = by_array(it);
+      int rem = it - arr * nlines * n2 * groupsA;
+      int line = by_line(rem);
+      rem -= line * n2 * groupsA;
+      int p2 = groupsA == 1 ? rem : rem / groupsA, g = rem - p2 * groupsA;
+      const cplx* x = (arr ? x1 : x0) + line * line_mul;
+      cplx* t = (arr ? t1 : t0) + line * line_mul;
+      cplx z[Q], acc[Q];
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      int q1 = g * Q + r;
-      z[r] = root(tw, ((q1 < n1 ? q1 : 0) * n2) % n, sgn);
-      acc[r] = czero();
-    }
-    for (int p1 = n1 - 1; p1 >= 0; --p1) {
-      cplx v = x[(p1 * n2 + p2) * stride];
+      for (int r = 0; r < Q; ++r) {
+        int q1 = g * Q + r;
+        z[r] = root(tw, (q1 < n1 ? q1 : 0) * n2, sgn);
+        acc[r] = czero();
+      }
+#pragma unroll 4
+      for (int p1 = n1 - 1; p1 >= 0; --p1) {
+        cplx v = x[(p1 * n2 + p2) * stride];
 #pragma unroll
-      for (int r = 0; r < Q; ++r) acc[r] = cadd(cmul(acc[r], z[r]), v);
-    }
+        for (int r = 0; r < Q; ++r) acc[r] = cadd(cmul(acc[r], z[r]), v);
+      }
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      int q1 = g * Q + r;
-      if (q1 < n1) t[(q1 * n2 + p2) * stride] = cmul(acc[r], root(tw, (p2 * q1) % n, sgn));
+      for (int r = 0; r < Q; ++r) {
+        int q1 = g * Q + r;
+        if (q1 < n1) t[(q1 * n2 + p2) * stride] = cmul(acc[r], root(tw, p2 * q1, sgn));
+      }
     }
   }
   __syncthreads();
   // stage B: item = (array, line, q1, group of 8 q2)
   const int groups = (n2 + Q - 1) / Q;
-  int itemsB = 2 * nlines * n1 * groups;
-  for (int it = threadIdx.x; it < itemsB; it += blockDim.x) {
-    int arr = it / (nlines * n1 * groups);
-    int rem = it - arr * nlines * n1 * groups;
-    int line = rem / (n1 * groups);
-    rem -= line * n1 * groups;
-    int q1 = rem / groups, g = rem - (rem / groups) * groups;
-    const cplx* t = (arr ? t1 : t0) + line * line_mul + q1 * n2 * stride;
-    cplx* x = (arr ? x1 : x0) + line * line_mul;
-    cplx z[Q], acc[Q];
+  const int itemsB = 2 * nlines * n1 * groups;
+  {
+    const FastDiv by_array(nlines * n1 * groups), by_line(n1 * groups);
+    for (int it = threadIdx.x; it < itemsB; it += blockDim.x) {
+      int arr = by_array(it);
+      int rem = it - arr * nlines * n1 * groups;
+      int line = by_line(rem);
+      rem -= line * n1 * groups;
+      int q1 = groups == 1 ? rem : rem / groups, g = rem - q1 * groups;
+      const cplx* t = (arr ? t1 : t0) + line * line_mul + q1 * n2 * stride;
+      cplx* x = (arr ? x1 : x0) + line * line_mul;
+      cplx z[Q], acc[Q];
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      int q2 = g * Q + r;
-      z[r] = root(tw, ((q2 < n2 ? q2 : 0) * n1) % n, sgn);
-      acc[r] = czero();
-    }
-    for (int p2 = n2 - 1; p2 >= 0; --p2) {
-      cplx v = t[p2 * stride];
+      for (int r = 0; r < Q; ++r) {
+        int q2 = g * Q + r;
+        z[r] = root(tw, (q2 < n2 ? q2 : 0) * n1, sgn);
+        acc[r] = czero();
+      }
+#pragma unroll 4
+      for (int p2 = n2 - 1; p2 >= 0; --p2) {
+        cplx v = t[p2 * stride];
 #pragma unroll
-      for (int r = 0; r < Q; ++r) acc[r] = cadd(cmul(acc[r], z[r]), v);
-    }
+        for (int r = 0; r < Q; ++r) acc[r] = cadd(cmul(acc[r], z[r]), v);
+      }
 #pragma unroll
-    for (int r = 0; r < Q; ++r) {
-      int q2 = g * Q + r;
-      if (q2 < n2) x[(q1 + n1 * q2) * stride] = cscal(acc[r], scale);
+      for (int r = 0; r < Q; ++r) {
+        int q2 = g * Q + r;
+        if (q2 < n2) x[(q1 + n1 * q2) * stride] = cscal(acc[r], scale);
+      }
     }
   }
   __syncthreads();
@@ -622,15 +645,15 @@ constexpr int fft_split_ct(int n) {
 
 // axis_dft with the line length, line count and layout fixed at compile time: the same two
 // Cooley-Tukey stages, with every loop unrolled so that the Horner chains of different outputs
-// are independent instruction streams (composite n only).
-template <int N, int NLINES, int LM, int ST>
+// are independent instruction streams (composite n only). The block has T threads.
+template <int N, int NLINES, int LM, int ST, int T>
 __device__ __forceinline__ void axis_dft_ct(cplx* __restrict__ x0, cplx* __restrict__ x1, cplx* __restrict__ t0,
                                             cplx* __restrict__ t1, const cplx* __restrict__ tw, int sgn, double scale) {
   constexpr int N1 = fft_split_ct(N), N2 = N / N1;
   static_assert(N1 > 1, "prime line lengths take the runtime transform");
   constexpr int IA = 2 * NLINES * N2;  // stage A items: (array, line, p2)
 #pragma unroll
-  for (int it0 = 0; it0 < IA; it0 += 256) {
+  for (int it0 = 0; it0 < IA; it0 += T) {
     int it = it0 + threadIdx.x;
     if (it < IA) {
       int arr = it / (NLINES * N2);
@@ -653,7 +676,7 @@ __device__ __forceinline__ void axis_dft_ct(cplx* __restrict__ x0, cplx* __restr
   __syncthreads();
   constexpr int IB = 2 * NLINES * N1;  // stage B items: (array, line, q1), all N2 outputs each
 #pragma unroll
-  for (int it0 = 0; it0 < IB; it0 += 256) {
+  for (int it0 = 0; it0 < IB; it0 += T) {
     int it = it0 + threadIdx.x;
     if (it < IB) {
       int arr = it / (NLINES * N1);
@@ -681,19 +704,19 @@ __device__ __forceinline__ void axis_dft_ct(cplx* __restrict__ x0, cplx* __restr
 }
 
 // Power-of-two line length n (one line per array, contiguous): Stockham autosort FFT in
-// radix-4 stages (one radix-2 stage first when log2 n is odd), ping-ponging between x and the
-// scratch t. Stage with sub-length Ns (the product of the radices before it) and radix R:
-// butterfly j reads x[j + r n/R], r < R, multiplies by w^{sgn (j mod Ns) r n/(Ns R)}, takes the
-// R-point transform and writes y[(j / Ns) Ns R + (j mod Ns) + r Ns]; after the last stage the
-// output is in natural order (n log4 n work instead of n (n1 + n2)). The scale is applied by
-// the last stage; a result left in the scratch is copied back. Roots from the LDS table tw
-// (n entries). Every stage ends with a block barrier; the caller synchronises before the first.
-__device__ __forceinline__ void axis_fft_pow2(cplx* __restrict__ x0, cplx* __restrict__ x1, cplx* __restrict__ t0,
-                                              cplx* __restrict__ t1, int n, const cplx* __restrict__ tw, int sgn,
-                                              double scale) {
+// radix-4 stages (one radix-2 stage first when log2 n is odd). Stage with sub-length Ns (the product
+// of the radices before it) and radix R: butterfly j reads x[j + r n/R], r < R, multiplies by
+// w^{sgn (j mod Ns) r n/(Ns R)}, takes the R-point transform and writes
+// x[(j / Ns) Ns R + (j mod Ns) + r Ns]; after the last stage the output is in natural order
+// (n log4 n work instead of n (n1 + n2)). The block has a thread for each of a stage's butterflies
+// (at least n / 2, n if log2 n is odd), which holds its inputs across a barrier, so the stages work in
+// place: half the LDS of a ping-pong, three blocks per CU instead of one at n = 1024. The scale is
+// applied by the last stage. Roots from the LDS table tw (n entries). Every stage ends with a block
+// barrier; the caller synchronises before the first.
+__device__ __forceinline__ void axis_fft_pow2(cplx* __restrict__ x0, cplx* __restrict__ x1, int n,
+                                              const cplx* __restrict__ tw, int sgn, double scale) {
   int lg = 0;
   while ((1 << lg) < n) ++lg;
-  cplx *s0 = x0, *s1 = x1, *d0 = t0, *d1 = t1;
   // Ns, R and n are powers of two: the index arithmetic below is shifts and masks
   int lgNs = 0;
   int rem = lg;
@@ -705,66 +728,62 @@ __device__ __forceinline__ void axis_fft_pow2(cplx* __restrict__ x0, cplx* __res
     const double sc = last ? scale : 1.0;
     const int nb = n >> lgR;                // butterflies per array
     const int lgu = lg - lgNs - lgR;        // root step of a butterfly: n / (Ns R) per unit of j mod Ns
-    for (int it = threadIdx.x; it < 2 * nb; it += blockDim.x) {
-      const int arr = it >= nb;
-      const int j = it - arr * nb;
-      const cplx* src = arr ? s1 : s0;
-      cplx* dst = arr ? d1 : d0;
-      const int jm = j & (Ns - 1);
-      const int ustep = jm << lgu;
-      const int base = ((j >> lgNs) << (lgNs + lgR)) + jm;
+    const int it = threadIdx.x;
+    const bool on = it < 2 * nb;
+    const int arr = it >= nb;
+    const int j = it - arr * nb;
+    cplx* x = arr ? x1 : x0;
+    const int jm = j & (Ns - 1);
+    const int ustep = jm << lgu;
+    const int base = ((j >> lgNs) << (lgNs + lgR)) + jm;
+    cplx v0 = czero(), v1 = czero(), v2 = czero(), v3 = czero();
+    if (on) {
+      v0 = x[j];
+      v1 = cmul(x[j + nb], root(tw, ustep, sgn));
+      if (R == 4) {
+        v2 = cmul(x[j + 2 * nb], root(tw, (2 * ustep) & (n - 1), sgn));
+        v3 = cmul(x[j + 3 * nb], root(tw, (3 * ustep) & (n - 1), sgn));
+      }
+    }
+    __syncthreads();
+    if (on) {
       if (R == 2) {
-        cplx a = src[j], b = cmul(src[j + nb], root(tw, ustep, sgn));
-        dst[base] = cscal(cadd(a, b), sc);
-        dst[base + Ns] = cscal(csub(a, b), sc);
+        x[base] = cscal(cadd(v0, v1), sc);
+        x[base + Ns] = cscal(csub(v0, v1), sc);
       } else {
-        cplx v0 = src[j];
-        cplx v1 = cmul(src[j + nb], root(tw, ustep, sgn));
-        cplx v2 = cmul(src[j + 2 * nb], root(tw, (2 * ustep) & (n - 1), sgn));
-        cplx v3 = cmul(src[j + 3 * nb], root(tw, (3 * ustep) & (n - 1), sgn));
         cplx s02 = cadd(v0, v2), d02 = csub(v0, v2), s13 = cadd(v1, v3), d13 = csub(v1, v3);
         cplx id13 = sgn > 0 ? cmuli(d13) : cneg(cmuli(d13));  // (sgn i) (v1 - v3)
-        dst[base] = cscal(cadd(s02, s13), sc);
-        dst[base + Ns] = cscal(cadd(d02, id13), sc);
-        dst[base + 2 * Ns] = cscal(csub(s02, s13), sc);
-        dst[base + 3 * Ns] = cscal(csub(d02, id13), sc);
+        x[base] = cscal(cadd(s02, s13), sc);
+        x[base + Ns] = cscal(cadd(d02, id13), sc);
+        x[base + 2 * Ns] = cscal(csub(s02, s13), sc);
+        x[base + 3 * Ns] = cscal(csub(d02, id13), sc);
       }
     }
     __syncthreads();
     lgNs += lgR;
-    cplx* q0 = s0;
-    cplx* q1 = s1;
-    s0 = d0;
-    s1 = d1;
-    d0 = q0;
-    d1 = q1;
-  }
-  if (s0 != x0) {  // an odd number of stages left the result in the scratch
-    for (int it = threadIdx.x; it < 2 * n; it += blockDim.x) {
-      if (it < n) x0[it] = t0[it];
-      else x1[it - n] = t1[it - n];
-    }
-    __syncthreads();
   }
 }
 
+// Chains that take the power-of-two transform (no scratch lines).
+__host__ __device__ __forceinline__ bool pow2_chain(int nx, int ny) { return ny == 1 && nx >= 128 && (nx & (nx - 1)) == 0; }
 // Index transform of an nx x ny grid (k = ix * ny + iy) for two arrays in place:
 //   x(R) <- scale * sum_k e^{sgn 2 pi i (ix Rx / nx + iy Ry / ny)} x(k); y lines, then x lines.
-__device__ __forceinline__ void grid_dft(cplx* x0, cplx* x1, cplx* t0, cplx* t1, int nx, int ny, const cplx* twx,
+__device__ __forceinline__ void grid_dft(const Dims& d, cplx* x0, cplx* x1, cplx* t0, cplx* t1, const cplx* twx,
                                          const cplx* twy, int sgn, double scale) {
-  if (ny == 1 && nx >= 128 && (nx & (nx - 1)) == 0) {  // long power-of-two chains
-    axis_fft_pow2(x0, x1, t0, t1, nx, twx, sgn, scale);
+  const int nx = d.nkx, ny = d.nky;
+  if (pow2_chain(nx, ny)) {  // long power-of-two chains
+    axis_fft_pow2(x0, x1, nx, twx, sgn, scale);
     return;
   }
-  if (ny > 1) axis_dft(x0, x1, t0, t1, ny, nx, ny, 1, twy, sgn, 1.0);
-  axis_dft(x0, x1, t0, t1, nx, ny, 1, ny, twx, sgn, scale);
+  if (ny > 1) axis_dft(x0, x1, t0, t1, ny, d.fy, nx, ny, 1, twy, sgn, 1.0);
+  axis_dft(x0, x1, t0, t1, nx, d.fx, ny, 1, ny, twx, sgn, scale);
 }
 // grid_dft for grid sizes fixed at compile time (NY = 1: a chain, only the x lines)
-template <int NX, int NY>
+template <int NX, int NY, int T = 256>
 __device__ __forceinline__ void grid_dft_ct(cplx* x0, cplx* x1, cplx* t0, cplx* t1, const cplx* twx, const cplx* twy,
                                             int sgn, double scale) {
-  if constexpr (NY > 1) axis_dft_ct<NY, NX, NY, 1>(x0, x1, t0, t1, twy, sgn, 1.0);
-  axis_dft_ct<NX, NY, 1, NY>(x0, x1, t0, t1, twx, sgn, scale);
+  if constexpr (NY > 1) axis_dft_ct<NY, NX, NY, 1, T>(x0, x1, t0, t1, twy, sgn, 1.0);
+  axis_dft_ct<NX, NY, 1, NY, T>(x0, x1, t0, t1, twx, sgn, scale);
 }
 
 }  // namespace kbe

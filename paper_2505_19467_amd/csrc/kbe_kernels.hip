@@ -514,8 +514,20 @@ __global__ __launch_bounds__(256) void k_props(Dims d, PropsArgs x, ObsArgs o, i
 // row m that several t_j share stay in one L2. NX, NY > 0: the grid size is fixed at compile
 // time (unrolled transforms, 1.8x faster on 24 x 24); NX = NY = 0: any grid, sizes from d.
 // Dynamic LDS: four lines of N_k points and the nx + ny roots of unity.
+// Threads per block: 256, or as many as the larger stage of a compile-time transform has items where
+// that is more (24 x 24: 288 -> 320 threads, 24.2 -> 22.9 us at m <= 300; with fewer than 256 on the small
+// grids the loads have too few wavefronts: 12 x 12 10.2 -> 10.9 us with 128). Any other grid takes 512
+// threads from 512 points on (a block's LDS leaves room for one to three such blocks per CU: at 1024
+// points 105 -> 58 and 118 -> 69 us for the two interband kernels with the in-place transform), else 256.
+template <int NX, int NY>
+constexpr int sigma_threads() {
+  if (NX == 0) return 512;
+  int items = 2 * NY * (NX / fft_split_ct(NX > 0 ? NX : 4));
+  if (NY > 1 && 2 * NX * (NY / fft_split_ct(NY)) > items) items = 2 * NX * (NY / fft_split_ct(NY));
+  return items > 256 ? (items + 63) / 64 * 64 : 256;
+}
 template <int NB, int NX, int NY>
-__global__ __launch_bounds__(256) void k_sigma(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ sig,
+__global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ sig,
                                                int m, double UU, int corr) {
   constexpr int NBB = NB * NB;
   extern __shared__ cplx lds[];
@@ -523,29 +535,41 @@ __global__ __launch_bounds__(256) void k_sigma(Dims d, const cplx* __restrict__ 
   const int nx = NX > 0 ? NX : d.nkx, ny = NX > 0 ? NY : d.nky;
   cplx* gl = lds;
   cplx* gg = lds + nk;
-  cplx* tl = lds + 2 * nk;
-  cplx* tg = lds + 3 * nk;
-  cplx* twx = lds + 4 * nk;  // roots of unity, nx and ny entries
+  // two lines and their scratch (a long power-of-two chain needs none)
+  const int lines = NX == 0 && pow2_chain(nx, ny) ? 2 : 4;
+  cplx* tl = lds + (lines - 2) * nk;
+  cplx* tg = lds + (lines - 1) * nk;
+  cplx* twx = lds + lines * nk;  // roots of unity, nx and ny entries
   cplx* twy = twx + nx;
   int total = (m + 1) * NBB;
   int per = (total + 7) >> 3;
   int item = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (item >= total) return;
   int j = item / NBB, ab = item - (item / NBB) * NBB;
-  int t = threadIdx.x;
+  const int t = threadIdx.x, nt = NX > 0 ? sigma_threads<NX, NY>() : blockDim.x;
+  // at most two points a thread; the roots are made while the loads are in flight
+  cplx vl[2], vg[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int k = t + i * nt < nk ? t + i * nt : nk - 1;
+    vl[i] = row64[row64_idx(d, m, k, ab, j)];
+    vg[i] = row64[row64_idx(d, m, k, NBB + ab, j)];
+  }
   fill_roots(twx, nx);
   fill_roots(twy, ny);
-  for (int k = t; k < nk; k += 256) {
-    gl[k] = row64[row64_idx(d, m, k, ab, j)];
-    gg[k] = row64[row64_idx(d, m, k, NBB + ab, j)];
-  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (t + i * nt < nk) {
+      gl[t + i * nt] = vl[i];
+      gg[t + i * nt] = vg[i];
+    }
   __syncthreads();
   // k -> R (1/N_k)
   if constexpr (NX > 0)
-    grid_dft_ct<NX, NY>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+    grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   else
-    grid_dft(gl, gg, tl, tg, nx, ny, twx, twy, +1, 1.0 / nk);
-  for (int o = t; o < nk; o += 256) {
+    grid_dft(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+  for (int o = t; o < nk; o += nt) {
     cplx al = gl[o], ag = gg[o];
     cplx sl = czero(), sg = czero();
     if (corr) {
@@ -558,10 +582,10 @@ __global__ __launch_bounds__(256) void k_sigma(Dims d, const cplx* __restrict__ 
   __syncthreads();
   // R -> k
   if constexpr (NX > 0)
-    grid_dft_ct<NX, NY>(gl, gg, tl, tg, twx, twy, -1, 1.0);
+    grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, -1, 1.0);
   else
-    grid_dft(gl, gg, tl, tg, nx, ny, twx, twy, -1, 1.0);
-  for (int o = t; o < nk; o += 256) {
+    grid_dft(d, gl, gg, tl, tg, twx, twy, -1, 1.0);
+  for (int o = t; o < nk; o += nt) {
     cplx al = gl[o], ag = gg[o];
     sig[sig_idx(d, o, 0, ab, j)] = al;
     sig[sig_idx(d, o, 1, ab, j)] = ag;
@@ -581,50 +605,64 @@ __device__ __forceinline__ int64_t gr_idx(const Dims& d, int j, int comp, int ab
   return (((int64_t)j * 2 + comp) * 4 + ab) * d.nk + R;
 }
 template <int NX, int NY>
-__global__ __launch_bounds__(256) void k_sigma_fwd(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ gR,
+__global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_fwd(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ gR,
                                                    int m) {
   extern __shared__ cplx lds[];
   const int nk = NX > 0 ? NX * NY : d.nk;
   const int nx = NX > 0 ? NX : d.nkx, ny = NX > 0 ? NY : d.nky;
   cplx* gl = lds;
   cplx* gg = lds + nk;
-  cplx* tl = lds + 2 * nk;
-  cplx* tg = lds + 3 * nk;
-  cplx* twx = lds + 4 * nk;
+  // two lines and their scratch (a long power-of-two chain needs none)
+  const int lines = NX == 0 && pow2_chain(nx, ny) ? 2 : 4;
+  cplx* tl = lds + (lines - 2) * nk;
+  cplx* tg = lds + (lines - 1) * nk;
+  cplx* twx = lds + lines * nk;
   cplx* twy = twx + nx;
   int total = (m + 1) * 4;
   int per = (total + 7) >> 3;
   int item = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (item >= total) return;
   int j = item >> 2, ab = item & 3;
-  int t = threadIdx.x;
+  const int t = threadIdx.x, nt = NX > 0 ? sigma_threads<NX, NY>() : blockDim.x;
+  // at most two points a thread; the roots are made while the loads are in flight
+  cplx vl[2], vg[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int k = t + i * nt < nk ? t + i * nt : nk - 1;
+    vl[i] = row64[row64_idx(d, m, k, ab, j)];
+    vg[i] = row64[row64_idx(d, m, k, 4 + ab, j)];
+  }
   fill_roots(twx, nx);
   fill_roots(twy, ny);
-  for (int k = t; k < nk; k += 256) {
-    gl[k] = row64[row64_idx(d, m, k, ab, j)];
-    gg[k] = row64[row64_idx(d, m, k, 4 + ab, j)];
-  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (t + i * nt < nk) {
+      gl[t + i * nt] = vl[i];
+      gg[t + i * nt] = vg[i];
+    }
   __syncthreads();
   if constexpr (NX > 0)
-    grid_dft_ct<NX, NY>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+    grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   else
-    grid_dft(gl, gg, tl, tg, nx, ny, twx, twy, +1, 1.0 / nk);
-  for (int o = t; o < nk; o += 256) {
+    grid_dft(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+  for (int o = t; o < nk; o += nt) {
     gR[gr_idx(d, j, 0, ab, o)] = gl[o];
     gR[gr_idx(d, j, 1, ab, o)] = gg[o];
   }
 }
 template <int NX, int NY>
-__global__ __launch_bounds__(256) void k_sigma_ib(Dims d, const cplx* __restrict__ gR, cplx* __restrict__ sig,
+__global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_ib(Dims d, const cplx* __restrict__ gR, cplx* __restrict__ sig,
                                                   int m, double UU, int corr) {
   extern __shared__ cplx lds[];
   const int nk = NX > 0 ? NX * NY : d.nk;
   const int nx = NX > 0 ? NX : d.nkx, ny = NX > 0 ? NY : d.nky;
   cplx* sl = lds;
   cplx* sg = lds + nk;
-  cplx* tl = lds + 2 * nk;
-  cplx* tg = lds + 3 * nk;
-  cplx* twx = lds + 4 * nk;
+  // two lines and their scratch (a long power-of-two chain needs none)
+  const int lines = NX == 0 && pow2_chain(nx, ny) ? 2 : 4;
+  cplx* tl = lds + (lines - 2) * nk;
+  cplx* tg = lds + (lines - 1) * nk;
+  cplx* twx = lds + lines * nk;
   cplx* twy = twx + nx;
   int total = (m + 1) * 4;
   int per = (total + 7) >> 3;
@@ -634,10 +672,10 @@ __global__ __launch_bounds__(256) void k_sigma_ib(Dims d, const cplx* __restrict
   int a = ab >> 1, b = ab & 1;
   int cross = (1 - a) * 2 + (1 - b);                 // orbital pair (abar, bbar)
   double pre = ((a + b) & 1) ? UU : -UU;             // -U^2 (-1)^(a+b)
-  int t = threadIdx.x;
+  const int t = threadIdx.x, nt = NX > 0 ? sigma_threads<NX, NY>() : blockDim.x;
   fill_roots(twx, nx);
   fill_roots(twy, ny);
-  for (int o = t; o < nk; o += 256) {
+  for (int o = t; o < nk; o += nt) {
     cplx l00 = gR[gr_idx(d, j, 0, 0, o)], l01 = gR[gr_idx(d, j, 0, 1, o)];
     cplx l10 = gR[gr_idx(d, j, 0, 2, o)], l11 = gR[gr_idx(d, j, 0, 3, o)];
     cplx g00 = gR[gr_idx(d, j, 1, 0, o)], g01 = gR[gr_idx(d, j, 1, 1, o)];
@@ -650,10 +688,10 @@ __global__ __launch_bounds__(256) void k_sigma_ib(Dims d, const cplx* __restrict
   }
   __syncthreads();
   if constexpr (NX > 0)
-    grid_dft_ct<NX, NY>(sl, sg, tl, tg, twx, twy, -1, 1.0);
+    grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(sl, sg, tl, tg, twx, twy, -1, 1.0);
   else
-    grid_dft(sl, sg, tl, tg, nx, ny, twx, twy, -1, 1.0);
-  for (int o = t; o < nk; o += 256) {
+    grid_dft(d, sl, sg, tl, tg, twx, twy, -1, 1.0);
+  for (int o = t; o < nk; o += nt) {
     cplx vl = sl[o], vg = sg[o];
     sig[sig_idx(d, o, 0, ab, j)] = vl;
     sig[sig_idx(d, o, 1, ab, j)] = vg;
@@ -2794,7 +2832,9 @@ struct Launch {
   static hipError_t sigma(const Dims& d, const LaunchArgs& a, int m, hipStream_t st) {
     int total = (m + 1) * NB * NB;
     int per = (total + 7) / 8;
-    size_t shm = (size_t)(4 * d.nk + d.nkx + d.nky) * sizeof(cplx);
+    const size_t shm = (size_t)((pow2_chain(d.nkx, d.nky) ? 2 : 4) * d.nk + d.nkx + d.nky) * sizeof(cplx);
+    // large grids: twice the threads (a block's LDS leaves room for one to three blocks per CU)
+    const bool large = d.nk >= 512;
     if constexpr (NB == 2) {
       if (a.interaction == KBE_DEV_INT_INTERBAND) {
         auto fwd = k_sigma_fwd<0, 0>;
@@ -2806,20 +2846,23 @@ struct Launch {
         hipError_t e = allow_lds((const void*)fwd, shm);
         if (e == hipSuccess) e = allow_lds((const void*)ib, shm);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(fwd, dim3(per * 8), dim3(256), shm, st, d, (const cplx*)a.row64, a.gR, m);
-        hipLaunchKernelGGL(ib, dim3(per * 8), dim3(256), shm, st, d, (const cplx*)a.gR, a.sig, m, a.UU, a.corr);
+        int nthr = large ? 512 : 256;
+        if (d.nkx == 16 && d.nky == 1) nthr = sigma_threads<16, 1>();
+        hipLaunchKernelGGL(fwd, dim3(per * 8), dim3(nthr), shm, st, d, (const cplx*)a.row64, a.gR, m);
+        hipLaunchKernelGGL(ib, dim3(per * 8), dim3(nthr), shm, st, d, (const cplx*)a.gR, a.sig, m, a.UU, a.corr);
         return hipGetLastError();
       }
     }
     // grids of the standard workloads with compile-time transforms, any other grid at run time
     auto kern = k_sigma<NB, 0, 0>;
-    if (d.nkx == 24 && d.nky == 24) kern = k_sigma<NB, 24, 24>;
-    else if (d.nkx == 16 && d.nky == 16) kern = k_sigma<NB, 16, 16>;
-    else if (d.nkx == 12 && d.nky == 12) kern = k_sigma<NB, 12, 12>;
-    else if (d.nkx == 16 && d.nky == 1) kern = k_sigma<NB, 16, 1>;
+    int nthr = large ? 512 : 256;
+    if (d.nkx == 24 && d.nky == 24) kern = k_sigma<NB, 24, 24>, nthr = sigma_threads<24, 24>();
+    else if (d.nkx == 16 && d.nky == 16) kern = k_sigma<NB, 16, 16>, nthr = sigma_threads<16, 16>();
+    else if (d.nkx == 12 && d.nky == 12) kern = k_sigma<NB, 12, 12>, nthr = sigma_threads<12, 12>();
+    else if (d.nkx == 16 && d.nky == 1) kern = k_sigma<NB, 16, 1>, nthr = sigma_threads<16, 1>();
     hipError_t e = allow_lds((const void*)kern, shm);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(per * 8), dim3(256), shm, st, d, (const cplx*)a.row64, a.sig, m, a.UU, a.corr);
+    hipLaunchKernelGGL(kern, dim3(per * 8), dim3(nthr), shm, st, d, (const cplx*)a.row64, a.sig, m, a.UU, a.corr);
     return hipGetLastError();
   }
   // the history sums and the equal-time integral of row m; with_props: the corrector's propagators too
