@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64) void k_init_eig(Dims d, const cplx* __restrict_
 __global__ __launch_bounds__(256) void k_init_mu(int n, const double* __restrict__ w, double temp,
                                                  double target, double* __restrict__ mu_out) {
   __shared__ double red[256];
-  __shared__ double lohi[2];
+  __shared__ double lohi[2], sum[1];
   int t = threadIdx.x;
   double lo = 1e300, hi = -1e300;
   for (int i = t; i < n; i += 256) {
@@ -94,14 +94,9 @@ __global__ __launch_bounds__(256) void k_init_mu(int n, const double* __restrict
     double mid = 0.5 * (lohi[0] + lohi[1]);
     double acc = 0.0;
     for (int i = t; i < n; i += 256) acc += 1.0 / (1.0 + exp((w[i] - mid) / temp));
-    red[t] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (t < s) red[t] += red[t + s];
-      __syncthreads();
-    }
+    block_sum_once<1>(&acc, red, sum);
     if (t == 0) {
-      if (red[0] < target) lohi[0] = mid;
+      if (sum[0] < target) lohi[0] = mid;
       else lohi[1] = mid;
     }
     __syncthreads();
