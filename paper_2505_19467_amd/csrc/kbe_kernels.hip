@@ -1823,7 +1823,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // FP32 form of k_hist_bulk_split: each half's 16 components are 8 column-interleaved pairs,
 // one 16-byte load each; FP32 products and row reductions, column sums in FP32 over each
 // wavefront's 16 rows of a 32-row chunk, then FP64. The row pair (0, 1) takes the even rows of
-// every 32-row chunk and (2, 3) the odd ones, so a chunk cut short by m keeps both pairs busy, and
+// every 32-row chunk and (2, 3) the odd ones, the next row's loads in flight through a row's arithmetic
+// (16 x 16, m = 200 / 800 400 -> 387 us, 4.36 -> 4.17 ms; 8 x 8, m = 300 230 -> 205 us; the FP64 kernel has no
+// registers for it), so a chunk cut short by m keeps both pairs busy, and
 // the whole block stores a chunk's row partials as 512-byte runs (this kernel is bound by the
 // vector ALU; the FP64 kernel's stream ran 1.7 % slower with interleaved rows and keeps 16
 // consecutive rows per pair).
@@ -1869,62 +1871,76 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const cplx32* hk = hist + strip_lane_base(d, k, s, lane) + 64 * NBB * h;
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, s));
   const float sgn = h ? 1.f : -1.f;
+  cplx32 Gq[NBB];        // the wavefront's next unmasked row, if primed
+  bool primed = false;
   int buf = 0;
   for (int cb = r0; cb < r1; cb += 32) {  // the same chunks in every wavefront
     const int rb = cb + rg;   // the wave pair's rows of the chunk: rb, rb + 2, ..., rb + 30
     cplx* st = stg[buf][h];
-    // groups of 16 rows past the strip's first 64 rows and below m need no masks (this
-    // kernel is bound by the vector ALU; the FP64 kernel keeps one path, a second one would
-    // not fit its registers)
-    auto rows16 = [&](auto tag) {
-      constexpr bool MASKED = decltype(tag)::value;
-      for (int i = 0; i < 16; ++i) {
-        const int j = rb + 2 * i;
-        if (MASKED && j >= r1) break;
-        bool v = MASKED ? (colv && tp <= j) : true;
-        const cplx32* row = hk + 64 * (int64_t)C * j;
-        cplx32 G[NBB];
+    // One row j from G (rv: the row term's mask)
+    auto row = [&](int j, bool rv, const cplx32* G) {
+      float x[NB][2 * NB];
 #pragma unroll
-        for (int p = 0; p < NBB / 2; ++p) {
-          if (v) {
-            load_stream32x2(row + 128 * p, G[2 * p], G[2 * p + 1]);
-          } else {
-            G[2 * p] = make_float2(0.f, 0.f);
-            G[2 * p + 1] = make_float2(0.f, 0.f);
-          }
-        }
-        bool rv = MASKED ? tp < j : true;
-        float x[NB][2 * NB];
+      for (int a = 0; a < NB; ++a) {
+        cplx32 SRa[NB];
 #pragma unroll
-        for (int a = 0; a < NB; ++a) {
-          cplx32 SRa[NB];
+        for (int l = 0; l < NB; ++l) SRa[l] = to32(sk[(2 * NBB + a * NB + l) * d.Tp + j]);
 #pragma unroll
-          for (int l = 0; l < NB; ++l) SRa[l] = to32(sk[(2 * NBB + a * NB + l) * d.Tp + j]);
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-          for (int b = 0; b < NB; ++b)
+          for (int l = 0; l < NB; ++l) cmac32(acc32[a * NB + b], SRa[l], G[l * NB + b]);
 #pragma unroll
-            for (int l = 0; l < NB; ++l) cmac32(acc32[a * NB + b], SRa[l], G[l * NB + b]);
+        for (int b = 0; b < NB; ++b) {
+          cplx32 t = make_float2(0.f, 0.f);
 #pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            cplx32 t = make_float2(0.f, 0.f);
-#pragma unroll
-            for (int l = 0; l < NB; ++l) cmacc32(t, sS[h][a * NB + l][lane], G[b * NB + l]);
-            x[a][2 * b] = rv ? sgn * t.x : 0.f;
-            x[a][2 * b + 1] = rv ? sgn * t.y : 0.f;
-          }
-        }
-        reduce_rows32<NB>(x);
-        int ra = reduced_row<NB>(lane);
-        if (ra >= 0) {
-#pragma unroll
-          for (int b = 0; b < NB; ++b) st[(ra * NB + b) * 32 + (j - cb)] = cmk((double)x[0][2 * b], (double)x[0][2 * b + 1]);
+          for (int l = 0; l < NB; ++l) cmacc32(t, sS[h][a * NB + l][lane], G[b * NB + l]);
+          x[a][2 * b] = rv ? sgn * t.x : 0.f;
+          x[a][2 * b + 1] = rv ? sgn * t.y : 0.f;
         }
       }
+      reduce_rows32<NB>(x);
+      int ra = reduced_row<NB>(lane);
+      if (ra >= 0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) st[(ra * NB + b) * 32 + (j - cb)] = cmk((double)x[0][2 * b], (double)x[0][2 * b + 1]);
+      }
     };
-    if (rb >= 64 * s + 64 && rb + 30 < r1)
-      rows16(BoolTag<false>{});
-    else
-      rows16(BoolTag<true>{});
+    auto load = [&](int j, cplx32* G) {
+      const cplx32* g = hk + 64 * (int64_t)C * j;
+#pragma unroll
+      for (int p = 0; p < NBB / 2; ++p) load_stream32x2(g + 128 * p, G[2 * p], G[2 * p + 1]);
+    };
+    if (rb >= 64 * s + 64 && rb + 30 < r1) {
+      // groups of 16 rows past the strip's first 64 rows and below the segment's end need no masks; the
+      // next row's loads are in flight through a row's arithmetic (across groups too)
+      if (!primed) load(rb, Gq);
+      for (int i = 0; i < 16; ++i) {
+        const int j = rb + 2 * i;
+        int jn = i < 15 ? j + 2 : rb + 32;
+        if (jn >= r1) jn = j;
+        cplx32 Gn[NBB];
+        load(jn, Gn);
+        row(j, true, Gq);
+#pragma unroll
+        for (int e = 0; e < NBB; ++e) Gq[e] = Gn[e];
+      }
+      primed = true;
+    } else {
+      primed = false;
+      for (int i = 0; i < 16; ++i) {
+        const int j = rb + 2 * i;
+        if (j >= r1) break;
+        const bool v = colv && tp <= j;
+        cplx32 G[NBB];
+        if (v) {
+          load(j, G);
+        } else {
+#pragma unroll
+          for (int e = 0; e < NBB; ++e) G[e] = make_float2(0.f, 0.f);
+        }
+        row(j, tp < j, G);
+      }
+    }
 #pragma unroll
     for (int e = 0; e < NBB; ++e) {
       acc[e].x += (double)acc32[e].x;
