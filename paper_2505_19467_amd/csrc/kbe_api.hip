@@ -353,12 +353,13 @@ struct kbe_ctx {
     if (e != hipSuccess) return fail(KBE_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
     return KBE_OK;
   }
-  int collide(const LaunchArgs& a, int m, bool with_props, const kbe::ObsStep* o = nullptr) {
+  int collide(const LaunchArgs& a, int m, const LaunchArgs* props = nullptr, double wb = 0.0,
+              const kbe::ObsStep* o = nullptr) {
     // the event pool is created whole by kbe_timing before any launch is queued; launches past
     // its end (more passes than it was sized for) run untimed
     const bool timed = timing && m >= 1 && ev_used + 2 <= ev.size();
     if (timed && hipEventRecord(ev[ev_used], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
-    int rc = check(kbe::launch_collide(L.d, a, m, with_props, o, st), "history-sum launch");
+    int rc = check(kbe::launch_collide(L.d, a, m, props, wb, o, st), "history-sum launch");
     if (rc) return rc;
     if (timed) {
       if (hipEventRecord(ev[ev_used + 1], st) != hipSuccess) return fail(KBE_ERR_HIP, "hipEventRecord failed");
@@ -367,13 +368,19 @@ struct kbe_ctx {
     }
     return KBE_OK;
   }
-  // Sigma row, equal-time collision integral, history sums of row m; with_props: also the
-  // propagators of the corrector's update. Takes the observables of the step before along.
-  int collision_parts(LaunchArgs& a, int m, bool with_props = false) {
-    if (with_props) set_A(a, (m - 0.5) * cfg.dt);
+  // What a pass of row m takes along: nothing, the propagators of the corrector's update, or (the
+  // evaluation pass, with another step to follow in the call) those of the next step's predictor.
+  enum PassProps { PROPS_NONE, PROPS_CORRECTOR, PROPS_NEXT };
+  // Sigma row, equal-time collision integral, history sums of row m, the propagators `with`. Takes
+  // the observables of the step before along.
+  int collision_parts(LaunchArgs& a, int m, PassProps with = PROPS_NONE) {
+    LaunchArgs p = a;
+    if (with == PROPS_NEXT) p.rho_prev = a.rho_cur;
+    if (with != PROPS_NONE) set_A(p, ((with == PROPS_NEXT ? m + 1 : m) - 0.5) * cfg.dt);
     int rc = check(kbe::launch_sigma(L.d, a, m, st), "self-energy launch");
     const bool o = obs_due && kbe::obs_in_pass(L.d);
-    if (!rc) rc = collide(a, m, with_props, o ? &obs_step : nullptr);
+    if (!rc) rc = collide(a, m, with == PROPS_NONE ? nullptr : &p, with == PROPS_CORRECTOR ? 0.5 : 0.0,
+                          o ? &obs_step : nullptr);
     if (!rc && o) obs_due = false;
     return rc;
   }
@@ -421,11 +428,13 @@ struct kbe_ctx {
     due_observables(m);
     return flush_observables();
   }
+  bool props_ready = false;   // the next step's propagators are in place; kbe_step leaves none so
   int one_step(bool more) {   // more: another step of the same call follows
     int m = step + 1;
     if (m > cfg.nt_max) return fail(KBE_ERR_STATE, "step index would pass nt_max");
     LaunchArgs a = args();
-    int rc = props(a, m, 0);
+    int rc = props_ready ? KBE_OK : props(a, m, 0);
+    props_ready = false;
     if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_PREDICT, st), "predictor launch");
     // Corrector passes of Algorithm "prop": all n_corr of them, or (corr_tol > 0) until the
     // largest change of row m is <= corr_tol, which needs the change on the host after each
@@ -435,7 +444,7 @@ struct kbe_ctx {
     double last_change = 0.0;
     int taken = 0;
     for (int it = 0; it < cfg.n_corr && !rc; ++it) {
-      rc = collision_parts(a, m, true);
+      rc = collision_parts(a, m, PROPS_CORRECTOR);
       a.chg = tol ? buf<double>(B_CHG) : nullptr;
       if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_CORRECT, st), "corrector launch");
       a.chg = nullptr;
@@ -460,8 +469,13 @@ struct kbe_ctx {
       }
     }
     if (!rc) passes[m] = taken;
-    if (!rc) rc = collision_parts(a, m);
+    // rho_m is final, and the evaluation reads no propagators: the next step's ride in its history
+    // pass, unless a kick replaces rho_m or this step ends the call. The observables of nb >= 3 ride
+    // in the propagators' own launch, which would be one of theirs alone.
+    const bool ahead = more && reached && !kicked(m) && kbe::obs_in_pass(L.d);
+    if (!rc) rc = collision_parts(a, m, ahead ? PROPS_NEXT : PROPS_NONE);
     if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_EVAL, st), "collision-row launch");
+    props_ready = !rc && ahead;
     if (!rc) due_observables(m);
     // the kick replaces the slice's density and collision row; a step that reports ends the call
     if (!rc && (!more || !reached || kicked(m))) rc = flush_observables();
@@ -578,9 +592,7 @@ struct kbe_ctx {
     e.I_cur = b.Ire_prev;
     e.D_cur = b.Dscratch;
     if (!rc) rc = check(kbe::launch_sigma(d, e, m - 1, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, false, nullptr, st), "history-sum launch");
-    if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
-    // recompute the predictor (row m of the working copy only)
+    // the predictor's arguments (row m of the working copy only); its propagators ride in that pass
     LaunchArgs p = a;
     p.I_prev = b.Ire_prev;
     p.rho_prev = rho0;
@@ -589,7 +601,8 @@ struct kbe_ctx {
     p.props = b.props_p;
     p.hfbuf = b.hf_p;
     p.commit = 0;
-    if (!rc) rc = check(kbe::launch_props(d, p, 0.0, nullptr, st), "propagator launch");
+    if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, &p, 0.0, nullptr, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
     if (!rc) rc = check(kbe::launch_row(d, p, m, KBE_ROW_PREDICT, st), "predictor launch");
     // recompute the corrector's collision row and propagators
     LaunchArgs c = p;
@@ -598,7 +611,7 @@ struct kbe_ctx {
     c.props = b.props_c;
     c.hfbuf = b.hf_c;
     if (!rc) rc = check(kbe::launch_sigma(d, c, m, st), "self-energy launch");
-    if (!rc) rc = check(kbe::launch_collide(d, c, m, true, nullptr, st), "history-sum launch");
+    if (!rc) rc = check(kbe::launch_collide(d, c, m, &c, 0.5, nullptr, st), "history-sum launch");
     if (!rc) rc = check(kbe::launch_row(d, c, m, KBE_ROW_EVAL, st), "collision-row launch");
     // corrector update, its propagators and mean field
     if (!rc) rc = check(kbe::launch_adj_update(d, p, b, m, 1, nubar, b.lam, b.Rbar, rho0, st), "adjoint update launch");
@@ -888,7 +901,7 @@ int kbe_stage_collision(kbe_ctx* ctx, int32_t m) {
   int rc = check_m(ctx, m, 0);
   if (rc) return rc;
   LaunchArgs a = ctx->args();
-  rc = ctx->collide(a, m, false);
+  rc = ctx->collide(a, m);
   if (!rc) rc = ctx->check(kbe::launch_row(ctx->L.d, a, m, KBE_ROW_EVAL, ctx->st), "collision-row launch");
   return rc;
 }

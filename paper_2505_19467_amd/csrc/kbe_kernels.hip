@@ -909,10 +909,11 @@ __device__ __forceinline__ void diag_block(const Dims& d, const cplx* __restrict
 }
 
 // Blocks that ride in front of a history pass's own, on work that is independent of it: the
-// equal-time integral of each k, in a corrector pass the propagators of the iterate, and in a step's
-// first pass the observables of the step before. They are a few microseconds of latency and N_k,
-// N_k nb / 256 and one block; in launches of their own they held up the stream 5 and 4 us per pass
-// and 8-18 us per step.
+// equal-time integral of each k, in a corrector pass the propagators of the iterate, in an evaluation
+// pass those of the next step's predictor (from the row's own density, final by then), and in a
+// step's first pass the observables of the step before. They are a few microseconds of latency and
+// N_k, N_k nb / 256 (propagators) and one block; in launches of their own they held up the stream
+// 5 and 4-7 us per pass and 8-18 us per step.
 struct PassExtras {
   const cplx *row64, *sig;
   cplx *Icur, *Dcur;
@@ -2876,11 +2877,11 @@ struct Launch {
     hipLaunchKernelGGL(kern, dim3(per * 8), dim3(nthr), shm, st, d, (const cplx*)a.row64, a.sig, m, a.UU, a.corr);
     return hipGetLastError();
   }
-  // the history sums and the equal-time integral of row m; with_props: the corrector's propagators too
-  static hipError_t collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
-                            hipStream_t st) {
-    PassExtras x{a.row64, a.sig, a.I_cur, a.D_cur, a.dt, a.quad, m, with_props ? props_blocks(d) : 0,
-                 props_args(a, 0.5), o ? 1 : 0, o ? obs_args(a, *o) : ObsArgs{}};
+  // the history sums and the equal-time integral of row m; props: those propagators too
+  static hipError_t collide(const Dims& d, const LaunchArgs& a, int m, const LaunchArgs* props, double wb,
+                            const ObsStep* o, hipStream_t st) {
+    PassExtras x{a.row64, a.sig, a.I_cur, a.D_cur, a.dt, a.quad, m, props ? props_blocks(d) : 0,
+                 props_args(props ? *props : a, wb), o ? 1 : 0, o ? obs_args(a, *o) : ObsArgs{}};
     const int nx = x.blocks(d);
     if (m < 1) {
       hipLaunchKernelGGL(k_extras<NB>, dim3(nx), dim3(256), 0, st, d, x);
@@ -2987,9 +2988,9 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
                      a.corr);
   return hipGetLastError();
 }
-hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
-                          hipStream_t st) {
-  KBE_DISPATCH(d.nb, collide(d, a, m, with_props, o, st));
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, const LaunchArgs* props, double wb,
+                          const ObsStep* o, hipStream_t st) {
+  KBE_DISPATCH(d.nb, collide(d, a, m, props, wb, o, st));
 }
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st) {
   KBE_DISPATCH(d.nb, row(d, a, m, mode, st));

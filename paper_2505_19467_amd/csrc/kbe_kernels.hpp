@@ -72,11 +72,11 @@ hipError_t launch_sigma_direct(const Dims& d, const LaunchArgs& a, int m, hipStr
 // the dipole kick on the completed slice m (nb = 2): the row's copies and rho_cur (and rho_other)
 hipError_t launch_kick(const Dims& d, const LaunchArgs& a, int m, double kc, double ks, cplx* rho_other,
                        hipStream_t st);
-// history sums of row m and the equal-time integral I(t_m, t_m), D_m; with_props: also what
-// launch_props(d, a, 0.5, nullptr, st) does; o (nb <= 2 only): also the observables of that slice
+// history sums of row m and the equal-time integral I(t_m, t_m), D_m; props: also what
+// launch_props(d, *props, wb, nullptr, st) does; o (nb <= 2 only): also the observables of that slice
 // (independent work in the same launch)
-hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, bool with_props, const ObsStep* o,
-                          hipStream_t st);
+hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, const LaunchArgs* props, double wb,
+                          const ObsStep* o, hipStream_t st);
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st);
 // out[0] = max of the row kernel's per-block changes at row m (one block, deterministic)
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st);
