@@ -428,14 +428,15 @@ struct kbe_ctx {
     due_observables(m);
     return flush_observables();
   }
-  bool props_ready = false;   // the next step's propagators are in place; kbe_step leaves none so
+  // what the step before left in place for the next one of the same call; kbe_step leaves nothing so
+  enum Ready { NOTHING_READY, PROPS_READY, ROW_READY } ready = NOTHING_READY;
   int one_step(bool more) {   // more: another step of the same call follows
     int m = step + 1;
     if (m > cfg.nt_max) return fail(KBE_ERR_STATE, "step index would pass nt_max");
     LaunchArgs a = args();
-    int rc = props_ready ? KBE_OK : props(a, m, 0);
-    props_ready = false;
-    if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_PREDICT, st), "predictor launch");
+    int rc = ready >= PROPS_READY ? KBE_OK : props(a, m, 0);
+    if (!rc && ready < ROW_READY) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_PREDICT, st), "predictor launch");
+    ready = NOTHING_READY;
     // Corrector passes of Algorithm "prop": all n_corr of them, or (corr_tol > 0) until the
     // largest change of row m is <= corr_tol, which needs the change on the host after each
     // pass (one stream synchronisation per pass in that mode).
@@ -474,8 +475,17 @@ struct kbe_ctx {
     // in the propagators' own launch, which would be one of theirs alone.
     const bool ahead = more && reached && !kicked(m) && kbe::obs_in_pass(L.d);
     if (!rc) rc = collision_parts(a, m, ahead ? PROPS_NEXT : PROPS_NONE);
-    if (!rc) rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_EVAL, st), "collision-row launch");
-    props_ready = !rc && ahead;
+    // the predictor of a t' follows from the evaluation of that t': both in one row launch then
+    const bool fused = ahead && kbe::row_next_fused(L.d);
+    if (!rc && fused) {
+      LaunchArgs next = a;
+      next.rho_prev = a.rho_cur;
+      next.rho_cur = a.rho_prev;
+      rc = check(kbe::launch_row_next(L.d, a, next, m, st), "collision-row and predictor launch");
+    } else if (!rc) {
+      rc = check(kbe::launch_row(L.d, a, m, KBE_ROW_EVAL, st), "collision-row launch");
+    }
+    if (!rc && ahead) ready = fused ? ROW_READY : PROPS_READY;
     if (!rc) due_observables(m);
     // the kick replaces the slice's density and collision row; a step that reports ends the call
     if (!rc && (!more || !reached || kicked(m))) rc = flush_observables();
@@ -602,8 +612,12 @@ struct kbe_ctx {
     p.hfbuf = b.hf_p;
     p.commit = 0;
     if (!rc) rc = check(kbe::launch_collide(d, e, m - 1, &p, 0.0, nullptr, st), "history-sum launch");
-    if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
-    if (!rc) rc = check(kbe::launch_row(d, p, m, KBE_ROW_PREDICT, st), "predictor launch");
+    if (m > 1 && kbe::row_next_fused(d)) {
+      if (!rc) rc = check(kbe::launch_row_next(d, e, p, m - 1, st), "collision-row and predictor launch");
+    } else {
+      if (!rc) rc = check(kbe::launch_row(d, e, m - 1, KBE_ROW_EVAL, st), "collision-row launch");
+      if (!rc) rc = check(kbe::launch_row(d, p, m, KBE_ROW_PREDICT, st), "predictor launch");
+    }
     // recompute the corrector's collision row and propagators
     LaunchArgs c = p;
     c.I_cur = b.Ire_c;

@@ -14,6 +14,7 @@
 #define KBE_ROW_PREDICT 0
 #define KBE_ROW_CORRECT 1
 #define KBE_ROW_EVAL 2
+#define KBE_ROW_EVAL_NEXT 3   // EVAL of row m, then PREDICT of row m + 1
 
 namespace kbe {
 
@@ -78,6 +79,10 @@ hipError_t launch_kick(const Dims& d, const LaunchArgs& a, int m, double kc, dou
 hipError_t launch_collide(const Dims& d, const LaunchArgs& a, int m, const LaunchArgs* props, double wb,
                           const ObsStep* o, hipStream_t st);
 hipError_t launch_row(const Dims& d, const LaunchArgs& a, int m, int mode, hipStream_t st);
+// launch_row(d, a, m, KBE_ROW_EVAL, st) and launch_row(d, next, m + 1, KBE_ROW_PREDICT, st) in one, m >= 1;
+// next: I_prev and D_prev are a's I_cur and D_cur, the working rows the same
+inline bool row_next_fused(const Dims& d) { return d.nb <= 2 && d.qp == 1; }
+hipError_t launch_row_next(const Dims& d, const LaunchArgs& a, const LaunchArgs& next, int m, hipStream_t st);
 // out[0] = max of the row kernel's per-block changes at row m (one block, deterministic)
 hipError_t launch_change_max(const Dims& d, const double* chg, int m, double* out, hipStream_t st);
 hipError_t launch_obs(const Dims& d, const LaunchArgs& a, const ObsStep& o, hipStream_t st);

@@ -45,3 +45,22 @@ def test_observables_of_a_step_that_reports():
             S.step(30 - m)          # each call commits one step and reports
         assert S.current_step == m
         assert np.array_equal(S.observables()[m], ref[m])
+
+
+@pytest.mark.parametrize("nb,precision", [(1, inputs.PRECISION_FP64), (2, inputs.PRECISION_FP64),
+                                          (2, inputs.PRECISION_FP32)])
+def test_evaluation_and_predictor_in_one_launch(nb, precision):
+    # within a call a row's evaluation and the next row's predictor are one launch: across the edges
+    # of its 64-column tiles (rows 63..65, 127..129) the bits are those of the two launches
+    from paper_2505_19467_amd import kbe
+    hop = np.zeros((3, nb, nb), complex)
+    hop[0] = np.diag(np.linspace(0.5, -0.5, nb))
+    hop[1] = -(0.3 + 0.7 * np.eye(nb))
+    cfg = inputs.Config(name="tiles", nkx=5, nky=1, nb=nb, hop=hop, U=1.2, dt=0.02, nt=130, precision=precision)
+    one, many = kbe.System(cfg), kbe.System(cfg)
+    for _ in range(130):
+        one.step(1)
+    many.step(130)
+    assert np.array_equal(many.observables(), one.observables())
+    for m in (63, 64, 65, 127, 128, 129, 130):
+        assert np.array_equal(many.history_row(m).cpu().numpy(), one.history_row(m).cpu().numpy()), m
