@@ -105,8 +105,9 @@ typedef struct {
                            modulus of the change of row m (every t', k, component and orbital
                            pair, the equal-time block included) is brought to the host, and the
                            passes stop once it is <= corr_tol or n_corr passes have run. This
-                           synchronises the stream once per pass; kbe_corrector_log reports the
-                           passes taken. The adjoint needs corr_tol = 0. */
+                           synchronises the stream once per pass (the context holds 8 bytes of
+                           pinned host memory for it); kbe_corrector_log reports the passes taken.
+                           The adjoint needs corr_tol = 0. */
 } kbe_config;
 
 /* Pulse kinds. */
@@ -187,7 +188,7 @@ int kbe_create(const kbe_config* cfg, const double* hop, const kbe_pulse* pulse,
  * for kbe_create. The call allocates no device memory.
  *   - The device is the one current at the call; hip_stream must belong to it.
  *   - KBE_ERR_SHAPE if the workspace of cfg (kbe_workspace_query) exceeds
- *     KBE_NOALLOC_WORKSPACE_MAX (e.g. the 12x12, nb = 2, nt_max = 400 workload needs 86 MiB and
+ *     KBE_NOALLOC_WORKSPACE_MAX (e.g. the 12x12, nb = 2, nt_max = 400 workload needs 108 MiB and
  *     fits; the 24x24, nt_max = 1000 one needs 1.1 GiB and does not); other argument errors as
  *     for kbe_create. Nothing is launched on an error.
  *   - One such context per device at a time: the array is the context's whole state, so a
@@ -231,8 +232,9 @@ const char* kbe_last_error(const kbe_ctx* ctx);
  *   propagators(m, 0); update(m, PREDICT);
  *   K x { sigma(m); collision(m); propagators(m, 1); update(m, CORRECT) };
  *   sigma(m); collision(m); observables(m); commit(m)
- * (the corrector's collision and update are fused inside kbe_step). The observables come
- * before the commit, which applies the dipole kick on its slice.
+ * (inside kbe_step the corrector's collision and update are fused, its propagators are computed
+ * beside the collision, and a step's observables beside the next step of the same call). The
+ * observables come before the commit, which applies the dipole kick on its slice.
  * ------------------------------------------------------------------------------------- */
 
 /* Sub-buffers of the workspace (kbe_buffer). */
@@ -294,6 +296,8 @@ int kbe_stage_commit(kbe_ctx* ctx, int32_t m);
 int kbe_rebuild_aux(kbe_ctx* ctx, int32_t m);
 
 /* Per-launch timing of the history-sum kernel with HIP events on the context's stream.
+ * (The launch also carries the pass's small independent blocks: the equal-time integrals, the
+ * corrector's propagators, the observables of the step before.)
  * kbe_timing(ctx, 1) synchronises the stream, clears earlier records and creates the whole
  * event pool up front (two events per history pass of every step up to nt_max), so that no
  * event is created while work is queued; history-sum launches beyond the pool run untimed.
