@@ -207,7 +207,9 @@ int kbe_create_noalloc(const kbe_config* cfg, const double* hop, const kbe_pulse
  * whose n_corr passes all end with the row changing by more than corr_tol is committed as the
  * algorithm commits it, and the call then returns KBE_ERR_NOT_CONVERGED without taking the
  * remaining steps: kbe_current_step is that step, kbe_corrector_log holds its changes, and a
- * further kbe_step call continues from it. */
+ * further kbe_step call continues from it. A pass after which any entry of the row has changed by an
+ * infinite amount or by something that is not a number ends the call with KBE_ERR_NONFINITE; that
+ * step is not committed. */
 int kbe_step(kbe_ctx* ctx, int32_t nsteps);
 
 /* Index of the last completed step (0 after kbe_create). */

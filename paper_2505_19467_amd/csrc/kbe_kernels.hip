@@ -2649,9 +2649,12 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         const int c = sc * NBB + a * NB + b;
-        if (MODE == KBE_ROW_CORRECT && chg) {  // change against the iterate this pass started from
-          cplx dg = csub(g[b], row64[row64_idx(d, m, k, c, tp)]);
-          dmax = fmax(dmax, sqrt(dg.x * dg.x + dg.y * dg.y));
+        if (MODE == KBE_ROW_CORRECT && chg) {
+          // change against the iterate this pass started from; one that is not a number counts as
+          // infinite (the maxima over lanes, wavefronts and blocks would drop it)
+          const cplx dg = csub(g[b], row64[row64_idx(d, m, k, c, tp)]);
+          const double c2 = dg.x * dg.x + dg.y * dg.y;
+          dmax = fmax(dmax, c2 >= 0.0 ? sqrt(c2) : INFINITY);
         }
       }
       // a corrector wavefront reads only its own row of the old iterate above, but the end-point
@@ -2684,7 +2687,8 @@ __global__ __launch_bounds__(128 * NB) void k_row(Dims d, void* __restrict__ his
 
 // Largest change of the corrector's row: out[0] = max over the row kernel's n blocks; out is in host
 // memory, which saves the copy that the host would wait for.
-// One block, a fixed reduction order (max is exact, so any order gives the same value).
+// One block, a fixed reduction order (max is exact, so any order gives the same value); infinite if any
+// change is infinite or not a number, which the caller reports.
 __global__ __launch_bounds__(1024) void k_change_max(const double* __restrict__ chg, int n, double* __restrict__ out) {
   __shared__ double red[16];
   double mx = 0.0;
