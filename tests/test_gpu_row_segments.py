@@ -72,3 +72,55 @@ def test_workspace_slots_stay_within_the_allocation_free_array():
                 assert w <= limit
     n = ctypes.c_size_t()
     assert kbe._lib.kbe_adjoint_query(ctypes.byref(kbe._c_config(inputs.c4())), ctypes.byref(n)) == 0
+
+
+def _column_slots(kbe, cfg, nt):
+    """Column-sum slots of a context, from its workspace size (all other large buffers are whole rows)."""
+    Tp, C = 8 * ((nt + 8) // 8), 2 * cfg.nb ** 2
+    seg = cfg.nk * C * Tp * 16
+    slots = (nt + 63) // 64
+    return round(kbe.workspace_query(cfg, nt)[1] / seg - (1.5 + 2 + 2 + 2 + 0.5 * slots))
+
+
+@pytest.mark.parametrize("precision,tol", [(inputs.PRECISION_FP64, 1e-12), (inputs.PRECISION_FP32, 1e-5),
+                                           (inputs.PRECISION_FP32_MFMA, 1e-5)])
+@pytest.mark.parametrize("nkx,nky,nb,long", [(24, 24, 2, 240), (16, 16, 2, 520), (32, 16, 1, 1030), (11, 11, 3, 490),
+                                             (8, 8, 4, 520)])
+def test_split_against_unsplit(precision, tol, nkx, nky, nb, long):
+    """The same row in a context with several column-sum slots and in one whose longer rows leave it one
+    slot, so that its passes are not split; and both against the oracle at a few k. 24 x 24 (nb = 2,
+    FP64) splits blocks of four wavefronts, 16 x 16 blocks of eight."""
+    import torch
+    from paper_2505_19467_amd import kbe
+    m = 140
+    print(f"split against unsplit nk={nkx}x{nky} nb={nb} precision={precision}", flush=True)
+    cfg = inputs.Config(name="seg", nkx=nkx, nky=nky, nb=nb, hop=np.zeros((3, nb, nb), complex), U=1.0, dt=0.02,
+                        nt=m, n_corr=2, precision=precision)
+    assert _column_slots(kbe, cfg, m) > 1 and _column_slots(kbe, cfg, long) == 1
+    gen = torch.Generator(device="cuda").manual_seed(nkx + nb)
+    draw = lambda *s: torch.view_as_complex(torch.rand(*s, 2, generator=gen, device="cuda", dtype=torch.float64) - 0.5)  # noqa: E731
+    sig = draw(cfg.nk, 2, nb * nb, m + 1)
+    systems = [kbe.System(cfg, nt_max=m), kbe.System(cfg, nt_max=long)]
+    sampled = [0, cfg.nk // 2, cfg.nk - 1]
+    rows = []
+    for j in range(m + 1):
+        r = draw(j + 1, cfg.nk, 2, nb, nb)
+        for S in systems:
+            S.set_history_row(j, r)
+        rows.append(r[:, sampled].cpu().numpy())
+    got = []
+    for S in systems:
+        planes = S.sigma_planes()
+        planes[:, :2, :, :m + 1] = sig
+        planes[:, 2, :, :m + 1] = sig[:, 1] - sig[:, 0]
+        S.rebuild_aux(m)
+        S.stage_collision(m)
+        got.append(S.collision_row(m))
+        S.close()
+    ref = O.collision_row(cfg.replace(nkx=len(sampled), nky=1), m, rows,
+                          np.ascontiguousarray(sig[sampled].permute(3, 0, 1, 2).reshape(m + 1, len(sampled), 2, nb, nb).cpu().numpy()))
+    scale = np.abs(ref).max()
+    split = (got[0] - got[1]).abs().max().item() / scale
+    err = [np.abs(g[:, sampled].cpu().numpy() - ref).max() / scale for g in got]
+    print(f"  split against unsplit {split:.2e}; against the oracle {err[0]:.2e} split, {err[1]:.2e} unsplit", flush=True)
+    assert split < tol and max(err) < tol
