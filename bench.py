@@ -34,26 +34,45 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 # scaled by what the same counters read for a plain 1 GiB device copy (x2.000 and x1.000), averaged
 # over the launches of the timed window (the last K steps of the trajectory), keyed by (workload,
 # nt, timed steps K); summary and commands in profiles/k_hist_pair_c2_sq24_nb2.md. Valid only for
-# the code it was measured on (SHA-1 of the k_hist_pair template and kbe_device.hpp, comments
-# removed); reported as null once that code changes, or for a window that was not measured.
+# the code it was measured on (SHA-1 of MEASURED_CODE below, comments removed); reported as null once
+# that code changes, or for a window that was not measured.
 MEASURED_TRAFFIC = {"bytes_per_launch": {("c2", 1000, 20): 3.72185e10, ("c2", 1000, 1000): 1.27624e10},
-                    "source_sha1": "d03217ddbe081d1c2c69525e01d86ca8d4eb4be0"}
+                    "source_sha1": "3ad8fba0b1cbb58120d4e57c506abf7bbffccc05"}
 
 
-def _kernel_source_sha1():
-    """SHA-1 of the FP64 history-sum kernel's code (the k_hist_pair template) and of the shared
-    device header, comments and blank lines removed: code changes of that kernel only."""
+# What a history-sum launch reads and writes is decided by, as (file, from, up to; None: the file):
+MEASURED_CODE = [
+    ("kbe_device.hpp", None, None),   # layout, row segments, shared device code
+    ("kbe_kernels.hpp", None, None),
+    # the small blocks that ride in the launch: observables, propagators, equal-time integral
+    ("kbe_kernels.hip", "// ------------------------------------------------------------------ observables",
+     "// ------------------------------------------------------------------ self-energy"),
+    ("kbe_kernels.hip", "// ------------------------------------------------------------------ equal-time collision",
+     "// ------------------------------------------------------------------ history sums (hot loop)"),
+    ("kbe_kernels.hip", "template <int NB, int WAVES>", "// ------------------------------------------------------------------"),
+    # wavefronts per block and rows per block, and the launch
+    ("kbe_kernels.hip", "static int hist_waves(", "template <int NB>"),
+    ("kbe_kernels.hip", "static hipError_t collide(", "static hipError_t row("),
+    # column-sum slots; what rides in which pass of a step
+    ("kbe_api.hip", "int make_layout(", "kbe::QuadW quad_corrections("),
+    ("kbe_api.hip", "int collision_parts(", "int kick_slice()"),
+    ("kbe_api.hip", "int one_step(bool more)", "template <class T>"),
+]
+
+
+def _kernel_source_sha1(csrc=os.path.join(ROOT, "paper_2505_19467_amd", "csrc")):
+    """SHA-1 of the code that decides the FP64 history-sum launch's traffic (MEASURED_CODE), comments and
+    blank lines removed."""
     import hashlib
     import re
-    d = os.path.join(ROOT, "paper_2505_19467_amd", "csrc")
-
-    def code(text):
+    lines = []
+    for name, start, end in MEASURED_CODE:
+        text = open(os.path.join(csrc, name)).read()
+        if start:
+            a = text.index(start)
+            text = text[a:text.index(end, a + len(start))]
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
-        return [ln.split("//")[0].rstrip() for ln in text.splitlines()]
-    k = open(os.path.join(d, "kbe_kernels.hip")).read()
-    a = k.index("void k_hist_pair(")
-    b = k.index("// ------------------------------------------------------------------", a)
-    lines = code(k[a:b]) + code(open(os.path.join(d, "kbe_device.hpp")).read())
+        lines += [ln.split("//")[0].rstrip() for ln in text.splitlines()]
     return hashlib.sha1("\n".join(ln for ln in lines if ln).encode()).hexdigest()
 
 
