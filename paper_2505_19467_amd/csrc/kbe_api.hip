@@ -13,6 +13,7 @@
 #include "kbe.h"
 #include "kbe_adjoint.hpp"
 #include "kbe_kernels.hpp"
+#include "kbe_pinned.hpp"
 
 using kbe::cplx;
 using kbe::Dims;
@@ -231,36 +232,8 @@ size_t adj_layout(const Layout& L, size_t* off) {
 
 }  // namespace
 
-// Pinned host words for the row changes of contexts with a tolerance. Pinning one takes 0.2 ms, as
-// long as a short run, so up to 8 words that contexts have given back are kept for the next ones (a
-// context gives its word back when its stream has completed).
 namespace {
-std::mutex pinned_mu;
-std::vector<double*> pinned_free;
-constexpr size_t PINNED_KEPT = 8;
-
-hipError_t take_pinned_word(double** p) {
-  {
-    std::lock_guard<std::mutex> lock(pinned_mu);
-    if (!pinned_free.empty()) {
-      *p = pinned_free.back();
-      pinned_free.pop_back();
-      return hipSuccess;
-    }
-  }
-  return hipHostMalloc((void**)p, sizeof(double), hipHostMallocMapped | hipHostMallocPortable);
-}
-void return_pinned_word(double* p) {
-  if (!p) return;
-  {
-    std::lock_guard<std::mutex> lock(pinned_mu);
-    if (pinned_free.size() < PINNED_KEPT) {
-      pinned_free.push_back(p);
-      return;
-    }
-  }
-  (void)hipHostFree(p);
-}
+kbe::PinnedWords pinned_words;
 }  // namespace
 
 struct kbe_ctx {
@@ -294,7 +267,7 @@ struct kbe_ctx {
   // corr_tol > 0: the row change of the latest pass, in pinned host memory that the GPU writes
   double* change_host = nullptr;
   double* change_dev = nullptr;
-  ~kbe_ctx() { return_pinned_word(change_host); }
+  ~kbe_ctx() { pinned_words.give_back(change_host); }
   int noalloc_dev = -1;  // device whose static workspace this context holds (kbe_create_noalloc)
 
   template <class T>
@@ -697,7 +670,7 @@ int create_context(const kbe_config* cfg, const double* hop, const kbe_pulse* pu
   c->passes.assign((size_t)cfg->nt_max + 1, 0);
   c->changes.assign((size_t)(cfg->nt_max + 1) * (cfg->n_corr > 0 ? cfg->n_corr : 1), -1.0);
   if (cfg->corr_tol > 0.0) {
-    rc = c->check(take_pinned_word(&c->change_host), "pinned host memory");
+    rc = c->check(pinned_words.take(&c->change_host), "pinned host memory");
     if (!rc) rc = c->check(hipHostGetDevicePointer((void**)&c->change_dev, c->change_host, 0), "pinned host memory");
     if (rc) {
       delete c;
