@@ -15,7 +15,7 @@
 //                 self-energy adjoint row and the adjoint of the current row
 //   k_adj_sigma   adjoint of eq. (2BSE) through the k <-> R transforms (Wirtinger products)
 //   k_adj_update  adjoint of the predictor/corrector update of G(t_m, .) and rho_m
-//   k_adj_props   adjoint of V, Vh, Phi: Frechet derivative of the augmented exponential
+//   k_adj_props1/2 adjoint of V, Vh, Phi: Frechet derivative of the exponential (nb = 1, 2)
 //   k_adj_hf      adjoint of the mean field and of the pulse; parameter gradients
 //   k_adj_seed    adjoint of the final-time observable
 //   k_adj_rho     rho_m = -i G^<(t_m, t_m) read back from the stored history diagonal
@@ -1002,50 +1002,42 @@ __global__ __launch_bounds__(64) void k_adj_props2(Dims d, const cplx* __restric
     if (c == 0) kpart[(int64_t)k * (NB + 1) + NB] = dA;
   }
 }
-// nb = 1 (and the general form): M = [[-i hbar dt, dt 1], [0, 0]];  V = exp(M)_tl,  Phi = -i exp(M)_tr,
+// nb = 1: M = [[-i hbar dt, dt], [0, 0]];  V = exp(M)_tl,  Phi = -i exp(M)_tr,
 // Vh = exp(M/2)_tl.
 // For E = exp(X) the adjoint is Xbar = L(X^dag, Ebar), the Frechet derivative of exp at X^dag
-// in the direction Ebar, read off the top-right block of exp([[X^dag, Ebar], [0, X^dag]]).
+// in the direction Ebar, read off the top-right block of exp([[X^dag, Ebar], [0, X^dag]]) (4 x 4).
 // Ebar = [[Vbar, i Phibar], [0, 0]] for exp(M), [[Vhbar, 0], [0, 0]] for exp(M/2);
 // hbarbar = i dt (Mbar)_tl. One wavefront per k.
-template <int NB>
-__global__ __launch_bounds__(256) void k_adj_props(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ hf,
-                                                   const cplx* __restrict__ pbar, double Ax, double Ay, double polx,
-                                                   double poly, double dt, double* __restrict__ kpart) {
-  constexpr int NBB = NB * NB, N2 = 2 * NB, B2 = 2 * N2, BB = B2 * B2;
-  static_assert(BB <= 64, "adjoint propagators support nb <= 2");
+__global__ __launch_bounds__(256) void k_adj_props1(Dims d, const cplx* __restrict__ hop, const cplx* __restrict__ hf,
+                                                    const cplx* __restrict__ pbar, double Ax, double Ay, double polx,
+                                                    double poly, double dt, double* __restrict__ kpart) {
+  constexpr int N2 = 2, B2 = 2 * N2, BB = B2 * B2;   // sizes of M and of the block matrix
   __shared__ cplx sX[4][BB], sE[4][BB];
-  __shared__ cplx hb[4][NBB];
+  __shared__ cplx hb[4];
   int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int k = blockIdx.x * 4 + wv;
   bool kval = k < d.nk;
   int r = lane / B2, c = lane - (lane / B2) * B2;
   bool act = kval && lane < BB;
-  cplx h[NBB];
+  cplx h = czero();
   if (kval) {
-    bloch_h0<NB>(hop, d.nkx, d.nky, k, Ax, Ay, h);
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) h[e] = cadd(h[e], hf[e]);
+    bloch_h0<1>(hop, d.nkx, d.nky, k, Ax, Ay, &h);
+    h = cadd(h, hf[0]);
   }
-  const cplx* pb = pbar + (int64_t)(kval ? k : 0) * 3 * NBB;
-  // M (N2 x N2) element (i, j)
+  const cplx* pb = pbar + (int64_t)(kval ? k : 0) * 3;   // Vbar, Vhbar, Phibar
+  // M element (i, j)
   auto Mel = [&](int i, int j, double sc) -> cplx {
-    if (i < NB && j < NB) return cscal(cmuli(h[i * NB + j]), -dt * sc);
-    if (i < NB && j == i + NB) return cmk(dt * sc, 0.0);
+    if (i == 0) return j == 0 ? cscal(cmuli(h), -dt * sc) : cmk(dt * sc, 0.0);
     return czero();
   };
-  cplx mbar = czero();  // (Mbar)_tl element of lane (r, c) when r, c < NB
+  cplx mbar = czero();  // (Mbar)_tl, in the lane of row 0, column N2
   for (int pass = 0; pass < 2; ++pass) {
     double sc = pass == 0 ? 1.0 : 0.5;
-    // Ebar (N2 x N2)
+    // Ebar element (i, j)
     auto Ebar = [&](int i, int j) -> cplx {
-      if (pass == 0) {
-        if (i < NB && j < NB) return pb[i * NB + j];
-        if (i < NB && j >= NB) return cmuli(pb[2 * NBB + i * NB + (j - NB)]);
-        return czero();
-      }
-      if (i < NB && j < NB) return pb[NBB + i * NB + j];
-      return czero();
+      if (i != 0) return czero();
+      if (pass == 0) return j == 0 ? pb[0] : cmuli(pb[2]);
+      return j == 0 ? pb[1] : czero();
     };
     // block matrix B = [[M^dag, Ebar/nE], [0, M^dag]] with the direction normalised
     double ne = 0.0;
@@ -1072,41 +1064,37 @@ __global__ __launch_bounds__(256) void k_adj_props(Dims d, const cplx* __restric
       if (lane < BB)
 #pragma unroll
         for (int l = 0; l < B2; ++l) cmac(acc, sX[wv][r * B2 + l], sE[wv][l * B2 + c]);
-      wave_sync();  // every LDS array here is per wavefront
+      wave_sync();
       e = cadd(id, cscal(acc, 1.0 / n));
       if (lane < BB) sE[wv][lane] = e;
-      wave_sync();  // every LDS array here is per wavefront
+      wave_sync();
     }
     for (int q = 0; q < s; ++q) {
       cplx acc = czero();
       if (lane < BB)
 #pragma unroll
         for (int l = 0; l < B2; ++l) cmac(acc, sE[wv][r * B2 + l], sE[wv][l * B2 + c]);
-      wave_sync();  // every LDS array here is per wavefront
+      wave_sync();
       e = acc;
       if (lane < BB) sE[wv][lane] = e;
-      wave_sync();  // every LDS array here is per wavefront
+      wave_sync();
     }
-    // top-right block, top-left (NB x NB) sub-block of L: (r, c - N2) with r, c - N2 < NB
-    if (act && r < NB && c >= N2 && c - N2 < NB) mbar = cadd(mbar, cscal(e, ne * sc));
+    // (0, 0) of the top-right block
+    if (act && r == 0 && c == N2) mbar = cadd(mbar, cscal(e, ne * sc));
   }
   // hbarbar = i dt Mbar_tl
-  if (act && r < NB && c >= N2 && c - N2 < NB) hb[wv][r * NB + (c - N2)] = cscal(cmuli(mbar), dt);
-  wave_sync();  // every LDS array here is per wavefront
+  if (act && r == 0 && c == N2) hb[wv] = cscal(cmuli(mbar), dt);
+  wave_sync();
   if (kval && lane == 0) {
-    // dL/dhf_aa += Re hbarbar_aa ;  dL/dA += Re sum conj(hbarbar) dh0/dA, dh0/dA = -(pol . v)
-    cplx vx[NBB], vy[NBB];
-    bloch_vel<NB>(hop, d.nkx, d.nky, k, Ax, Ay, 0, vx);
-    bloch_vel<NB>(hop, d.nkx, d.nky, k, Ax, Ay, 1, vy);
+    // dL/dhf += Re hbarbar ;  dL/dA += Re conj(hbarbar) dh0/dA, dh0/dA = -(pol . v)
+    cplx vx, vy;
+    bloch_vel<1>(hop, d.nkx, d.nky, k, Ax, Ay, 0, &vx);
+    bloch_vel<1>(hop, d.nkx, d.nky, k, Ax, Ay, 1, &vy);
     double dA = 0.0;
-#pragma unroll
-    for (int e = 0; e < NBB; ++e) {
-      cplx dh = cneg(cadd(cscal(vx[e], polx), cscal(vy[e], poly)));
-      dA += hb[wv][e].x * dh.x + hb[wv][e].y * dh.y;
-    }
-#pragma unroll
-    for (int a = 0; a < NB; ++a) kpart[(int64_t)k * (NB + 1) + a] = hb[wv][a * NB + a].x;
-    kpart[(int64_t)k * (NB + 1) + NB] = dA;
+    cplx dh = cneg(cadd(cscal(vx, polx), cscal(vy, poly)));
+    dA += hb[wv].x * dh.x + hb[wv].y * dh.y;
+    kpart[2 * (int64_t)k] = hb[wv].x;
+    kpart[2 * (int64_t)k + 1] = dA;
   }
 }
 
@@ -1334,7 +1322,7 @@ struct AdjLaunch {
       hipLaunchKernelGGL(k_adj_props2, dim3((2 * d.nk + 63) / 64), dim3(64), 0, st, d, (const cplx*)a.hop, hf,
                          (const cplx*)b.pbar, a.Ax, a.Ay, a.polx, a.poly, a.dt, b.kpart);
     else
-      hipLaunchKernelGGL(k_adj_props<NB>, dim3((d.nk + 3) / 4), dim3(256), 0, st, d, (const cplx*)a.hop, hf,
+      hipLaunchKernelGGL(k_adj_props1, dim3((d.nk + 3) / 4), dim3(256), 0, st, d, (const cplx*)a.hop, hf,
                          (const cplx*)b.pbar, a.Ax, a.Ay, a.polx, a.poly, a.dt, b.kpart);
     return hipGetLastError();
   }

@@ -23,7 +23,7 @@ namespace {
 
 enum {
   B_SIGMA = 0, B_IA, B_IB, B_RHOA, B_RHOB, B_DA, B_DB, B_PROP, B_COL0, B_DIAG, B_COLSUM, B_ROWPART,
-  B_HF, B_HOP, B_EIGW, B_EIGU, B_MU, B_ROW64, B_CHG, B_CHGMAX, B_GR, B_COUNT
+  B_HF, B_HOP, B_EIGW, B_EIGU, B_MU, B_ROW64, B_CHG, B_GR, B_COUNT
 };
 
 struct Layout {
@@ -100,9 +100,9 @@ int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   sz[B_EIGU] = nk * d.nbb * cz;
   sz[B_MU] = sizeof(double);
   sz[B_ROW64] = (size_t)d.rring * nk * d.C * d.Tp * cz;
-  // corrector change per (k, t') and its maximum, only when the corrector stops on a tolerance
+  // the row kernel's changes, only when the corrector stops on a tolerance: one per block of 64 t' of a
+  // k (the size is that of one per (k, t'))
   sz[B_CHG] = c->corr_tol > 0.0 ? nk * d.Tp * sizeof(double) : 0;
-  sz[B_CHGMAX] = c->corr_tol > 0.0 ? sizeof(double) : 0;
   // interband self-energy: real-space lines of the current row, [t_j][comp][ab][R]
   sz[B_GR] = c->interaction == KBE_INT_INTERBAND ? (size_t)d.Tp * 2 * d.nbb * nk * cz : 0;
   // Column-sum slots, one per row segment: up to 24 (the most that blocks of 16 rows want on the
@@ -524,8 +524,7 @@ struct kbe_ctx {
     for (int i = A_IBAR0; i <= A_IBAR1 && !rc; ++i) rc = zero_adj(i, row);
     if (d.nb == 2)
       for (int i = A_LAMD; i <= A_LAMC && !rc; ++i) rc = zero_adj(i, row);
-    // A_RHOP too: the recomputed predictor's mean field reads it with weight 0 before it is written
-    for (int i = A_DBAR0; i <= A_RHOP && !rc; ++i) rc = zero_adj(i, mat);
+    for (int i = A_DBAR0; i <= A_RHOBARP && !rc; ++i) rc = zero_adj(i, mat);
     if (!rc) rc = zero_adj(A_THETA, 3 * sizeof(double));
     if (rc) return rc;
     LaunchArgs a = args();

@@ -326,27 +326,9 @@ __device__ void jacobi_eigh(cplx* A, double* w, cplx* V) {
 }
 
 // ------------------------------------------------------------------ block reductions
-template <int N>
-__device__ __forceinline__ void block_sum_cplx(cplx* v, cplx* lds /* [N][256] */) {
-  int t = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < N; ++i) lds[i * 256 + t] = v[i];
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) lds[i * 256 + t] = cadd(lds[i * 256 + t], lds[i * 256 + t + s]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = lds[i * 256];
-  __syncthreads();
-}
-
 // Block sums of N values of the first 256 threads into out[N], with two block barriers: the values
 // of threads t, t + 64, t + 128, t + 192 are added pairwise by one wavefront per value, then across
-// its lanes (the order of block_sum_cplx). Every thread of the block calls it.
+// its lanes (the order of a halving tree over the 256). Every thread of the block calls it.
 template <int N>
 __device__ __forceinline__ void block_sum_once(const double* v, double* lds /* [N][256] */, double* out) {
   const int t = threadIdx.x, lane = t & 63;

@@ -1111,7 +1111,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_hist_pair(Dims d, const cplx* __
     for (int c = 0; c < C; ++c) acc[h][c] = czero();
   cplx* rp = const_cast<cplx*>(rowpart_slot(d, rowpart, k, sp));
   for (int cb = r0; cb < r1; cb += 64) {
-    const int rb = cb + wv;   // the wavefront's rows of the chunk: rb, rb + 4, ..., rb + 60
+    const int rb = cb + wv;   // the wavefront's rows of the chunk: rb, rb + RSTEP, ... (RPC of them)
     const int cslot = ((cb - r0) >> 6) % (ROWS_ST / 64);   // chunk's place in the staging
     cplx* st = &stg[0][64 * cslot];                                // st[e * ROWS_ST + (row - cb)]
     for (int i = 0; i < RPC;) {
@@ -1190,7 +1190,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_hist_pair(Dims d, const cplx* __
       // rows of the pair's first 64 lie above every column of its second strip: one strip's
       // work; in its next 64 rows every column of the first strip lies below the row: masks for
       // the second strip only
-      // (an iteration's rows jb, jb + 4, ..., jb + 4 (RR - 1) lie in one 64-row chunk)
+      // (an iteration's rows jb, jb + RSTEP, ..., jb + RSTEP (RR - 1) lie in one 64-row chunk)
       if (jb >= 128 * sp + 128 && jb + RSTEP * (R - 1) < r1) {
         iteration(IntTag<0>{}, IntTag<2>{}, IntTag<R>{});
         i += R;
@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_hist_pair(Dims d, const cplx* __
         i += R;
       }
     }
-    // every fourth chunk (and the last): the staged rows of all four wavefronts leave as one
+    // every fourth chunk (and the last): the staged rows of all the wavefronts leave as one
     // contiguous run of up to 256 rows per component (4 KB), streaming stores
     if (cslot == ROWS_ST / 64 - 1 || cb + 64 >= r1) {
       __syncthreads();
