@@ -2788,14 +2788,22 @@ static hipError_t allow_lds(const void* kern, size_t bytes) {
 // Blocks of 64 t' per k of the row kernel: t' < m in the evaluation mode, t' <= m otherwise.
 static int row_tiles(int m, int mode) { return mode == KBE_ROW_EVAL ? (m + 63) / 64 : m / 64 + 1; }
 
-// Wavefronts per block of the FP64 nb <= 2 kernel: at nb = 2 eight where one block per strip pair gives
-// less than two rounds of the 512 four-wavefront blocks that the chip holds (its registers allow two
-// wavefronts per SIMD, so it holds 256 of eight): the same rows in flight with half the blocks to start
-// and to combine. 144 points, m = 300 / 400, best split of either 156 -> 154, 272 -> 265 us; 61 points,
-// m = 400 130 -> 120 us; but 576 points, m = 300 592 -> 608 us, and one band (126 registers, four
-// wavefronts per SIMD), 61 points, m = 200 12.1 -> 13.2 us.
+// Wavefronts per block of the FP64 nb <= 2 kernel: at nb = 2 eight where that is less time in rounds of
+// the chip (its registers allow two wavefronts per SIMD, so it holds 512 blocks of four or 256 of eight,
+// which take half as long each): the same rows in flight with half the blocks to start and to combine.
+// With one strip pair (m <= 128) the blocks are equal: eight wins up to 256 points and, from 64 rows on
+// (below, the small blocks in front of the pass weigh more), for the last half-empty round of 513..768.
+// Four -> eight: 230 points, m = 100 58 -> 47 us; 300 points, m = 128 94 -> 100; 513 points, m = 100 118 -> 111,
+// m = 32 37 -> 43; 784 points, m = 16 / 100 33 -> 39, 144 -> 155; 961 points, m = 5 26 -> 36 us. With two pairs
+// up to 256 points (256 points, m = 200 146 -> 135 us; 300 points 168 -> 177), with more while the pairs give
+// less than two rounds of four-wavefront blocks (300 points, m = 300 353 -> 335 us; 144 points, m = 400
+// 272 -> 265 us; but 576 points, m = 300 592 -> 608 us). One band (126 registers, four wavefronts per SIMD):
+// 61 points, m = 200 12.1 -> 13.2 us.
 static int hist_waves(const Dims& d, int m) {
-  return d.nb == 2 && !d.fp32 && d.nk * ((m + 127) / 128) < 1024 ? 8 : 4;
+  if (d.nb != 2 || d.fp32) return 4;
+  const int pairs = (m + 127) / 128;
+  if (pairs == 1) return d.nk <= 256 || (d.nk > 512 && d.nk <= 768 && m >= 64) ? 8 : 4;
+  return pairs == 2 ? (d.nk <= 256 ? 8 : 4) : (d.nk * pairs < 1024 ? 8 : 4);
 }
 // Rows per block of a history pass at row m, as a power of two (30: every strip is one block).
 // One block per strip leaves a small N_k with fewer blocks than the chip holds at a time (512: two per
@@ -2808,6 +2816,10 @@ static int hist_waves(const Dims& d, int m) {
 // this rule: 16 points, m = 128 / 200 48 -> 13, 84 -> 19 us; 61 points, m = 200 / 400 93 -> 38, 230 -> 120 us;
 // 144 points, m = 128 / 200 / 400 66 -> 48, 102 -> 79, 287 -> 265 us; 1024 points 2.76 ms unsplit against
 // 2.83 ms in blocks of 256 rows at m = 500.
+// Up to one and a half strips the unsplit blocks are about equal and a split has no long ones to level: where
+// the last round of unsplit blocks is more than three quarters full it is taken only if it shortens the
+// rounds (two segments -> unsplit: 449 points, m = 128 124 -> 113 us; 401 points, m = 32 31 -> 26 us; 961 points,
+// FP32, m = 20 42 -> 35 us; but 300 points, FP32, m = 20 18 -> 20 us; nb = 4, FP32, 400 points, m = 20 62 -> 74 us).
 static int hist_lgseg(const Dims& d, int m) {
   if (d.cseg == 1) return 30;
   const int W = 64 * d.spb;
@@ -2819,7 +2831,13 @@ static int hist_lgseg(const Dims& d, int m) {
   int lg = d.mfma ? 6 : (d.nb == 4 && !d.fp32 ? 5 : 4);
   while ((2 << lg) <= share && (1 << lg) < m) ++lg;
   while (hist_nseg(m, lg) > d.cseg) ++lg;
-  return (1 << lg) < m ? lg : 30;
+  if ((1 << lg) >= m) return 30;
+  if (d.nb <= 2 && 2 * m <= 3 * W) {
+    const int held = d.nb == 1 ? 1024 : slots;   // blocks the chip holds
+    const int n = hist_nseg(m, lg), rounds = (d.nk + held - 1) / held;
+    if (4 * (d.nk - (rounds - 1) * held) > 3 * held && (d.nk * n + held - 1) / held >= n * rounds) return 30;
+  }
+  return lg;
 }
 // Blocks per k of a history pass whose strips have W columns.
 static int hist_tasks(int W, int m, int lgL) {

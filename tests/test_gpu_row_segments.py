@@ -82,25 +82,16 @@ def _column_slots(kbe, cfg, nt):
     return round(kbe.workspace_query(cfg, nt)[1] / seg - (1.5 + 2 + 2 + 2 + 0.5 * slots))
 
 
-@pytest.mark.parametrize("precision,tol", [(inputs.PRECISION_FP64, 1e-12), (inputs.PRECISION_FP32, 1e-5),
-                                           (inputs.PRECISION_FP32_MFMA, 1e-5)])
-@pytest.mark.parametrize("nkx,nky,nb,long", [(24, 24, 2, 240), (16, 16, 2, 520), (32, 16, 1, 1030), (11, 11, 3, 490),
-                                             (8, 8, 4, 520)])
-def test_split_against_unsplit(precision, tol, nkx, nky, nb, long):
-    """The same row in a context with several column-sum slots and in one whose longer rows leave it one
-    slot, so that its passes are not split; and both against the oracle at a few k. 24 x 24 (nb = 2,
-    FP64) splits blocks of four wavefronts, 16 x 16 blocks of eight."""
+def _collision_rows(cfg, lengths):
+    """The collision row of t_nt from random rows, in contexts of the given lengths: errors against the oracle
+    at a few k, and the largest difference between the first context and the last, by the largest entry."""
     import torch
     from paper_2505_19467_amd import kbe
-    m = 140
-    print(f"split against unsplit nk={nkx}x{nky} nb={nb} precision={precision}", flush=True)
-    cfg = inputs.Config(name="seg", nkx=nkx, nky=nky, nb=nb, hop=np.zeros((3, nb, nb), complex), U=1.0, dt=0.02,
-                        nt=m, n_corr=2, precision=precision)
-    assert _column_slots(kbe, cfg, m) > 1 and _column_slots(kbe, cfg, long) == 1
-    gen = torch.Generator(device="cuda").manual_seed(nkx + nb)
+    m, nb = cfg.nt, cfg.nb
+    gen = torch.Generator(device="cuda").manual_seed(cfg.nk + nb)
     draw = lambda *s: torch.view_as_complex(torch.rand(*s, 2, generator=gen, device="cuda", dtype=torch.float64) - 0.5)  # noqa: E731
     sig = draw(cfg.nk, 2, nb * nb, m + 1)
-    systems = [kbe.System(cfg, nt_max=m), kbe.System(cfg, nt_max=long)]
+    systems = [kbe.System(cfg, nt_max=n) for n in lengths]
     sampled = [0, cfg.nk // 2, cfg.nk - 1]
     rows = []
     for j in range(m + 1):
@@ -120,7 +111,40 @@ def test_split_against_unsplit(precision, tol, nkx, nky, nb, long):
     ref = O.collision_row(cfg.replace(nkx=len(sampled), nky=1), m, rows,
                           np.ascontiguousarray(sig[sampled].permute(3, 0, 1, 2).reshape(m + 1, len(sampled), 2, nb, nb).cpu().numpy()))
     scale = np.abs(ref).max()
-    split = (got[0] - got[1]).abs().max().item() / scale
-    err = [np.abs(g[:, sampled].cpu().numpy() - ref).max() / scale for g in got]
+    return ([np.abs(g[:, sampled].cpu().numpy() - ref).max() / scale for g in got],
+            (got[0] - got[-1]).abs().max().item() / scale)
+
+
+def _config(nkx, nky, nb, m, precision):
+    return inputs.Config(name="seg", nkx=nkx, nky=nky, nb=nb, hop=np.zeros((3, nb, nb), complex), U=1.0, dt=0.02,
+                         nt=m, n_corr=2, precision=precision)
+
+
+@pytest.mark.parametrize("precision,tol", [(inputs.PRECISION_FP64, 1e-12), (inputs.PRECISION_FP32, 1e-5),
+                                           (inputs.PRECISION_FP32_MFMA, 1e-5)])
+@pytest.mark.parametrize("nkx,nky,nb,long", [(24, 24, 2, 240), (12, 12, 2, 920), (32, 16, 1, 1030), (11, 11, 3, 490),
+                                             (8, 8, 4, 520)])
+def test_split_against_unsplit(precision, tol, nkx, nky, nb, long):
+    """The same row in a context with several column-sum slots and in one whose longer rows leave it one
+    slot, so that its passes are not split; and both against the oracle at a few k. 24 x 24 (nb = 2,
+    FP64) splits blocks of four wavefronts, 12 x 12 blocks of eight."""
+    from paper_2505_19467_amd import kbe
+    print(f"split against unsplit nk={nkx}x{nky} nb={nb} precision={precision}", flush=True)
+    cfg = _config(nkx, nky, nb, 140, precision)
+    assert _column_slots(kbe, cfg, 140) > 1 and _column_slots(kbe, cfg, long) == 1
+    err, split = _collision_rows(cfg, (140, long))
     print(f"  split against unsplit {split:.2e}; against the oracle {err[0]:.2e} split, {err[1]:.2e} unsplit", flush=True)
     assert split < tol and max(err) < tol
+
+
+@pytest.mark.parametrize("nk,nb,precision,m", [(256, 2, inputs.PRECISION_FP64, 128), (257, 2, inputs.PRECISION_FP64, 129),
+                                               (385, 2, inputs.PRECISION_FP64, 192), (449, 2, inputs.PRECISION_FP64, 193),
+                                               (513, 2, inputs.PRECISION_FP64, 63), (513, 2, inputs.PRECISION_FP64, 64),
+                                               (768, 2, inputs.PRECISION_FP64, 128), (769, 2, inputs.PRECISION_FP64, 64),
+                                               (449, 2, inputs.PRECISION_FP32, 20), (961, 1, inputs.PRECISION_FP64, 20)])
+def test_lines_of_the_block_rule(nk, nb, precision, m):
+    """Points and rows on either side of the lines between four and eight wavefronts, split and unsplit."""
+    print(f"block rule nk={nk} nb={nb} precision={precision} m={m}", flush=True)
+    err, _ = _collision_rows(_config(nk, 1, nb, m, precision), (m,))
+    print(f"  relative error {err[0]:.2e}", flush=True)
+    assert err[0] < (1e-12 if precision == inputs.PRECISION_FP64 else 1e-5)
