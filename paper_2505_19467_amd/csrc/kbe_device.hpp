@@ -512,8 +512,9 @@ struct FastDiv {
 // scratch, then the n2-point transforms over p2 back into x; each output costs n1 + n2
 // multiply-adds instead of n. Horner chains in registers (8 outputs per item), roots from the
 // LDS table tw (n entries, fill_roots). Bound by the latency of the chains and of their LDS reads
-// (unrolled, so that a chain's next reads are in flight). n >= 2.
+// (unrolled by U, so that a chain's next reads are in flight). n >= 2.
 // Every stage ends with a block barrier; the caller synchronises before the first.
+template <int U>
 __device__ __forceinline__ void axis_dft(cplx* __restrict__ x0, cplx* __restrict__ x1, cplx* __restrict__ t0,
                                          cplx* __restrict__ t1, int n, int n1, int nlines, int line_mul, int stride,
                                          const cplx* __restrict__ tw, int sgn, double scale) {
@@ -567,7 +568,7 @@ __device__ __forceinline__ void axis_dft(cplx* __restrict__ x0, cplx* __restrict
         z[r] = root(tw, (q1 < n1 ? q1 : 0) * n2, sgn);
         acc[r] = czero();
       }
-#pragma unroll 4
+#pragma unroll U
       for (int p1 = n1 - 1; p1 >= 0; --p1) {
         cplx v = x[(p1 * n2 + p2) * stride];
 #pragma unroll
@@ -601,7 +602,7 @@ __device__ __forceinline__ void axis_dft(cplx* __restrict__ x0, cplx* __restrict
         z[r] = root(tw, (q2 < n2 ? q2 : 0) * n1, sgn);
         acc[r] = czero();
       }
-#pragma unroll 4
+#pragma unroll U
       for (int p2 = n2 - 1; p2 >= 0; --p2) {
         cplx v = t[p2 * stride];
 #pragma unroll
@@ -750,6 +751,7 @@ __device__ __forceinline__ void axis_fft_pow2(cplx* __restrict__ x0, cplx* __res
 __host__ __device__ __forceinline__ bool pow2_chain(int nx, int ny) { return ny == 1 && nx >= 128 && (nx & (nx - 1)) == 0; }
 // Index transform of an nx x ny grid (k = ix * ny + iy) for two arrays in place:
 //   x(R) <- scale * sum_k e^{sgn 2 pi i (ix Rx / nx + iy Ry / ny)} x(k); y lines, then x lines.
+template <int U = 4>
 __device__ __forceinline__ void grid_dft(const Dims& d, cplx* x0, cplx* x1, cplx* t0, cplx* t1, const cplx* twx,
                                          const cplx* twy, int sgn, double scale) {
   const int nx = d.nkx, ny = d.nky;
@@ -757,8 +759,8 @@ __device__ __forceinline__ void grid_dft(const Dims& d, cplx* x0, cplx* x1, cplx
     axis_fft_pow2(x0, x1, nx, twx, sgn, scale);
     return;
   }
-  if (ny > 1) axis_dft(x0, x1, t0, t1, ny, d.fy, nx, ny, 1, twy, sgn, 1.0);
-  axis_dft(x0, x1, t0, t1, nx, d.fx, ny, 1, ny, twx, sgn, scale);
+  if (ny > 1) axis_dft<U>(x0, x1, t0, t1, ny, d.fy, nx, ny, 1, twy, sgn, 1.0);
+  axis_dft<U>(x0, x1, t0, t1, nx, d.fx, ny, 1, ny, twx, sgn, scale);
 }
 // grid_dft for grid sizes fixed at compile time (NY = 1: a chain, only the x lines)
 template <int NX, int NY, int T = 256>

@@ -521,7 +521,11 @@ constexpr int sigma_threads() {
   if (NY > 1 && 2 * NX * (NY / fft_split_ct(NY)) > items) items = 2 * NX * (NY / fft_split_ct(NY));
   return items > 256 ? (items + 63) / 64 * 64 : 256;
 }
-template <int NB, int NX, int NY>
+// U (run-time grids): terms of a chain whose LDS reads are in flight, 4 or 2. Four take 116 registers (four
+// wavefronts per SIMD), two take 90 (five): the launch takes two where that saves it a round of the chip
+// (1025..1280 blocks of 256 threads and so on: 9 x 7, m = 280 17.2 -> 12.8 us, 128 points 13.8 -> 11.1), else
+// four (64 points, m = 255 / 400 12.1 -> 11.5, 22.2 -> 20.3 us).
+template <int NB, int NX, int NY, int U = 4>
 __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ sig,
                                                int m, double UU, int corr) {
   constexpr int NBB = NB * NB;
@@ -563,7 +567,7 @@ __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma(Dims d, con
   if constexpr (NX > 0)
     grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   else
-    grid_dft(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+    grid_dft<U>(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   for (int o = t; o < nk; o += nt) {
     cplx al = gl[o], ag = gg[o];
     cplx sl = czero(), sg = czero();
@@ -579,7 +583,7 @@ __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma(Dims d, con
   if constexpr (NX > 0)
     grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, -1, 1.0);
   else
-    grid_dft(d, gl, gg, tl, tg, twx, twy, -1, 1.0);
+    grid_dft<U>(d, gl, gg, tl, tg, twx, twy, -1, 1.0);
   for (int o = t; o < nk; o += nt) {
     cplx al = gl[o], ag = gg[o];
     sig[sig_idx(d, o, 0, ab, j)] = al;
@@ -599,7 +603,7 @@ __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma(Dims d, con
 __device__ __forceinline__ int64_t gr_idx(const Dims& d, int j, int comp, int ab, int R) {
   return (((int64_t)j * 2 + comp) * 4 + ab) * d.nk + R;
 }
-template <int NX, int NY>
+template <int NX, int NY, int U = 4>
 __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_fwd(Dims d, const cplx* __restrict__ row64, cplx* __restrict__ gR,
                                                    int m) {
   extern __shared__ cplx lds[];
@@ -639,13 +643,13 @@ __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_fwd(Dims d,
   if constexpr (NX > 0)
     grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   else
-    grid_dft(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
+    grid_dft<U>(d, gl, gg, tl, tg, twx, twy, +1, 1.0 / nk);
   for (int o = t; o < nk; o += nt) {
     gR[gr_idx(d, j, 0, ab, o)] = gl[o];
     gR[gr_idx(d, j, 1, ab, o)] = gg[o];
   }
 }
-template <int NX, int NY>
+template <int NX, int NY, int U = 4>
 __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_ib(Dims d, const cplx* __restrict__ gR, cplx* __restrict__ sig,
                                                   int m, double UU, int corr) {
   extern __shared__ cplx lds[];
@@ -685,7 +689,7 @@ __global__ __launch_bounds__((sigma_threads<NX, NY>())) void k_sigma_ib(Dims d, 
   if constexpr (NX > 0)
     grid_dft_ct<NX, NY, sigma_threads<NX, NY>()>(sl, sg, tl, tg, twx, twy, -1, 1.0);
   else
-    grid_dft(d, sl, sg, tl, tg, twx, twy, -1, 1.0);
+    grid_dft<U>(d, sl, sg, tl, tg, twx, twy, -1, 1.0);
   for (int o = t; o < nk; o += nt) {
     cplx vl = sl[o], vg = sg[o];
     sig[sig_idx(d, o, 0, ab, j)] = vl;
@@ -2877,10 +2881,16 @@ struct Launch {
     const size_t shm = (size_t)((pow2_chain(d.nkx, d.nky) ? 2 : 4) * d.nk + d.nkx + d.nky) * sizeof(cplx);
     // large grids: twice the threads (a block's LDS leaves room for one to three blocks per CU)
     const bool large = d.nk >= 512;
+    const int fit = (int)(163840 / shm);   // blocks whose LDS a CU holds
+    auto rounds = [&](int percu) {
+      const int held = 256 * (percu < fit ? percu : fit);
+      return (total + held - 1) / held;
+    };
+    const bool five = !large && rounds(5) < rounds(4);
     if constexpr (NB == 2) {
       if (a.interaction == KBE_DEV_INT_INTERBAND) {
-        auto fwd = k_sigma_fwd<0, 0>;
-        auto ib = k_sigma_ib<0, 0>;
+        auto fwd = five ? k_sigma_fwd<0, 0, 2> : k_sigma_fwd<0, 0>;
+        auto ib = five ? k_sigma_ib<0, 0, 2> : k_sigma_ib<0, 0>;
         if (d.nkx == 16 && d.nky == 1) {
           fwd = k_sigma_fwd<16, 1>;
           ib = k_sigma_ib<16, 1>;
@@ -2896,7 +2906,7 @@ struct Launch {
       }
     }
     // grids of the standard workloads with compile-time transforms, any other grid at run time
-    auto kern = k_sigma<NB, 0, 0>;
+    auto kern = five ? k_sigma<NB, 0, 0, 2> : k_sigma<NB, 0, 0>;
     int nthr = large ? 512 : 256;
     if (d.nkx == 24 && d.nky == 24) kern = k_sigma<NB, 24, 24>, nthr = sigma_threads<24, 24>();
     else if (d.nkx == 16 && d.nky == 16) kern = k_sigma<NB, 16, 16>, nthr = sigma_threads<16, 16>();
