@@ -36,8 +36,8 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 # nt, timed steps K); summary and commands in profiles/k_hist_pair_c2_sq24_nb2.md. Valid only for
 # the code it was measured on (SHA-1 of MEASURED_CODE below, comments removed); reported as null once
 # that code changes, or for a window that was not measured.
-MEASURED_TRAFFIC = {"bytes_per_launch": {("c2", 1000, 20): 3.72185e10, ("c2", 1000, 1000): 1.27624e10},
-                    "source_sha1": "3ad8fba0b1cbb58120d4e57c506abf7bbffccc05"}
+MEASURED_TRAFFIC = {"bytes_per_launch": {("c2", 1000, 20): 3.72189e10, ("c2", 1000, 1000): 1.27630e10},
+                    "source_sha1": "5d1f90c8c19e271f79e8386172b2ae07625ac080"}
 
 
 # What a history-sum launch reads and writes is decided by, as (file, from, up to; None: the file):

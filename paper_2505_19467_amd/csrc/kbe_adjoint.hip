@@ -593,8 +593,10 @@ __global__ __launch_bounds__(256) void k_adj_bulk(Dims d, const cplx* __restrict
 //   gbar^< = 2 c conj(g^<) g^> sbar^< + c g^>^2 conj(sbar^>),
 //   gbar^> = c g^<^2 conj(sbar^<) + 2 c conj(g^>) g^< sbar^>,
 //   Gbar(k) += N_k^{-1} F^- gbar,   dL/dU += sum Re conj(sbar) ds/dU,  ds/dU = 2 s / U.
-// NX, NY > 0: the grid is fixed at compile time (unrolled transforms, as in the forward kernel:
-// 42.0 -> 14.1 us on the 12 x 12 grid, m <= 400); 0: any grid, sizes from d.
+// NX, NY > 0: the grid is fixed at compile time (unrolled transforms, nb = 2 and the forward kernel's grids:
+// 42.0 -> 14.1 us on the 12 x 12 grid, m <= 400); 0: any grid, sizes from d. Averages over m <= 200, before
+// either and now: 12 x 12 31.3 -> 11.8 us, 24 x 24 57.3 -> 30.3, 16 points 17.5 -> 6.7; at run time 10 x 10
+// 26.9 -> 23.2, 14 x 14 34.0 -> 27.9, 20 x 20 43.7 -> 35.1, 20 points 18.1 -> 14.8.
 template <int NB, int NX, int NY>
 __global__ __launch_bounds__(256) void k_adj_sigma(Dims d, const cplx* __restrict__ row64,
                                                    const cplx* __restrict__ sbar, cplx* __restrict__ Rbar,

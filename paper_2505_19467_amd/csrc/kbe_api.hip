@@ -106,10 +106,15 @@ int make_layout(const kbe_config* c, Layout* L, std::string* why) {
   // interband self-energy: real-space lines of the current row, [t_j][comp][ab][R]
   sz[B_GR] = c->interaction == KBE_INT_INTERBAND ? (size_t)d.Tp * 2 * d.nbb * nk * cz : 0;
   // Column-sum slots, one per row segment: up to 24 (the most that blocks of 16 rows want on the
-  // smallest grids) and 32 MB in all, which leaves the large grids, whose blocks are not split, with
-  // one; and no more than keep a workspace that fits the allocation-free contexts' array within it.
-  // One-band contexts that the adjoint accepts keep one: their gradients vanish by particle
-  // conservation, so what a caller gets is the rounding residue of the sums in their order.
+  // smallest grids) and 32 MB in all, and no more than keep a workspace that fits the allocation-free
+  // contexts' array within it. The 32 MB bound the memory, not the time: a slot grows with nt_max, so a
+  // medium grid in a long run has one and its short passes stay unsplit (576 points, nb = 2: three slots at
+  // nt_max = 140, one from 224 on; FP32, unsplit against the best split 49 / 44 us at m = 64, 106 / 95 at
+  // m = 128, 172 / 168 at m = 200, none at 300; FP64 60 / 54, 156 / 146, 285 / 285); larger bounds were not
+  // measured in whole runs.
+  // One-band contexts that the adjoint accepts keep one: their gradients vanish by particle conservation,
+  // so what a caller gets is the rounding residue of the sums in their order, and that stays. The price is
+  // the split's gain in such a run (61 points, m = 200 / 300: 25.2 against 11.9 us, 35.4 against 20.4).
   size_t total = 0;
   for (int i = 0; i < B_COUNT; ++i) total += (sz[i] + 255) / 256 * 256;
   const size_t seg = sz[B_COLSUM];
